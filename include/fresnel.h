@@ -387,12 +387,8 @@ int propagate_train(fr_ctx *ctx, const fr_train_desc *desc, int32_t n_lambda,
  *     (rows per block, columns per tile) and the pass orders of the mixed-radix plan of n (the
  *     orders of its greedy radices and, for the per-wavelength grids of a broadband model, the
  *     plan of the register-resident sweeps, which is also their default);
- *   FR_TUNE_MFT, a = pupil-side edge n, b = focal edge m: the GEMM tile configuration and split-K
- *     factor of each of the two GEMMs of mft_forward (n -> m) and mft_adjoint (m -> n). Tiles
- *     0-3 form each complex k-step from four real products, tiles 4-5 from three (Gauss; the
- *     three sums are combined in float64 at every 32-deep group), tile 6 from four real products
- *     each summed from six products of exact bfloat16 pieces of the float32 operands on the
- *     bf16 matrix cores.
+ *   FR_TUNE_MFT, a = pupil-side edge n, b = focal edge m: the number of slices (split factor) in
+ *     which each of the two products of mft_forward (n -> m) and mft_adjoint (m -> n) is summed.
  * Every candidate computes the same result up to the order of float32 roundings. fr_autotune and
  * fr_autotune_load drop every recorded graph (fresnel_step_batched_graph, FR_TRAIN_GRAPH), after
  * waiting for the device, since a recording holds the kernel choices of its time. The call
@@ -403,8 +399,10 @@ int propagate_train(fr_ctx *ctx, const fr_train_desc *desc, int32_t n_lambda,
  * 1..64, or 0 = as many as fit the last-level cache together), "plan n packed_order" (radices
  * 2-10, 12, 14, 15 or 16, 5 bits each from the first pass up, at most 6, product n),
  * "gemm M N K transA transB tile [split]" or
- * "gemm_default tile split" per line; the default applies to GEMM shapes without their own line,
- * tile -1 restoring the choice by shape); a malformed or inconsistent line makes load return
+ * "gemm_default tile split" per line: an MFT product's output rows and columns, input length, 0 and
+ * 1 for a product along rows or 0 for one along columns, a tile number 0-6 that is kept but selects
+ * nothing (the tile follows from the shape) and the split factor, 0 = the choice by shape; the
+ * default, tile -1 for none, applies to products without their own line); a malformed or inconsistent line makes load return
  * FR_EINVAL (valid lines are still taken). */
 #define FR_TUNE_FRESNEL 1
 #define FR_TUNE_MFT 2

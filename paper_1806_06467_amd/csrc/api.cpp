@@ -96,8 +96,11 @@ int Ctx::sweep_variant(int n) const {
   return k;
 }
 
-Ctx::GemmChoice Ctx::gemm_choice(const CGemmArgs &g) const {
-  auto it = tuned_gemm.find({g.M, g.N, g.K, g.transA, g.transB});
+// a product's shape as the tuning file names it: output rows and columns, input length, and
+// (0, 1) for a product along the rows of the data, (0, 0) along its columns
+Ctx::GemmChoice Ctx::gemm_choice(const FoldArgs &g) const {
+  const int M = g.cols ? g.P : g.F, N = g.cols ? g.F : g.P;
+  auto it = tuned_gemm.find({M, N, g.Q, 0, g.cols ? 0 : 1});
   return it == tuned_gemm.end() ? default_gemm : it->second;
 }
 
@@ -338,26 +341,45 @@ int Ctx::direct_phases(int n, double dx, double lam, double z, double f, hipStre
   return st != FR_OK ? st : build(kpost, false, post);
 }
 
-// W[k][m] = exp(-2 pi i (k - M/2)(m - N/2) du / n_d), M x N row-major (or its transpose, N x M)
-int Ctx::mft_matrix(int m_out, int n_in, double n_d, double du, hipStream_t s, const float2 **out,
-                    bool transposed) {
-  TableKey key{kMft, m_out, uint64_t(n_in), bits(n_d), bits(du), transposed ? 1u : 0u};
+// float64 value as three bfloat16 pieces, each rounded to nearest even
+static void bf16_pieces(double x, uint16_t (&out)[3]) {
+  for (int q = 0; q < 3; ++q) {
+    const float f = float(x);
+    uint32_t u;
+    std::memcpy(&u, &f, sizeof u);
+    u = (u + 0x7fffu + ((u >> 16) & 1u)) & 0xffff0000u;
+    out[q] = uint16_t(u >> 16);
+    float back;
+    std::memcpy(&back, &u, sizeof back);
+    x -= double(back);
+  }
+}
+
+// cos and sin of 2 pi k j du / n_d over the positive halves of an output of length p and an input
+// of length q, in the layout of fold_table_bytes (fr_internal.h)
+int Ctx::mft_table(int p, int q, double n_d, double du, hipStream_t s, const void **out) {
+  TableKey key{kMft, p, uint64_t(q), bits(n_d), bits(du), 0};
   if (auto it = tables.find(key); it != tables.end()) {
-    *out = static_cast<const float2 *>(it->second);
+    *out = it->second;
     return FR_OK;
   }
-  std::vector<float2> h(size_t(m_out) * n_in);
-  const double coef = -du / n_d;
-  for (int k = 0; k < m_out; ++k) {
-    const long long a = k - m_out / 2;
-    for (int m = 0; m < n_in; ++m) {
-      const long long b = m - n_in / 2;
-      h[transposed ? size_t(m) * m_out + k : size_t(k) * n_in + m] = turn_to_c64(double(a * b) * coef, 1.0);
+  const int tiles = fold_tiles(p), steps = fold_steps(q);
+  std::vector<uint16_t> h(fold_table_bytes(p, q) / 2, 0);
+  const double coef = du / n_d;
+  for (int k = 1; k <= p / 2; ++k)
+    for (int j = 1; j <= q / 2; ++j) {
+      const double t = 2.0 * M_PI * frac_turn(double((long long)k * j) * coef);
+      const int tile = (k - 1) / 32, step = (j - 1) / 16, lane = (k - 1) % 32 + 32 * ((j - 1) % 16 / 8);
+      for (int par = 0; par < 2; ++par) {
+        uint16_t b[3];
+        bf16_pieces(par ? std::sin(t) : std::cos(t), b);
+        const size_t at = ((size_t(par) * tiles + tile) * steps + step) * 3;
+        for (int piece = 0; piece < 3; ++piece) h[((at + piece) * 64 + lane) * 8 + (j - 1) % 8] = b[piece];
+      }
     }
-  }
   void *d;
-  int st = upload(key, h.data(), h.size() * sizeof(float2), s, &d);
-  *out = static_cast<const float2 *>(d);
+  int st = upload(key, h.data(), h.size() * sizeof(uint16_t), s, &d);
+  *out = d;
   return st;
 }
 
@@ -418,84 +440,69 @@ size_t mft_ws_bytes(int n, int m) {
   return mft_t_bytes(n, m) + size_t(kMaxSplit) * size_t(n) * size_t(m) * 2 * sizeof(double);
 }
 
-static CGemmArgs gemm_args() {
-  CGemmArgs g;
+static FoldArgs fold_args(int F, int P, int Q, bool cols, double sign, const float2 *data, int ldd,
+                          const void *table, float2 *C, int ldc) {
+  FoldArgs g;
   std::memset(&g, 0, sizeof g);
-  g.alpha_re = 1.0;
+  g.F = F; g.P = P; g.Q = Q;
+  g.cols = cols ? 1 : 0;
+  g.sign = sign;
+  g.data = data; g.ldd = ldd;
+  g.table = table;
+  g.C = C; g.ldc = ldc;
+  g.alpha = 1.0;
   return g;
 }
 
-hipError_t run_gemm(Ctx *ctx, CGemmArgs &g, void *partial, size_t partial_elems, hipStream_t s, int cfg,
-                    int split) {
-  if (cfg < 0) {
-    const Ctx::GemmChoice c = ctx->gemm_choice(g);
-    cfg = c.tile;
-    split = c.split;
-  }
-  if (split <= 0) split = cgemm_split_for(g.M, g.N, g.K, cfg);
+hipError_t run_fold(Ctx *ctx, const FoldArgs &g, void *partial, size_t partial_elems, hipStream_t s, int split) {
+  if (split <= 0) split = ctx->gemm_choice(g).split;
+  if (split <= 0) split = fold_split_for(g);
   split = std::min(split, kMaxSplit);
-  while (split > 1 && size_t(split) * size_t(g.M) * size_t(g.N) > partial_elems) split /= 2;
-  return launch_cgemm_split(g, split, cfg, partial, s, ctx->hook());
+  while (split > 1 && size_t(split) * size_t(g.F) * size_t(g.P) > partial_elems) split /= 2;
+  return launch_fold(g, split, partial, s, ctx->hook());
 }
 
 int mft_forward_impl(Ctx *ctx, const float2 *in, int n_in, int ld_in, int m_out, double n_d,
                      double du, const MftOut &o, void *ws, hipStream_t s, size_t partial_cap) {
-  const float2 *w;
-  int st = ctx->mft_matrix(m_out, n_in, n_d, du, s, &w);
+  const void *w;
+  int st = ctx->mft_table(m_out, n_in, n_d, du, s, &w);
   if (st != FR_OK) return st;
   float2 *t = static_cast<float2 *>(ws);
   void *partial = static_cast<char *>(ws) + mft_t_bytes(n_in, m_out);
   const size_t pcap = std::min(size_t(kMaxSplit) * n_in * m_out, partial_cap);
   // T = E W^T  (n_in x m_out)
-  CGemmArgs g1 = gemm_args();
-  g1.M = n_in; g1.N = m_out; g1.K = n_in;
-  g1.A = in; g1.lda = ld_in;
-  g1.B = w; g1.ldb = n_in; g1.transB = 1;
-  g1.C = t; g1.ldc = m_out;
-  hipError_t e = run_gemm(ctx, g1, partial, pcap, s);
+  const FoldArgs g1 = fold_args(n_in, m_out, n_in, false, -1.0, in, ld_in, w, t, m_out);
+  hipError_t e = run_fold(ctx, g1, partial, pcap, s);
   if (e != hipSuccess) return record_hip(e);
   // out = (du / n_d) W T (* mask), optionally + weight |out|^2 into the intensity
-  CGemmArgs g2 = gemm_args();
-  g2.M = m_out; g2.N = m_out; g2.K = n_in;
-  g2.A = w; g2.lda = n_in;
-  g2.B = t; g2.ldb = m_out;
-  g2.C = o.out; g2.ldc = o.ld_out; g2.skip_c = o.skip_out ? 1 : 0;
-  g2.alpha_re = du / n_d;
+  FoldArgs g2 = fold_args(m_out, m_out, n_in, true, -1.0, t, m_out, w, o.out, o.ld_out);
+  g2.skip_c = o.skip_out ? 1 : 0;
+  g2.alpha = du / n_d;
   g2.mask = o.mask; g2.ldm = m_out;
   g2.intensity = o.intensity; g2.ldi = m_out; g2.weight = o.weight;
-  e = run_gemm(ctx, g2, partial, pcap, s);
+  e = run_fold(ctx, g2, partial, pcap, s);
   return e == hipSuccess ? FR_OK : record_hip(e);
 }
 
 int mft_adjoint_impl(Ctx *ctx, const float2 *in, int m_in, int ld_in, float2 *out, int n_out,
                      int ld_out, double n_d, double du, float alpha, float beta,
                      const float2 *cin, int ld_cin, const float *mask, void *ws, hipStream_t s) {
-  // with Wt = W^T (n_out x m_in): conj(W) = conj(Wt)^T and W^H = conj(Wt), so both GEMMs read
-  // the matrix with k contiguous
-  const float2 *wt;
-  int st = ctx->mft_matrix(m_in, n_out, n_d, du, s, &wt, true);
+  const void *w;
+  int st = ctx->mft_table(n_out, m_in, n_d, du, s, &w);
   if (st != FR_OK) return st;
   float2 *t = static_cast<float2 *>(ws);
   void *partial = static_cast<char *>(ws) + mft_t_bytes(n_out, m_in);
   const size_t pcap = size_t(kMaxSplit) * n_out * m_in;
-  // T = E_B conj(W) = E_B conj(Wt)^T  (m_in x n_out)
-  CGemmArgs g1 = gemm_args();
-  g1.M = m_in; g1.N = n_out; g1.K = m_in;
-  g1.A = in; g1.lda = ld_in;
-  g1.B = wt; g1.ldb = m_in; g1.transB = 1; g1.conjB = 1;
-  g1.C = t; g1.ldc = n_out;
-  hipError_t e = run_gemm(ctx, g1, partial, pcap, s);
+  // T = E_B conj(W)  (m_in x n_out)
+  const FoldArgs g1 = fold_args(m_in, n_out, m_in, false, 1.0, in, ld_in, w, t, n_out);
+  hipError_t e = run_fold(ctx, g1, partial, pcap, s);
   if (e != hipSuccess) return record_hip(e);
-  // out = alpha (du / n_d) conj(Wt) T + beta cin (* mask)
-  CGemmArgs g2 = gemm_args();
-  g2.M = n_out; g2.N = n_out; g2.K = m_in;
-  g2.A = wt; g2.lda = m_in; g2.conjA = 1;
-  g2.B = t; g2.ldb = n_out;
-  g2.C = out; g2.ldc = ld_out;
-  g2.alpha_re = double(alpha) * (du / n_d);
+  // out = alpha (du / n_d) W^H T + beta cin (* mask)
+  FoldArgs g2 = fold_args(n_out, n_out, m_in, true, 1.0, t, n_out, w, out, ld_out);
+  g2.alpha = double(alpha) * (du / n_d);
   g2.beta = beta; g2.Cin = cin; g2.ldcin = ld_cin;
   g2.mask = mask; g2.ldm = n_out;
-  e = run_gemm(ctx, g2, partial, pcap, s);
+  e = run_fold(ctx, g2, partial, pcap, s);
   return e == hipSuccess ? FR_OK : record_hip(e);
 }
 

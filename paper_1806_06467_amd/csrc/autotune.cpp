@@ -5,8 +5,8 @@
 // Candidates (all compute the same result up to float32 rounding order):
 //   Fresnel plane of edge n: the tile variants of the power-of-two sweeps (row lines per block,
 //     column tile width) and the distinct pass orders of the mixed-radix plan;
-//   MFT n <-> m: the GEMM tile configurations (64 x 64, 64 x 128, 128 x 128) of the two GEMMs
-//     of the forward and of the adjoint transform.
+//   MFT n <-> m: the number of slices that each of the two products of the forward and of the
+//     adjoint transform is summed in.
 // Each candidate runs once untimed, then kReps times between events; the minimum counts.
 #include <hip/hip_runtime.h>
 
@@ -133,48 +133,44 @@ int tune_mft(Ctx *ctx, int n, int m, hipStream_t s) {
   Scratch mem;
   const size_t big = size_t(std::max(n, m)) * std::max(n, m);
   float2 *a = static_cast<float2 *>(mem.get(big * sizeof(float2), s));
-  float2 *w = static_cast<float2 *>(mem.get(size_t(n) * m * sizeof(float2), s));
   float2 *t = static_cast<float2 *>(mem.get(size_t(n) * m * sizeof(float2), s));
   float2 *c = static_cast<float2 *>(mem.get(big * sizeof(float2), s));
+  void *wf = mem.get(fold_table_bytes(m, n), s), *wa = mem.get(fold_table_bytes(n, m), s);
   const size_t pcap = size_t(kMaxSplit) * n * m;
   void *partial = mem.get(pcap * 2 * sizeof(double), s);
-  if (!a || !w || !t || !c || !partial) return FR_ENOMEM;
-  // the four GEMM shapes of mft_forward(n -> m) and mft_adjoint(m -> n)
-  std::vector<CGemmArgs> shapes;
-  auto add = [&](int M, int N, int K, const float2 *A, int lda, int ta, const float2 *B, int ldb, int tb,
-                 float2 *C, int ldc) {
-    CGemmArgs g;
+  if (!a || !t || !c || !wf || !wa || !partial) return FR_ENOMEM;
+  // the four products of mft_forward(n -> m) and mft_adjoint(m -> n)
+  std::vector<FoldArgs> shapes;
+  auto add = [&](int F, int P, int Q, int cols, const float2 *data, int ldd, const void *table, float2 *C, int ldc) {
+    FoldArgs g;
     std::memset(&g, 0, sizeof g);
-    g.M = M, g.N = N, g.K = K;
-    g.A = A, g.lda = lda, g.transA = ta;
-    g.B = B, g.ldb = ldb, g.transB = tb;
+    g.F = F, g.P = P, g.Q = Q, g.cols = cols, g.sign = 1.0;
+    g.data = data, g.ldd = ldd, g.table = table;
     g.C = C, g.ldc = ldc;
-    g.alpha_re = 1.0;
+    g.alpha = 1.0;
     shapes.push_back(g);
   };
-  add(n, m, n, a, n, 0, w, n, 1, t, m);  // forward: T = E W^T
-  add(m, m, n, w, n, 0, t, m, 0, c, m);  // forward: W T
-  add(m, n, m, a, m, 0, w, m, 1, t, n);  // adjoint: E_B conj(Wt)^T (Wt = W^T, n x m)
-  add(n, n, m, w, m, 0, t, n, 0, c, n);  // adjoint: conj(Wt) T
-  for (CGemmArgs &g : shapes) {
-    Ctx::GemmChoice best{0, 0};
+  add(n, m, n, 0, a, n, wf, t, m);  // forward: T = E W^T
+  add(m, m, n, 1, t, m, wf, c, m);  // forward: W T
+  add(m, n, m, 0, a, m, wa, t, n);  // adjoint: E_B conj(W)
+  add(n, n, m, 1, t, n, wa, c, n);  // adjoint: W^H T
+  for (const FoldArgs &g : shapes) {
+    int best = 0;
     float best_ms = -1.f;
-    for (int cfg = 0; cfg < kGemmTiles; ++cfg) {
-      // the tile's default split, and every power of two up to kMaxSplit that leaves slices of
-      // at least 64 (the default is tried first, so it wins ties)
-      std::vector<int> splits{0};
-      for (int sp = 1; sp <= kMaxSplit && g.K / sp >= 64; sp *= 2)
-        if (size_t(sp) * size_t(g.M) * size_t(g.N) <= pcap) splits.push_back(sp);
-      for (int sp : splits) {
-        const float ms = time_min(s, [&] { return run_gemm(ctx, g, partial, pcap, s, cfg, sp); });
-        if (ms < 0.f) return record_hip(hipGetLastError());
-        if (best_ms < 0.f || ms < best_ms) {
-          best_ms = ms;
-          best = {cfg, sp};
-        }
+    // the default split, and every power of two up to kMaxSplit that leaves slices of at least
+    // 64 pairs (the default is tried first, so it wins ties)
+    std::vector<int> splits{fold_split_for(g)};
+    for (int sp = 1; sp <= kMaxSplit && g.Q / 2 / sp >= 64; sp *= 2)
+      if (size_t(sp) * size_t(g.F) * size_t(g.P) <= pcap) splits.push_back(sp);
+    for (int sp : splits) {
+      const float ms = time_min(s, [&] { return run_fold(ctx, g, partial, pcap, s, sp); });
+      if (ms < 0.f) return record_hip(hipGetLastError());
+      if (best_ms < 0.f || ms < best_ms) {
+        best_ms = ms;
+        best = sp;
       }
     }
-    ctx->tuned_gemm[{g.M, g.N, g.K, g.transA, g.transB}] = best;
+    ctx->tuned_gemm[{g.cols ? g.P : g.F, g.cols ? g.F : g.P, g.Q, 0, g.cols ? 0 : 1}] = {0, best};
   }
   return record_hip(hipStreamSynchronize(s));
 }

@@ -113,41 +113,43 @@ hipError_t launch_mr_batch(const MrBatch &all, const int *rows_per_cu, const int
 constexpr int kMrPolicies = 8;
 void mr_resident(int *rows_per_cu, int *cols_per_cu);
 
-// ---- MFT: out = alpha * c * A in B^T (+ beta * out) (* mask), complex, FP32 MFMA ------
-// Generic complex GEMM pieces used by the MFT entry points.
-struct CGemmArgs {
-  int M, N, K;
-  const float2 *A;  // M x K, row stride lda
-  int lda;
-  const float2 *B;  // K x N (or its transpose), row stride ldb
-  int ldb;
-  float2 *C;        // M x N, row stride ldc
+// ---- MFT: one product with the Fourier matrix, folded about its axis, on MFMA ------------
+// out(a) = alpha sum_b in(b) exp(sign 2 pi i a b c) (+ beta Cin) (* mask) along one axis of the
+// data, a and b signed indices about P/2 and Q/2; the other axis is free.
+struct FoldArgs {
+  int F, P, Q;         // free indices, output length, input length
+  int cols;            // 0: along each row (data F x Q, out F x P); 1: along each column (Q x F, P x F)
+  double sign;         // -1 (W) or +1 (conj(W))
+  const float2 *data;  // row stride ldd
+  int ldd;
+  const void *table;   // fold_table_build(P, Q, c)
+  float2 *C;           // row stride ldc
   int ldc;
-  int transA;       // 1: A is given as K x M (use A^T)
-  int transB;       // 1: B is given as N x K (use B^T)
-  int conjA, conjB; // conjugate the operand on load
-  double alpha_re, alpha_im;  // applied in float64 in the epilogue
-  float beta;       // real; the beta term reads Cin (row stride ldcin), or C when Cin is null
+  double alpha;        // applied in float64 in the epilogue
+  float beta;          // the beta term reads Cin (row stride ldcin), or C when Cin is null
   const float2 *Cin;
   int ldcin;
-  const float *mask;  // M x N (row stride ldm) or null: multiplies the result
+  const float *mask;   // like the output (row stride ldm) or null: multiplies the result
   int ldm;
-  double *intensity;  // M x N (row stride ldi) or null: intensity += weight |result|^2 (float64)
+  double *intensity;   // like the output (row stride ldi) or null: intensity += weight |result|^2 (float64)
   int ldi;
   double weight;
-  int skip_c;         // 1: do not write C (only the intensity)
+  int skip_c;          // 1: do not write C (only the intensity)
 };
-// C = alpha op(A) op(B) (+ beta C) (* mask). split > 1 slices K; the slices' partial sums go
-// to `partial` (split x M x N complex float64, 16-byte aligned) and are added in a fixed order
-// by a second kernel.
+// The table: bfloat16 pieces of cos (parity 0) and sin (parity 1) of 2 pi k j c, k = 1 .. P/2,
+// j = 1 .. Q/2, as MFMA fragments [parity][tile of 32 k][step of 16 j][piece][lane][8]: lane l
+// holds k = l % 32 of the tile, j = 8 (l / 32) .. + 7 of the step; zero past P/2 and Q/2. The
+// steps are padded to whole stages of four.
+__host__ __device__ inline int fold_tiles(int P) { return (P / 2 + 31) / 32 > 0 ? (P / 2 + 31) / 32 : 1; }
+__host__ __device__ inline int fold_steps(int Q) { return (Q / 2 + 63) / 64 > 0 ? (Q / 2 + 63) / 64 * 4 : 4; }
+inline size_t fold_table_bytes(int P, int Q) { return size_t(2) * fold_tiles(P) * fold_steps(Q) * 3 * 64 * 8 * 2; }
+// split > 1 slices the pairs; the slices' partial sums go to `partial` (split x output complex
+// float64, 16-byte aligned) and are added in a fixed order by a second kernel.
 constexpr int kMaxSplit = 16;
-// cfg: tile configuration (0 small 64 x 64, 1 large 64 x 128, 2 extra large 128 x 128, 3 small
-// with two stages of operand loads in flight, 4 small and 5 large with three real products per
-// complex step, 6 small with the four real products formed from bfloat16 pieces of the
-// operands on the bf16 matrix cores), or -1 for the default choice by shape
+// tile numbers a tuning file may carry (they name complex tiles that the folded product, which
+// picks its tile by shape, has replaced; the split factor beside them is used)
 constexpr int kGemmTiles = 7;
-int cgemm_split_for(int M, int N, int K, int cfg);
-hipError_t launch_cgemm_split(const CGemmArgs &a, int split, int cfg, void *partial, hipStream_t stream,
-                              const LaunchHook &hook);
+int fold_split_for(const FoldArgs &a);
+hipError_t launch_fold(const FoldArgs &a, int split, void *partial, hipStream_t stream, const LaunchHook &hook);
 
 }  // namespace fr

@@ -94,13 +94,12 @@ struct Ctx {
   };
   std::map<std::tuple<int, int, int, int, int>, GemmChoice> tuned_gemm;  // (M, N, K, transA, transB)
   GemmChoice default_gemm{-1, 0};  // for shapes without an entry (tile -1: chosen by shape)
-  GemmChoice gemm_choice(const CGemmArgs &g) const;
+  GemmChoice gemm_choice(const FoldArgs &g) const;
   int transfer(int n, double dx, double lam, double z, hipStream_t s, const float2 **out);
   int lens(int n, double dx, double lam, double f, hipStream_t s, const float2 **out);
   int direct_phases(int n, double dx, double lam, double z, double f, hipStream_t s, const float2 **pre,
                     const float2 **post, bool inverse = false);
-  int mft_matrix(int m_out, int n_in, double n_d, double du, hipStream_t s, const float2 **out,
-                 bool transposed = false);
+  int mft_table(int p, int q, double n_d, double du, hipStream_t s, const void **out);
   int dm_influence(int n, int n_d, int n_act, hipStream_t s, const float **out);
   // the rows [lo, hi) of that table with a nonzero entry (the Gaussians underflow float32 to
   // exactly 0 beyond about 14.4 actuator pitches from the outermost actuators); host arithmetic
@@ -120,11 +119,9 @@ struct MftOut {
   double weight = 0.0;
   bool skip_out = false;
 };
-// one complex GEMM with the tuned (or, cfg >= 0, the given) tile configuration and a split-K
-// that fits `partial_elems` float64 complex partial sums
-// split > 0 forces that many K slices (at most kMaxSplit, reduced to fit partial_elems)
-hipError_t run_gemm(Ctx *ctx, CGemmArgs &g, void *partial, size_t partial_elems, hipStream_t s, int cfg = -1,
-                    int split = 0);
+// one folded product with the tuned (or, split > 0, the given) number of slices, at most kMaxSplit
+// and reduced to fit `partial_elems` float64 complex partial sums
+hipError_t run_fold(Ctx *ctx, const FoldArgs &g, void *partial, size_t partial_elems, hipStream_t s, int split = 0);
 // partial_cap: float64 complex split-K partial sums that fit ws after the n_in x m_out product
 // (the split factor is reduced to fit; 0 runs every GEMM unsplit)
 int mft_forward_impl(Ctx *ctx, const float2 *in, int n_in, int ld_in, int m_out, double n_d,

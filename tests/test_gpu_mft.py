@@ -153,3 +153,19 @@ def test_bfloat16_split_tile_on_8192_field(tmp_path):
         got = to_np(fb.mft_forward(to_gpu(e), nd, m, du))
     ref = oracle.mft(f32(e), nd, m, du)
     assert rel_l2(got, ref) <= TOL
+
+
+# edges of the folded products: lengths 1 to 3 (no pair, an unpaired first element), 63 / 64 / 65
+# outputs and 127 to 130 inputs (32-wide tiles, 64-pair stages, odd and even), several stages
+@pytest.mark.parametrize("n,m", [(1, 1), (2, 3), (3, 2), (64, 65), (65, 64), (127, 63), (128, 129), (129, 128),
+                                 (130, 257), (258, 130), (385, 66), (1030, 34)])
+def test_folded_products_at_tile_edges(n, m):
+    # float32 roundings in a row: the fold and the product T of each axis, the result, the matrix
+    # pieces (2^-25 and 2^-23 left out) and eight float32 sums per 128 pairs: below 24 x 2^-24
+    banner(f"folded mft {n} <-> {m}")
+    n_d, du = max(1.0, 0.4 * n), 0.37
+    e, eb = synth.random_field(n, n + m), synth.random_field(m, n + m + 1)
+    got = to_np(fb.mft_forward(to_gpu(e), n_d, m, du))
+    assert rel_l2(got, oracle.mft(f32(e), n_d, m, du)) <= 1.5e-6
+    got = to_np(fb.mft_adjoint(to_gpu(eb), n_d, n, du))
+    assert rel_l2(got, oracle.mft_adjoint(f32(eb), n_d, n, du)) <= 1.5e-6
