@@ -1,11 +1,11 @@
 // The matrix Fourier transform in float64 (Sec. 1.1, after Soummer et al.; Sec. 2.3 for the
 // precision the paper benchmarks): out = (du / n_d) W in W^T and its adjoint
-// (du / n_d) W^H in conj(W), as two complex GEMMs in float64 on the matrix cores (on gfx950 their
-// dense float64 peak, 78.6 TFLOP/s, equals the vector units'; the matrix-core tile reads each
-// operand from LDS once per 16 x 16 x 4 product instead of once per multiply-add, and leaves the
-// vector units free for the loads).
+// (du / n_d) W^H in conj(W), each as two products along one axis, folded about it and formed in
+// float64 on the matrix cores (on gfx950 their dense float64 peak, 78.6 TFLOP/s, equals the vector
+// units').
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <vector>
@@ -20,154 +20,233 @@ struct z64 {
   double x, y;
 };
 
-constexpr int kDepth = 16;
-
-// C[i][j] = s sum_k A(i, k) B(k, j). A(i, k) = a[i lda + k] (or a[k lda + i] when TA), conjugated
-// when CA; B(k, j) = b[k ldb + j] (or b[j ldb + k] when TB), conjugated when CB. Split K:
-// blockIdx.z takes k in [z kc, (z + 1) kc) and writes its partial C at c + z c_split. A may be
-// the ordered sum of sa partial matrices a_split apart (the previous product's split-K slices).
-// On the float64 matrix cores: a 256-thread block forms a 64 x 64 tile of C from 16-deep slices of
-// A and B staged in LDS (the next slice read into registers while the current one is
-// multiplied), each wave a 32 x 32 piece as 2 x 2 blocks of 16 x 16, every complex k-step of 4 as
-// four real v_mfma_f64_16x16x4 per block (Cr += Ar Br - Ai Bi, Ci += Ar Bi + Ai Br). Fragment
-// layouts (checked on gfx950 with one-hot operands): lane l holds A[l % 16][l / 16] and
-// B[l / 16][l % 16] of the 16 x 4 and 4 x 16 operands, and item r of the result
-// D[4 r + l / 16][l % 16].
 typedef double d4 __attribute__((ext_vector_type(4)));
+typedef double d2 __attribute__((ext_vector_type(2)));
 
-// At most three waves per SIMD (170 registers; left alone the compiler takes 144 + 64
-// accumulation registers, which allow two): 0.61 ms against 0.66 ms for the occulter MFT's
-// first product; four waves spill and run slower.
-template <bool TA, bool CA, bool TB, bool CB>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) zgemm_mfma_kernel(const z64 *__restrict__ a, int lda,
-                                                         const z64 *__restrict__ b, int ldb, z64 *__restrict__ c,
-                                                         int ldc, int M, int N, int K, double s, int kc,
-                                                         size_t c_split, int sa, size_t a_split) {
-  constexpr int TM = 64, TN = 64, R = TM * kDepth / 256, Q = TN * kDepth / 256;
-  __shared__ z64 As[kDepth][TM + 1];
-  __shared__ z64 Bs[kDepth][TN + 1];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1;
-  const int i0 = blockIdx.y * TM, j0 = blockIdx.x * TN;
-  d4 cr[2][2], ci[2][2];
+constexpr int kFree = 32;      // free indices (rows or columns of the data) per block
+constexpr int kStage = 32;     // pairs per stage
+constexpr int kThreads = 256;  // four waves
+
+struct ZFold {
+  int F, P, Q;       // free indices, output length, input length
+  double sign;       // -1 (W) or +1 (conj(W))
+  const z64 *data;   // row stride ldd
+  int ldd;
+  const d2 *table;   // ztable_bytes
+  z64 *out;          // split == 1: the output (rows of ldc); else partials of ldc x rows each
+  int ldc;
+  double scale;
+  int j_per_split;   // pairs per slice, a multiple of kStage
+  size_t split_stride;
+};
+
+// cosines (parity 0) and sines (parity 1) of 2 pi k j du / n_d, k = 1 .. P/2, j = 1 .. Q/2, as
+// MFMA fragments [parity][tile of 32 k][step of 8 j][16 k][lane][2]: lane l holds k = l % 16 and
+// j = l / 16 and l / 16 + 4 of the step; zero past P/2 and Q/2, the steps padded to whole stages
+__host__ __device__ inline int ztiles(int P) { return P / 2 > 0 ? (P / 2 + 31) / 32 : 1; }
+__host__ __device__ inline int zsteps(int Q) { return Q / 2 > 0 ? (Q / 2 + kStage - 1) / kStage * 4 : 4; }
+
+// One product with the Fourier matrix along one axis, folded about it: with P(j) = in(j) + in(-j)
+// and M(j) = in(j) - in(-j), out(+-k) = in(0) + sum_j P(j) cos(2 pi k j du / n_d)
+// +- i sign sum_j M(j) sin(2 pi k j du / n_d), j = 1 .. Q/2, k = 1 .. P/2, a quarter of the complex
+// product's operations, and out(0) = in(0) + sum_j P(j).
+//
+// Bound by the float64 matrix cores (a 16 x 16 x 4 product holds its SIMD's unit for 64 cycles;
+// the folds, the LDS and the loads need far less). A block of four waves forms 32 free indices by
+// KT * 32 positive outputs (both signs): each wave one parity, a 32 x 32 tile and, for KT = 1, one
+// half of every stage's pairs (added in the epilogue); 68 KiB of LDS and under 256 registers, so
+// two blocks share a compute unit and one's loads, folds and stores overlap the other's products.
+// Stages are double-buffered in LDS: the next stage's data and matrix fragments are on their way
+// while the current one is multiplied. COLS: the transform runs along the columns (the free index
+// is the column), so the tile is transposed by swapping the MFMA operands. Fragment layouts
+// (checked on gfx950 with one-hot operands): lane l holds A[l % 16][l / 16] and B[l / 16][l % 16]
+// of the 16 x 4 and 4 x 16 operands, and item r of the result D[4 r + l / 16][l % 16].
+// Measured (MI355X, 4096^2 -> 256^2 and back): 1198 us as complex products of 64 x 64 tiles, 409 us
+// folded (the long products 223 us and 204 us, 38 and 42 TFLOP/s on the folded operations).
+template <int KT, bool COLS>
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) zfold_kernel(ZFold a) {
+  constexpr int KS = 2 / KT;
+  constexpr int STEPS = 4 / KS;  // 8-deep steps per wave and stage
+  constexpr int kVal = kFree * kStage;
+  // [buffer][P.re, P.im, M.re, M.im][pair][free index, xored with the pair's low four bits so that
+  // stores along the pairs spread over the banks]; later the waves' sums, [wave][item][lane]
+  __shared__ double lds[2 * 4 * kVal];
+  __shared__ z64 zs[8 * kFree];
+  static_assert(sizeof(lds) >= 4 * 16 * 64 * sizeof(z64), "the exchange fits the stage buffers");
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int par = wave & 1, kt = KT == 2 ? wave >> 1 : 0, ks = KT == 2 ? 0 : wave >> 1;
+  // an XCD's blocks walk a contiguous range of tiles, eight tiles of free indices at a time and all
+  // their output tiles, so that they share the data in its L2
+  const int gx = gridDim.x, gy = gridDim.y, total = gx * gy * gridDim.z;
+  const int lin = blockIdx.x + gx * (blockIdx.y + gy * blockIdx.z);
+  const int tile = total % 8 == 0 ? (lin & 7) * (total >> 3) + (lin >> 3) : lin;
+  const int bz = tile / (gx * gy), in_z = tile % (gx * gy);
+  const int grp = in_z / (8 * gx), rows_g = min(8, gy - grp * 8), u = in_z % (8 * gx);
+  const int bx = u / rows_g, f0 = (grp * 8 + u % rows_g) * kFree;
+
+  const int half = a.Q / 2, full_pairs = a.Q - 1 - half;
+  const int jbeg = bz * a.j_per_split, jend = min(half, jbeg + a.j_per_split);
+  const int nst = jend > jbeg ? (jend - jbeg + kStage - 1) / kStage : 0;
+  const bool zero_tile = bx == 0;
+
+  // four (free index, pair) items per thread and stage, 8 apart in the index the lanes do not walk
+  const ptrdiff_t step = COLS ? a.ldd : 1, fstep = COLS ? 1 : a.ldd;
+  const int walk = tid & 31, other = tid >> 5;
+  z64 p[4], m[4], zero[COLS ? 1 : 4];
 #pragma unroll
-  for (int ib = 0; ib < 2; ++ib)
+  for (int i = 0; i < (COLS ? 1 : 4); ++i) zero[i] = {0.0, 0.0};
+  auto load = [&](int j0) {
 #pragma unroll
-    for (int jb = 0; jb < 2; ++jb) cr[ib][jb] = ci[ib][jb] = d4{0.0, 0.0, 0.0, 0.0};
-  const int kbeg = blockIdx.z * kc, kend = min(K, kbeg + kc);
-  c += blockIdx.z * c_split;
-  const int fr = lane & 15, fk = lane >> 4;  // fragment row (column) and k within a 4-deep step
-  // the next slice's operands are read into registers while the current one is multiplied
-  z64 va[R], vb[Q];
-  auto fetch = [&](int k0) {
+    for (int i = 0; i < 4; ++i) {
+      const int lf = COLS ? walk : other + 8 * i, j = j0 + (COLS ? other + 8 * i : walk) + 1;
+      const z64 *c = a.data + half * step + min(f0 + lf, a.F - 1) * fstep;
+      p[i] = j <= full_pairs ? c[j * step] : z64{0.0, 0.0};
+      m[i] = j <= half ? c[-j * step] : z64{0.0, 0.0};
+    }
+  };
+  auto put = [&](int buf, bool count) {
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int e = tid + 256 * r;
-      int i, k;
-      if constexpr (TA) { i = e % TM; k = e / TM; } else { k = e % kDepth; i = e / kDepth; }
-      va[r] = {0.0, 0.0};
-      if (i0 + i < M && k0 + k < kend) {
-        const size_t at = TA ? size_t(k0 + k) * lda + (i0 + i) : size_t(i0 + i) * lda + (k0 + k);
-        va[r] = a[at];
-        for (int p = 1; p < sa; ++p) {
-          const z64 w = a[p * a_split + at];
-          va[r].x += w.x;
-          va[r].y += w.y;
-        }
+    for (int i = 0; i < 4; ++i) {
+      const int lf = COLS ? walk : other + 8 * i, j = COLS ? other + 8 * i : walk;
+      double *d = lds + buf * 4 * kVal + j * kFree + (lf ^ (j & 15));
+      const double sx = p[i].x + m[i].x, sy = p[i].y + m[i].y;
+      d[0] = sx;
+      d[kVal] = sy;
+      d[2 * kVal] = p[i].x - m[i].x;
+      d[3 * kVal] = p[i].y - m[i].y;
+      if (count && zero_tile) {
+        zero[COLS ? 0 : i].x += sx;
+        zero[COLS ? 0 : i].y += sy;
       }
     }
-#pragma unroll
-    for (int q = 0; q < Q; ++q) {
-      const int e = tid + 256 * q;
-      int j, kb;
-      if constexpr (TB) { kb = e % kDepth; j = e / kDepth; } else { j = e % TN; kb = e / TN; }
-      vb[q] = {0.0, 0.0};
-      if (j0 + j < N && k0 + kb < kend)
-        vb[q] = TB ? b[size_t(j0 + j) * ldb + (k0 + kb)] : b[size_t(k0 + kb) * ldb + (j0 + j)];
-    }
   };
-  auto put = [&] {
+  const int tiles = ztiles(a.P), steps = zsteps(a.Q), out_half = a.P / 2;
+  const int ktile = bx * KT + kt;
+  const d2 *tab = a.table + (size_t(par) * tiles + min(ktile, tiles - 1)) * steps * 128 + lane;
+  d2 tc[STEPS][2], tn[STEPS][2];
+  auto load_tab = [&](d2 (&t)[STEPS][2], int s) {
+    const int st = jbeg / 8 + s * 4 + ks * STEPS;
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int e = tid + 256 * r;
-      int i, k;
-      if constexpr (TA) { i = e % TM; k = e / TM; } else { k = e % kDepth; i = e / kDepth; }
-      z64 v = va[r];
-      if constexpr (CA) v.y = -v.y;
-      As[k][i] = v;
-    }
+    for (int q = 0; q < STEPS; ++q)
 #pragma unroll
-    for (int q = 0; q < Q; ++q) {
-      const int e = tid + 256 * q;
-      int j, kb;
-      if constexpr (TB) { kb = e % kDepth; j = e / kDepth; } else { j = e % TN; kb = e / TN; }
-      z64 v = vb[q];
-      if constexpr (CB) v.y = -v.y;
-      Bs[kb][j] = v;
-    }
+      for (int h = 0; h < 2; ++h) t[q][h] = tab[(size_t(st + q) * 2 + h) * 64];
   };
-  if (kbeg < kend) {
-    fetch(kbeg);
-    put();
+  d4 re[2][2], im[2][2];  // [16 free indices][16 outputs]
+#pragma unroll
+  for (int i = 0; i < 4; ++i) re[i >> 1][i & 1] = im[i >> 1][i & 1] = d4{0.0, 0.0, 0.0, 0.0};
+  auto mm = [](double d, double t, d4 c) {
+    if constexpr (COLS) return __builtin_amdgcn_mfma_f64_16x16x4f64(t, d, c, 0, 0, 0);
+    else return __builtin_amdgcn_mfma_f64_16x16x4f64(d, t, c, 0, 0, 0);
+  };
+  const int fl = lane & 15, fk = lane >> 4;
+  if (nst > 0) {
+    load_tab(tc, 0);
+    load(jbeg);
+    put(0, true);
+    __syncthreads();
+    for (int s = 0; s < nst; ++s) {
+      // the last stage loads and stores itself again, to a buffer nobody reads
+      const int next = min(s + 1, nst - 1);
+      load_tab(tn, next);
+      load(jbeg + next * kStage);
+      const double *src = lds + (s & 1) * 4 * kVal + 2 * par * kVal;
+#pragma unroll
+      for (int q = 0; q < STEPS; ++q)
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          const int j = ((ks * STEPS + q) * 2 + e) * 4 + fk;
+          double dr[2], di[2];
+#pragma unroll
+          for (int ft = 0; ft < 2; ++ft) {
+            const double *d = src + j * kFree + ft * 16 + (fl ^ (j & 15));
+            dr[ft] = d[0];
+            di[ft] = d[kVal];
+          }
+#pragma unroll
+          for (int ft = 0; ft < 2; ++ft)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+              re[ft][h] = mm(dr[ft], tc[q][h][e], re[ft][h]);
+              im[ft][h] = mm(di[ft], tc[q][h][e], im[ft][h]);
+            }
+        }
+      put((s & 1) ^ 1, s + 1 < nst);
+#pragma unroll
+      for (int q = 0; q < STEPS; ++q)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) tc[q][h] = tn[q][h];
+      __syncthreads();
+    }
+  }
+
+  // exchange: every wave's sums, then each wave of a tile (2 parities x KS halves) forms both signs
+  // of its share of the tile's outputs. Item t = (16 free indices, 16 outputs, r).
+  z64 *ex = reinterpret_cast<z64 *>(lds);
+  __syncthreads();
+#pragma unroll
+  for (int t = 0; t < 16; ++t)
+    ex[(wave * 16 + t) * 64 + lane] = {re[t >> 3][(t >> 2) & 1][t & 3], im[t >> 3][(t >> 2) & 1][t & 3]};
+  if (zero_tile) {
+    if constexpr (COLS) {
+      zs[other * kFree + walk] = zero[0];
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        for (int o = 16; o > 0; o >>= 1) {
+          zero[i].x += __shfl_xor(zero[i].x, o);
+          zero[i].y += __shfl_xor(zero[i].y, o);
+        }
+        if (walk == 0) zs[other + 8 * i] = zero[i];
+      }
+    }
   }
   __syncthreads();
-  for (int k0 = kbeg; k0 < kend; k0 += kDepth) {
-    const bool more = k0 + kDepth < kend;
-    if (more) fetch(k0 + kDepth);
+  z64 *out = a.out + bz * a.split_stride;
+  auto emit = [&](int o, int f, double x, double y) {
+    out[COLS ? size_t(o) * a.ldc + f : size_t(f) * a.ldc + o] = {a.scale * x, a.scale * y};
+  };
+  auto in0 = [&](int f) { return bz == 0 ? a.data[half * step + f * fstep] : z64{0.0, 0.0}; };
+  constexpr int SHARE = 16 / (2 * KS);
 #pragma unroll
-    for (int k4 = 0; k4 < kDepth; k4 += 4) {
-      double ar[2], ai[2], nai[2], br[2], bi[2];
+  for (int tt = 0; tt < SHARE; ++tt) {
+    const int t = (par * KS + ks) * SHARE + tt;
+    z64 c = {0.0, 0.0}, sn = {0.0, 0.0};
 #pragma unroll
-      for (int ib = 0; ib < 2; ++ib) {
-        const z64 v = As[k4 + fk][wm * 32 + ib * 16 + fr];
-        ar[ib] = v.x;
-        ai[ib] = v.y;
-        nai[ib] = -v.y;
-      }
-#pragma unroll
-      for (int jb = 0; jb < 2; ++jb) {
-        const z64 v = Bs[k4 + fk][wn * 32 + jb * 16 + fr];
-        br[jb] = v.x;
-        bi[jb] = v.y;
-      }
-#pragma unroll
-      for (int ib = 0; ib < 2; ++ib)
-#pragma unroll
-        for (int jb = 0; jb < 2; ++jb) {
-          cr[ib][jb] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar[ib], br[jb], cr[ib][jb], 0, 0, 0);
-          ci[ib][jb] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar[ib], bi[jb], ci[ib][jb], 0, 0, 0);
-        }
-#pragma unroll
-      for (int ib = 0; ib < 2; ++ib)
-#pragma unroll
-        for (int jb = 0; jb < 2; ++jb) {
-          cr[ib][jb] = __builtin_amdgcn_mfma_f64_16x16x4f64(nai[ib], bi[jb], cr[ib][jb], 0, 0, 0);
-          ci[ib][jb] = __builtin_amdgcn_mfma_f64_16x16x4f64(ai[ib], br[jb], ci[ib][jb], 0, 0, 0);
-        }
+    for (int h = 0; h < KS; ++h) {
+      const int w = KT == 2 ? 2 * kt : 2 * h;
+      const z64 cv = ex[(w * 16 + t) * 64 + lane], sv = ex[((w + 1) * 16 + t) * 64 + lane];
+      c.x += cv.x;
+      c.y += cv.y;
+      sn.x += sv.x;
+      sn.y += sv.y;
     }
-    __syncthreads();
-    if (more) put();
-    __syncthreads();
+    const int row = 4 * (t & 3) + fk, col = fl;
+    const int f = f0 + (t >> 3) * 16 + (COLS ? col : row);
+    const int k = ktile * 32 + ((t >> 2) & 1) * 16 + (COLS ? row : col) + 1;
+    if (f >= a.F || k > out_half) continue;
+    const z64 z = in0(f);
+    c.x += z.x;
+    c.y += z.y;
+    if (k < a.P - out_half) emit(out_half + k, f, c.x - a.sign * sn.y, c.y + a.sign * sn.x);
+    emit(out_half - k, f, c.x + a.sign * sn.y, c.y - a.sign * sn.x);
   }
+  if (zero_tile && tid < kFree && f0 + tid < a.F) {
+    z64 z = in0(f0 + tid);
 #pragma unroll
-  for (int ib = 0; ib < 2; ++ib)
-#pragma unroll
-    for (int jb = 0; jb < 2; ++jb) {
-      const int j = j0 + wn * 32 + jb * 16 + fr;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int i = i0 + wm * 32 + ib * 16 + 4 * r + fk;
-        if (i < M && j < N) c[size_t(i) * ldc + j] = {s * cr[ib][jb][r], s * ci[ib][jb][r]};
-      }
+    for (int q = 0; q < (COLS ? 8 : 1); ++q) {
+      z.x += zs[q * kFree + tid].x;
+      z.y += zs[q * kFree + tid].y;
     }
+    emit(out_half, f0 + tid, z.x, z.y);
+  }
 }
 
 // most partials zsum_kernel adds
 constexpr int kMaxZsum = 32;
 
-// split-K factors of the forward transform's two products (m x n x n, then m x m x n): 4 and 32
-// where their 64 x 64 tiles alone would give a launch fewer than 4 blocks per compute unit and
-// the pupil is large
+// most slices that the workspace holds for the forward transform's two products: 4 and 32 where
+// their outputs are small and the pupil is large
 int f64_split(int n, int m) {
   const long tiles = long((n + 63) / 64) * long((m + 63) / 64);
   return tiles < 1024 && n >= 1024 ? 4 : 1;
@@ -210,15 +289,27 @@ __global__ void __launch_bounds__(256) zsum_inplace_kernel(z64 *part, size_t str
   part[i] = acc;
 }
 
-template <bool TA, bool CA, bool TB, bool CB>
-hipError_t zgemm(const z64 *a, int lda, const z64 *b, int ldb, z64 *c, int ldc, int M, int N, int K, double s,
-                 hipStream_t st, const LaunchHook &hook, const char *name, int split = 1, int sa = 1,
-                 size_t a_split = 0) {
+int div_up(int x, int y) { return (x + y - 1) / y; }
+// one output tile per block unless two still give every compute unit two blocks
+int zblocks(const ZFold &a, int kt) { return div_up(ztiles(a.P), kt) * div_up(a.F, kFree); }
+
+// slices of the pairs, at most `most`, so that every compute unit gets two blocks, each slice at
+// least 128 pairs deep
+int zsplit(const ZFold &a, int most) {
+  int s = 1;
+  while (zblocks(a, 1) * s < 512 && 2 * s <= most && a.Q / 2 / (2 * s) >= 128) s *= 2;
+  return s;
+}
+
+template <bool COLS>
+hipError_t zfold(ZFold a, hipStream_t st, const LaunchHook &hook, const char *name, int split = 1) {
   hook(st, name, 1, 0);
-  const int kc = ((K + split - 1) / split + kDepth - 1) / kDepth * kDepth;
-  const size_t c_split = size_t(M) * size_t(ldc);
-  hipLaunchKernelGGL((zgemm_mfma_kernel<TA, CA, TB, CB>), dim3((N + 63) / 64, (M + 63) / 64, split), dim3(256), 0,
-                     st, a, lda, b, ldb, c, ldc, M, N, K, s, kc, c_split, sa, a_split);
+  a.j_per_split = std::max(div_up(div_up(a.Q / 2, split), kStage), 1) * kStage;
+  const int ftiles = div_up(a.F, kFree);
+  if (zblocks(a, 2) * split >= 512)
+    hipLaunchKernelGGL((zfold_kernel<2, COLS>), dim3(div_up(ztiles(a.P), 2), ftiles, split), dim3(kThreads), 0, st, a);
+  else
+    hipLaunchKernelGGL((zfold_kernel<1, COLS>), dim3(ztiles(a.P), ftiles, split), dim3(kThreads), 0, st, a);
   hipError_t e = hipGetLastError();
   hook(st, name, 1, 1);
   return e;
@@ -230,27 +321,30 @@ uint64_t dbits(double v) {
   return u;
 }
 
-// W[k][x] = exp(-2 pi i (k - m/2)(x - n/2) du / n_d), m x n float64 pairs; the index product is
-// an exact integer, its turns reduced to [-1/2, 1/2] before the exponential
-int mft64_matrix(Ctx *ctx, int m, int n, double n_d, double du, hipStream_t s, const z64 **out) {
-  const TableKey key{kMft64, m, uint64_t(n), dbits(n_d), dbits(du), 0};
+// the table of ztiles / zsteps for an output of length p and an input of length q; the index
+// product is an exact integer, its turns reduced to [-1/2, 1/2] before the cosine and sine
+int mft64_table(Ctx *ctx, int p, int q, double n_d, double du, hipStream_t s, const d2 **out) {
+  const TableKey key{kMft64, p, uint64_t(q), dbits(n_d), dbits(du), 0};
   if (auto it = ctx->tables.find(key); it != ctx->tables.end()) {
-    *out = static_cast<const z64 *>(it->second);
+    *out = static_cast<const d2 *>(it->second);
     return FR_OK;
   }
-  std::vector<double> w(size_t(2) * m * n);
+  const int tiles = ztiles(p), steps = zsteps(q);
+  const size_t par = size_t(tiles) * steps * 256;
+  std::vector<double> w(2 * par, 0.0);
   const double r = du / n_d;
-  for (int k = 0; k < m; ++k)
-    for (int x = 0; x < n; ++x) {
-      const double p = double(int64_t(k - m / 2) * int64_t(x - n / 2));
-      double t = p * r;
+  for (int k = 0; k < p / 2; ++k)
+    for (int j = 0; j < q / 2; ++j) {
+      double t = double(int64_t(k + 1) * int64_t(j + 1)) * r;
       t -= std::rint(t);
-      w[2 * (size_t(k) * n + x)] = std::cos(2.0 * M_PI * t);
-      w[2 * (size_t(k) * n + x) + 1] = -std::sin(2.0 * M_PI * t);
+      const int lane = k % 16 + 16 * (j % 4);
+      const size_t at = (((size_t(k / 32) * steps + j / 8) * 2 + k % 32 / 16) * 64 + lane) * 2 + j % 8 / 4;
+      w[at] = std::cos(2.0 * M_PI * t);
+      w[par + at] = std::sin(2.0 * M_PI * t);
     }
   void *d = nullptr;
   const int st = ctx->upload(key, w.data(), w.size() * sizeof(double), s, &d);
-  *out = static_cast<const z64 *>(d);
+  *out = static_cast<const d2 *>(d);
   return st;
 }
 
@@ -276,50 +370,56 @@ extern "C" int mft_f64(fr_ctx *ctx_, const fr_c128 *in, fr_c128 *out, int32_t n_
   if (e != hipSuccess) return fr::record_hip(e);
   if (int st = ctx->begin_call(); st != FR_OK) return st;
   const int n = n_pupil, m = m_focal;
-  const fr::z64 *w;
-  int st = fr::mft64_matrix(ctx, m, n, n_d, du, s, &w);
+  const bool adj = flags & FR_ADJOINT;
+  // forward: T = in W^T (n x m), out = scale W T (m x m); adjoint: T = in conj(W) (m x n),
+  // out = scale W^H T (n x n); both read one table, of the output's and the input's length
+  const int p = adj ? n : m, q = adj ? m : n;
+  const fr::d2 *w;
+  int st = fr::mft64_table(ctx, p, q, n_d, du, s, &w);
   if (st != FR_OK) return st;
-  const auto *src = reinterpret_cast<const fr::z64 *>(in);
-  auto *dst = reinterpret_cast<fr::z64 *>(out);
-  auto *t = reinterpret_cast<fr::z64 *>(ws);
-  const double scale = du / n_d;
   const fr::LaunchHook hook = ctx->hook();
-  if (!(flags & FR_ADJOINT)) {
-    // T = W in (m x n, in `split` partial sums over k, added in order into the first by
-    // zsum_kernel); out = scale T W^T (m x m), that product in turn split over k into `split2`
-    // partials after T in the workspace, added in order by zsum_kernel. (Adding T's partials as
-    // the second product reads them made each of its column tiles read all of them: 0.78 ms
-    // against 0.71 ms for the forward transform at the occulter shape.)
-    const int split = fr::f64_split(n, m), split2 = fr::f64_split2(n, m);
-    const size_t part = size_t(m) * size_t(n), part2 = size_t(m) * size_t(m);
-    e = fr::zgemm<false, false, false, false>(w, n, src, n, t, n, m, n, n, 1.0, s, hook, "zgemm_mft64_1", split);
-    if (e == hipSuccess && split > 1) {
-      hook(s, "zsum_mft64_t", 1, 0);
-      hipLaunchKernelGGL(fr::zsum_inplace_kernel, dim3(unsigned((part + 255) / 256)), dim3(256), 0, s, t, part,
-                         split, part);
-      e = hipGetLastError();
-      hook(s, "zsum_mft64_t", 1, 1);
+  auto *t = reinterpret_cast<fr::z64 *>(ws);
+  fr::ZFold g;
+  std::memset(&g, 0, sizeof g);
+  g.F = q; g.P = p; g.Q = q;
+  g.sign = adj ? 1.0 : -1.0;
+  g.data = reinterpret_cast<const fr::z64 *>(in); g.ldd = q;
+  g.table = w;
+  g.out = t; g.ldc = p;
+  g.scale = 1.0;
+  // the forward's products may be split over the pairs: the first into partials that are added in
+  // place into T, the second into partials after them (the adjoint's sums are short)
+  const size_t part = size_t(m) * size_t(n), part2 = size_t(m) * size_t(m);
+  const int most = adj ? 1 : fr::f64_split(n, m), most2 = adj ? 1 : fr::f64_split2(n, m);
+  const int split = fr::zsplit(g, most);
+  g.split_stride = part;
+  e = fr::zfold<false>(g, s, hook, adj ? "zfold_mft64_adj_1" : "zfold_mft64_1", split);
+  if (e == hipSuccess && split > 1) {
+    hook(s, "zsum_mft64_t", 1, 0);
+    hipLaunchKernelGGL(fr::zsum_inplace_kernel, dim3(unsigned((part + 255) / 256)), dim3(256), 0, s, t, part, split,
+                       part);
+    e = hipGetLastError();
+    hook(s, "zsum_mft64_t", 1, 1);
+  }
+  if (e == hipSuccess) {
+    g.F = p;
+    g.data = t; g.ldd = p;
+    g.out = reinterpret_cast<fr::z64 *>(out);
+    g.scale = du / n_d;
+    const int split2 = fr::zsplit(g, most2);
+    if (split2 > 1) {
+      g.out = t + part * most;
+      g.scale = 1.0;
+      g.split_stride = part2;
     }
-    if (e == hipSuccess && split2 == 1)
-      e = fr::zgemm<false, false, true, false>(t, n, w, n, dst, m, m, m, n, scale, s, hook, "zgemm_mft64_2");
+    e = fr::zfold<true>(g, s, hook, adj ? "zfold_mft64_adj_2" : "zfold_mft64_2", split2);
     if (e == hipSuccess && split2 > 1) {
-      fr::z64 *t2 = t + part * split;
-      e = fr::zgemm<false, false, true, false>(t, n, w, n, t2, m, m, m, n, 1.0, s, hook, "zgemm_mft64_2", split2);
-      if (e == hipSuccess) {
-        hook(s, "zsum_mft64", 1, 0);
-        hipLaunchKernelGGL(fr::zsum_kernel, dim3(unsigned((part2 + 255) / 256)), dim3(256), 0, s, t2, part2, split2,
-                           dst, part2, scale);
-        e = hipGetLastError();
-        hook(s, "zsum_mft64", 1, 1);
-      }
+      hook(s, "zsum_mft64", 1, 0);
+      hipLaunchKernelGGL(fr::zsum_kernel, dim3(unsigned((part2 + 255) / 256)), dim3(256), 0, s, g.out, part2, split2,
+                         reinterpret_cast<fr::z64 *>(out), part2, du / n_d);
+      e = hipGetLastError();
+      hook(s, "zsum_mft64", 1, 1);
     }
-  } else {
-    // T = W^H in (n x m); out = scale T conj(W) (n x n). (T in split-K partials would be summed
-    // by every column tile of the second product: 0.99 ms against 0.62 ms for it at the occulter
-    // shape.)
-    e = fr::zgemm<true, true, false, false>(w, n, src, m, t, m, n, m, m, 1.0, s, hook, "zgemm_mft64_adj_1");
-    if (e == hipSuccess)
-      e = fr::zgemm<false, false, false, true>(t, m, w, n, dst, n, n, n, m, scale, s, hook, "zgemm_mft64_adj_2");
   }
   if (e != hipSuccess) return fr::record_hip(e);
   return FR_OK;

@@ -65,3 +65,17 @@ def test_mft_f64_matches_float32_mft_within_its_bar():
     got32 = fb.mft_forward(torch.from_numpy(e.astype(np.complex64)).to("cuda:0"), n_d, m, du)
     torch.cuda.synchronize()
     assert rel_l2(got32.cpu().numpy().astype(np.complex128), got64) <= 1e-5
+
+
+# edges of the folded products: lengths without a pair, 31 to 33 and 63 to 66 outputs, whole and
+# partial stages of 32 pairs, odd and even, and a pupil whose products are summed in slices
+@pytest.mark.parametrize("n,m", [(1, 2), (3, 1), (63, 65), (66, 33), (127, 64), (130, 129), (1025, 70), (1536, 260)])
+def test_folded_products_at_tile_edges(n, m):
+    # float64 roundings: the sums over half the length, twice, below (n + m) 2^-53 relative to a
+    # random field's rms output
+    n_d, du = max(1.0, 0.4 * n), 0.37
+    e, eb = synth.random_field(n, n + m), synth.random_field(m, n + m + 1)
+    got = fb.mft_f64(torch.from_numpy(e.astype(np.complex128)).cuda(), n_d, m, du).cpu().numpy()
+    assert rel_l2(got, oracle.mft(e.astype(np.complex128), n_d, m, du)) <= 1e-12
+    got = fb.mft_f64(torch.from_numpy(eb.astype(np.complex128)).cuda(), n_d, n, du, adjoint=True).cpu().numpy()
+    assert rel_l2(got, oracle.mft_adjoint(eb.astype(np.complex128), n_d, n, du)) <= 1e-12
