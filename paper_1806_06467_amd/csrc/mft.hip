@@ -28,7 +28,8 @@
 // float64. Products with few tiles and long sums are split over j; the float64 partial sums go
 // to the workspace and split_reduce adds them in a fixed order (deterministic).
 // Measured (MI355X, 4096^2 -> 256^2 and back): 765 us with the complex products on float32 MFMA
-// tiles, 214 us folded; the result's distance from 64 bits 1.5e-7 before, 7.9e-8 now.
+// tiles, 214 us folded on the general kernel alone, 164 us with the short sums on their own kernel
+// and the loads ordered as below; the result's distance from 64 bits 1.5e-7 before, 8e-8 now.
 #include <hip/hip_runtime.h>
 
 #include <cstdio>
@@ -109,103 +110,168 @@ constexpr int kFoldDepth = 128;    // pairs a float32 sum runs over before it go
 constexpr int kFoldPieces = 12;    // P.re, P.im, M.re, M.im, each hi, mid, lo
 // a piece of one stage in LDS: 16-byte units of eight consecutive pairs of one free index, unit
 // (pair / 8) * 32 + free index, so that a wave's fragment read is 1 KiB contiguous; the free
-// index is xored with 4 in the odd groups of eight pairs, which spreads the stores of a wave
-// that walks along the pairs over all banks
-__device__ __forceinline__ int fold_unit(int g8, int f) { return g8 * kFoldFree + (f ^ ((g8 & 1) << 2)); }
+// index is xored with twice the group of eight pairs, so that half a wave's 8-byte stores along
+// the pairs (eight groups of two free indices) fall on 32 different bank pairs
+__device__ __forceinline__ int fold_unit(int g8, int f) { return g8 * kFoldFree + (f ^ ((g8 & 7) << 1)); }
 
-// One folded product. A block forms 32 free indices by KT * 32 positive outputs (both signs of
-// each): eight waves, each one parity (cosine or sine), one 32-wide output tile and, for KT = 2,
-// one half of every stage's pairs (the halves are added in the epilogue). The data are loaded
-// two stages ahead, folded and split by all threads into the other LDS buffer while the current
-// stage is multiplied; the matrix comes fragment by fragment (1 KiB, L2-resident) straight from
-// its table, one step ahead. COLS: the transform runs along the rows' index (the free index is
-// the column), so the output tile is transposed by swapping the MFMA operands.
-template <int KT, bool COLS>
+constexpr int kPieceUnits = kFoldFree * kFoldStage / 8;  // 16-byte units of a piece of one stage
+
+// A thread's share of the folding: four consecutive pairs of one free index per stage.
+template <bool COLS>
+struct FoldLoader {
+  struct Regs {
+    float2 p[4], m[4];
+  };
+  const float2 *centre;  // element 0 of this thread's free index (clamped to the last)
+  ptrdiff_t step;        // elements between consecutive indices
+  int half, full_pairs;  // pairs j = 1 .. half; in(+j) exists up to full_pairs (one less for even Q)
+  int lf, jq, wunit, wbyte;
+  bool zero_tile;        // keep the sum of P for out(0)
+  double zero_re = 0.0, zero_im = 0.0;
+  // the block's free indices as a raw buffer, when its bytes fit 32-bit offsets: this thread's
+  // offsets of in(+j) and in(-j - 3) (rows) or in(-j) (columns), j its first pair of stage 0
+  __amdgpu_buffer_rsrc_t rsrc;
+  unsigned row_bytes, vp, vm;
+  bool fits;
+
+  __device__ __forceinline__ FoldLoader(const FoldArgs &a, int tid, int f0, bool zero) {
+    half = a.Q / 2;
+    full_pairs = a.Q - 1 - half;
+    lf = COLS ? tid & 31 : tid >> 4;
+    jq = COLS ? tid >> 5 : tid & 15;
+    const int f = min(f0 + lf, a.F - 1);
+    step = COLS ? a.ldd : 1;
+    centre = COLS ? a.data + size_t(half) * a.ldd + f : a.data + size_t(f) * a.ldd + half;
+    wunit = fold_unit(jq >> 1, lf);
+    wbyte = (jq & 1) * 8;
+    zero_tile = zero;
+    const float2 *base = COLS ? a.data + f0 : a.data + size_t(f0) * a.ldd;
+    const int nf = min(kFoldFree, a.F - f0);
+    const size_t bytes = (COLS ? size_t(a.Q - 1) * a.ldd + nf : size_t(nf - 1) * a.ldd + a.Q) * 8;
+    fits = bytes < (size_t(1) << 31);
+    rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float2 *>(base), (short)0, int(fits ? bytes : 0), 0x00020000);
+    row_bytes = unsigned(a.ldd) * 8u;
+    const unsigned at = COLS ? unsigned(half) * row_bytes + unsigned(f - f0) * 8u
+                             : unsigned(f - f0) * row_bytes + unsigned(half) * 8u;
+    const unsigned j = 4u * jq + 1u;
+    vp = at + (COLS ? j * row_bytes : j * 8u);
+    vm = at - (COLS ? j * row_bytes : (j + 3u) * 8u);
+  }
+  // a whole stage of pairs j0 + 1 .. j0 + kFoldStage <= half. An even Q has no in(+half): what its
+  // slot reads (the next row's start, or 0 past the buffer, whose range check sees the whole
+  // per-lane offset) is replaced by 0.
+  __device__ __forceinline__ void load(Regs &r, int j0) const {
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    const unsigned d = unsigned(j0) * (COLS ? row_bytes : 8u);
+    if constexpr (COLS) {
+#pragma unroll
+      for (unsigned q = 0; q < 4; ++q) {
+        r.p[q] = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(rsrc, vp + d + q * row_bytes, 0, 0));
+        r.m[q] = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(rsrc, vm - d - q * row_bytes, 0, 0));
+      }
+    } else {
+      const f4 p0 = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, vp + d, 0, 0));
+      const f4 p1 = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, vp + d + 16u, 0, 0));
+      const f4 m1 = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, vm - d, 0, 0));
+      const f4 m0 = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, vm - d + 16u, 0, 0));
+      r.p[0] = make_float2(p0[0], p0[1]);
+      r.p[1] = make_float2(p0[2], p0[3]);
+      r.p[2] = make_float2(p1[0], p1[1]);
+      r.p[3] = make_float2(p1[2], p1[3]);
+      r.m[0] = make_float2(m0[2], m0[3]);
+      r.m[1] = make_float2(m0[0], m0[1]);
+      r.m[2] = make_float2(m1[2], m1[3]);
+      r.m[3] = make_float2(m1[0], m1[1]);
+    }
+  }
+  __device__ __forceinline__ void trim(Regs &r, int j0) const {
+    if (j0 + 4 * jq + 4 > full_pairs) r.p[3] = make_float2(0.f, 0.f);
+  }
+  // any stage, element by element, zero past the last pair
+  __device__ __forceinline__ void load_any(Regs &r, int j0) const {
+    const int j = j0 + 4 * jq + 1;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      r.p[q] = j + q <= full_pairs ? centre[(j + q) * step] : make_float2(0.f, 0.f);
+      r.m[q] = j + q <= half ? centre[-(j + q) * step] : make_float2(0.f, 0.f);
+    }
+  }
+  __device__ __forceinline__ void put_part(uint4 *dst, float v0, float v1, float v2, float v3) const {
+    unsigned h[2], m[2], l[2];
+    bf_split2(v0, v1, h[0], m[0], l[0]);
+    bf_split2(v2, v3, h[1], m[1], l[1]);
+    unsigned char *d = reinterpret_cast<unsigned char *>(dst + wunit) + wbyte;
+    *reinterpret_cast<uint2 *>(d) = make_uint2(h[0], h[1]);
+    *reinterpret_cast<uint2 *>(d + kPieceUnits * 16) = make_uint2(m[0], m[1]);
+    *reinterpret_cast<uint2 *>(d + 2 * kPieceUnits * 16) = make_uint2(l[0], l[1]);
+  }
+  // fold the real (imaginary) parts of the four pairs, split them and write their six pieces to
+  // the stage buffer [kFoldPieces][kPieceUnits]; `count`: add to the sum for out(0)
+  __device__ __forceinline__ void put_re(const Regs &r, uint4 *buf, bool count) {
+    const float s0 = r.p[0].x + r.m[0].x, s1 = r.p[1].x + r.m[1].x, s2 = r.p[2].x + r.m[2].x, s3 = r.p[3].x + r.m[3].x;
+    if (zero_tile && count) zero_re += double((s0 + s1) + (s2 + s3));
+    put_part(buf, s0, s1, s2, s3);
+    put_part(buf + 6 * kPieceUnits, r.p[0].x - r.m[0].x, r.p[1].x - r.m[1].x, r.p[2].x - r.m[2].x, r.p[3].x - r.m[3].x);
+  }
+  __device__ __forceinline__ void put_im(const Regs &r, uint4 *buf, bool count) {
+    const float s0 = r.p[0].y + r.m[0].y, s1 = r.p[1].y + r.m[1].y, s2 = r.p[2].y + r.m[2].y, s3 = r.p[3].y + r.m[3].y;
+    if (zero_tile && count) zero_im += double((s0 + s1) + (s2 + s3));
+    put_part(buf + 3 * kPieceUnits, s0, s1, s2, s3);
+    put_part(buf + 9 * kPieceUnits, r.p[0].y - r.m[0].y, r.p[1].y - r.m[1].y, r.p[2].y - r.m[2].y, r.p[3].y - r.m[3].y);
+  }
+};
+
+// data fragment times matrix fragment; COLS: the output tile is transposed (the free index along
+// the lanes) by swapping the operands
+template <bool COLS>
+__device__ __forceinline__ floatx16 fold_mfma(bf16x8 d, bf16x8 t, floatx16 c) {
+  if constexpr (COLS) return __builtin_amdgcn_mfma_f32_32x32x16_bf16(t, d, c, 0, 0, 0);
+  else return __builtin_amdgcn_mfma_f32_32x32x16_bf16(d, t, c, 0, 0, 0);
+}
+
+// one 16-deep step of one parity: re and im, each into its hi hi and its correction sum. The five
+// corrections smallest first (mid mid, lo hi, hi lo, mid hi, hi mid), then hi hi
+template <bool COLS>
+__device__ __forceinline__ void fold_step(const bf16x8 (&d)[6], const bf16x8 (&b)[3], floatx16 &rh, floatx16 &rc,
+                                          floatx16 &ih, floatx16 &ic) {
+  constexpr int lx[5] = {1, 2, 0, 1, 0}, ly[5] = {1, 0, 2, 0, 1};
+#pragma unroll
+  for (int q = 0; q < 5; ++q) {
+    rc = fold_mfma<COLS>(d[lx[q]], b[ly[q]], rc);
+    ic = fold_mfma<COLS>(d[3 + lx[q]], b[ly[q]], ic);
+  }
+  rh = fold_mfma<COLS>(d[0], b[0], rh);
+  ih = fold_mfma<COLS>(d[3], b[0], ih);
+}
+
+// One folded product. A block forms 32 free indices by 64 positive outputs (both signs of each):
+// eight waves, each one parity (cosine or sine), one 32-wide output tile and one half of every
+// stage's pairs (the halves are added in the epilogue). The data are loaded two stages ahead,
+// folded and split by all threads into the other LDS buffer while the current stage is
+// multiplied; the matrix comes fragment by fragment (1 KiB, L2-resident) straight from its table,
+// a stage ahead. Vector loads return in order, so each stage issues its matrix loads before its
+// data loads: a wait for the matrix then never waits for data still on their way from HBM.
+template <bool COLS>
 __global__ void __launch_bounds__(kFoldThreads) __attribute__((amdgpu_waves_per_eu(2)))
 fold_kernel(FoldParams gp) {
-  constexpr int KS = 4 / KT;        // stage halves summed by different waves
-  constexpr int STEPS = 4 / KS;     // 16-deep steps per wave and stage
-  constexpr int kPieceUnits = kFoldFree * kFoldStage / 8;
+  constexpr int KT = 2, KS = 2;  // output tiles per block, halves of a stage
+  using Loader = FoldLoader<COLS>;
   const FoldArgs &a = gp.a;
   __shared__ __attribute__((aligned(16))) unsigned char lds[8 * 16 * 64 * 16 + 16 * kFoldFree * 16];
   uint4 *pieces = reinterpret_cast<uint4 *>(lds);  // [2][kFoldPieces][kPieceUnits]
-  static_assert(2 * kFoldPieces * kPieceUnits * 16 <= 8 * 16 * 64 * 16, "stage buffers fit the exchange area");
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  constexpr int kBuf = kFoldPieces * kPieceUnits;
+  static_assert(2 * kBuf * 16 <= 8 * 16 * 64 * 16, "stage buffers fit the exchange area");
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int par = wave & 1, kt = (wave >> 1) % KT, ks = (wave >> 1) / KT;
   int bx, by, bz;
   block_tile(bx, by, bz);
   const int f0 = by * kFoldFree;
-  const int half = a.Q / 2;                 // pairs j = 1 .. half (0-based below)
-  const int full_pairs = a.Q - 1 - half;    // pairs whose in(+j) exists (half, less one for even Q)
+  Loader ld(a, tid, f0, bx == 0);
+  const int half = ld.half;
   const int jbeg = bz * gp.j_per_split;
   const int jend = min(half, jbeg + gp.j_per_split);
   const int nst = jend > jbeg ? (jend - jbeg + kFoldStage - 1) / kFoldStage : 0;
-
-  // this thread's free index and its four pairs of a stage
-  const int lf = COLS ? tid & 31 : tid >> 4;
-  const int jq = COLS ? tid >> 5 : tid & 15;
-  const int f = min(f0 + lf, a.F - 1);
-  const float2 *centre = COLS ? a.data + size_t(half) * a.ldd + f : a.data + size_t(f) * a.ldd + half;
-  struct Regs {
-    float2 p[4], m[4];
-  };
-  auto load = [&](Regs &r, int j0) {
-    const int j = j0 + 4 * jq + 1;
-    if (j0 + kFoldStage <= full_pairs) {
-      if constexpr (COLS) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          r.p[q] = centre[ptrdiff_t(j + q) * a.ldd];
-          r.m[q] = centre[-ptrdiff_t(j + q) * a.ldd];
-        }
-      } else {
-        typedef float f4 __attribute__((ext_vector_type(4), aligned(8)));
-        const f4 p0 = *reinterpret_cast<const f4 *>(centre + j), p1 = *reinterpret_cast<const f4 *>(centre + j + 2);
-        const f4 m1 = *reinterpret_cast<const f4 *>(centre - j - 3), m0 = *reinterpret_cast<const f4 *>(centre - j - 1);
-        r.p[0] = make_float2(p0[0], p0[1]);
-        r.p[1] = make_float2(p0[2], p0[3]);
-        r.p[2] = make_float2(p1[0], p1[1]);
-        r.p[3] = make_float2(p1[2], p1[3]);
-        r.m[0] = make_float2(m0[2], m0[3]);
-        r.m[1] = make_float2(m0[0], m0[1]);
-        r.m[2] = make_float2(m1[2], m1[3]);
-        r.m[3] = make_float2(m1[0], m1[1]);
-      }
-    } else {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const ptrdiff_t o = COLS ? ptrdiff_t(j + q) * a.ldd : ptrdiff_t(j + q);
-        r.p[q] = j + q <= full_pairs ? centre[o] : make_float2(0.f, 0.f);
-        r.m[q] = j + q <= half ? centre[-o] : make_float2(0.f, 0.f);
-      }
-    }
-  };
-  // fold the real (imaginary) parts of the four pairs, split them and write their six pieces; the
-  // blocks of the first output tile keep the sum of P for out(0)
-  double zero_re = 0.0, zero_im = 0.0;
-  const bool zero_tile = bx == 0;
-  const int wunit = fold_unit(jq >> 1, lf), wbyte = (jq & 1) * 8;
-  auto put_part = [&](int buf, int base, float v0, float v1, float v2, float v3) {
-    unsigned h[2], m[2], l[2];
-    bf_split2(v0, v1, h[0], m[0], l[0]);
-    bf_split2(v2, v3, h[1], m[1], l[1]);
-    unsigned char *dst = reinterpret_cast<unsigned char *>(pieces + (buf * kFoldPieces + base) * kPieceUnits + wunit) + wbyte;
-    *reinterpret_cast<uint2 *>(dst) = make_uint2(h[0], h[1]);
-    *reinterpret_cast<uint2 *>(dst + kPieceUnits * 16) = make_uint2(m[0], m[1]);
-    *reinterpret_cast<uint2 *>(dst + 2 * kPieceUnits * 16) = make_uint2(l[0], l[1]);
-  };
-  auto put_re = [&](const Regs &r, int buf) {
-    const float s0 = r.p[0].x + r.m[0].x, s1 = r.p[1].x + r.m[1].x, s2 = r.p[2].x + r.m[2].x, s3 = r.p[3].x + r.m[3].x;
-    if (zero_tile) zero_re += double((s0 + s1) + (s2 + s3));
-    put_part(buf, 0, s0, s1, s2, s3);
-    put_part(buf, 6, r.p[0].x - r.m[0].x, r.p[1].x - r.m[1].x, r.p[2].x - r.m[2].x, r.p[3].x - r.m[3].x);
-  };
-  auto put_im = [&](const Regs &r, int buf) {
-    const float s0 = r.p[0].y + r.m[0].y, s1 = r.p[1].y + r.m[1].y, s2 = r.p[2].y + r.m[2].y, s3 = r.p[3].y + r.m[3].y;
-    if (zero_tile) zero_im += double((s0 + s1) + (s2 + s3));
-    put_part(buf, 3, s0, s1, s2, s3);
-    put_part(buf, 9, r.p[0].y - r.m[0].y, r.p[1].y - r.m[1].y, r.p[2].y - r.m[2].y, r.p[3].y - r.m[3].y);
-  };
 
   // this wave's matrix fragments: [parity][output tile][step][piece], 64 lanes of eight values
   const int out_half = a.P / 2;
@@ -213,93 +279,101 @@ fold_kernel(FoldParams gp) {
   const int ktile = bx * KT + kt;
   const bf16x8 *tab = reinterpret_cast<const bf16x8 *>(a.table) +
                       (size_t(par) * tiles + min(ktile, tiles - 1)) * steps * 3 * 64 + lane;
-  auto load_tab = [&](bf16x8 (&b)[3], int step) {
-    const bf16x8 *p = tab + size_t(min(step, steps - 1)) * 3 * 64;
+  auto load_tab = [&](bf16x8 (&b)[2][3], int step) {
 #pragma unroll
-    for (int q = 0; q < 3; ++q) b[q] = p[q * 64];
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int q = 0; q < 3; ++q) b[t][q] = tab[(size_t(step + t) * 3 + q) * 64];
   };
 
-  // float32 sums of the current group (re and im, each as hi hi and correction sums)
-  floatx16 rh, rc, ih, ic;
+  // float32 sums of the current group (re and im, each as hi hi and correction sums; the
+  // corrections are at most 2^-7 of the sum, so theirs run on to the end)
+  floatx16 rh = floatx16{0.f}, rc = floatx16{0.f}, ih = floatx16{0.f}, ic = floatx16{0.f};
   double totr[16], toti[16];
 #pragma unroll
   for (int r = 0; r < 16; ++r) totr[r] = toti[r] = 0.0;
-  auto clear = [&] {
-    rh = floatx16{0.f};
-    rc = floatx16{0.f};
-    ih = floatx16{0.f};
-    ic = floatx16{0.f};
-  };
-  clear();
-  auto mm = [](bf16x8 d, bf16x8 t, floatx16 c) {
-    if constexpr (COLS) return __builtin_amdgcn_mfma_f32_32x32x16_bf16(t, d, c, 0, 0, 0);
-    else return __builtin_amdgcn_mfma_f32_32x32x16_bf16(d, t, c, 0, 0, 0);
-  };
   auto multiply = [&](int buf, int sub, const bf16x8 (&b)[3]) {
     const int g8 = sub * 2 + (lane >> 5);
-    const uint4 *src = pieces + (buf * kFoldPieces + 6 * par) * kPieceUnits + fold_unit(g8, lane & 31);
+    const uint4 *src = pieces + buf * kBuf + 6 * par * kPieceUnits + fold_unit(g8, lane & 31);
     bf16x8 d[6];
 #pragma unroll
     for (int q = 0; q < 6; ++q) d[q] = __builtin_bit_cast(bf16x8, src[q * kPieceUnits]);
-    // the five corrections smallest first (mid mid, lo hi, hi lo, mid hi, hi mid), then hi hi
-    constexpr int lx[5] = {1, 2, 0, 1, 0}, ly[5] = {1, 0, 2, 0, 1};
-#pragma unroll
-    for (int q = 0; q < 5; ++q) {
-      rc = mm(d[lx[q]], b[ly[q]], rc);
-      ic = mm(d[3 + lx[q]], b[ly[q]], ic);
-    }
-    rh = mm(d[0], b[0], rh);
-    ih = mm(d[3], b[0], ih);
+    fold_step<COLS>(d, b, rh, rc, ih, ic);
   };
   auto fold = [&] {
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      totr[r] += double(rh[r]) + double(rc[r]);
-      toti[r] += double(ih[r]) + double(ic[r]);
+      totr[r] += double(rh[r]);
+      toti[r] += double(ih[r]);
     }
-    clear();
+    rh = floatx16{0.f};
+    ih = floatx16{0.f};
   };
 
-  if (nst > 0) {
-    constexpr int kStagesPerFold = kFoldDepth / (16 * STEPS);
-    Regs r0, r1;
-    bf16x8 tb[2][3];
-    load(r0, jbeg);
-    load_tab(tb[0], jbeg / 16 + ks * STEPS);
-    put_re(r0, 0);
-    put_im(r0, 0);
-    load(r1, jbeg + min(1, nst - 1) * kFoldStage);
+  constexpr int kStagesPerFold = kFoldDepth / 32;
+  typename Loader::Regs r0, r1;
+  bf16x8 tb[2][2][3];
+  const int step0 = jbeg / 16 + 2 * ks;  // the steps are padded to whole stages
+  const int nfull = ld.fits ? (jend - jbeg) / kFoldStage : 0;
+  int pending = 0;
+  if (nfull > 0) {
+    ld.load(r0, jbeg);
+    load_tab(tb[0], step0);
+    ld.load(r1, jbeg + min(1, nfull - 1) * kFoldStage);
+    ld.trim(r0, jbeg);
+    ld.put_re(r0, pieces, true);
+    ld.put_im(r0, pieces, true);
     __syncthreads();
-    int pending = 0;
     // stage s: multiply LDS buffer `buf` while `ready` (stage s + 1) is split into the other
     // buffer and `fill` receives stage s + 2 (the last stages reload the last one; their split
-    // goes to a buffer nobody reads again, and its sums for out(0) are left out)
-    auto stage = [&](int s, int buf, Regs &fill, const Regs &ready) {
-      load(fill, jbeg + min(s + 2, nst - 1) * kFoldStage);
-      const int st0 = jbeg / 16 + s * 4 + ks * STEPS;
-      const double keep_re = zero_re, keep_im = zero_im;
-#pragma unroll
-      for (int t = 0; t < STEPS; ++t) {
-        const int next = t + 1 < STEPS ? st0 + t + 1 : jbeg / 16 + min(s + 1, nst - 1) * 4 + ks * STEPS;
-        load_tab(tb[(t + 1) & 1], next);
-        multiply(buf, ks * STEPS + t, tb[t & 1]);
-        if (t == 0) put_re(ready, buf ^ 1);
-        if (t == STEPS - 1) put_im(ready, buf ^ 1);
-      }
-      if (s + 1 >= nst) {
-        zero_re = keep_re;
-        zero_im = keep_im;
-      }
-      if (++pending == kStagesPerFold || s + 1 == nst) {
+    // goes to a buffer nobody reads again)
+    auto stage = [&](int s, int buf, typename Loader::Regs &fill, typename Loader::Regs &ready) {
+      uint4 *other = pieces + (buf ^ 1) * kBuf;
+      const int next = min(s + 1, nfull - 1);
+      load_tab(tb[buf ^ 1], step0 + 4 * next);
+      __builtin_amdgcn_sched_barrier(0);
+      ld.load(fill, jbeg + min(s + 2, nfull - 1) * kFoldStage);
+      __builtin_amdgcn_sched_barrier(0);
+      multiply(buf, 2 * ks, tb[buf][0]);
+      __builtin_amdgcn_sched_barrier(0);  // half a stage more for the loads of stage s + 1
+      ld.trim(ready, jbeg + next * kFoldStage);
+      multiply(buf, 2 * ks + 1, tb[buf][1]);
+      ld.put_re(ready, other, s + 1 < nfull);
+      ld.put_im(ready, other, s + 1 < nfull);
+      if (++pending == kStagesPerFold) {
         fold();
         pending = 0;
       }
       __syncthreads();
     };
-    for (int s = 0; s < nst; s += 2) {
+    // (one exit at the end of both halves keeps the register sets in place: with another in the
+    // middle the compiler moved them at the loop's head, waiting for the loads under way)
+    int s = 0;
+    for (; s + 2 <= nfull; s += 2) {
       stage(s, 0, r0, r1);
-      if (s + 1 < nst) stage(s + 1, 1, r1, r0);
+      stage(s + 1, 1, r1, r0);
     }
+    if (s < nfull) stage(s, 0, r0, r1);
+  }
+  // a last partial stage (every stage where the data's bytes do not fit 32-bit offsets)
+  for (int s = nfull; s < nst; ++s) {
+    ld.load_any(r0, jbeg + s * kFoldStage);
+    load_tab(tb[0], step0 + 4 * s);
+    ld.put_re(r0, pieces, true);
+    ld.put_im(r0, pieces, true);
+    __syncthreads();
+    multiply(0, 2 * ks, tb[0][0]);
+    multiply(0, 2 * ks + 1, tb[0][1]);
+    if (++pending == kStagesPerFold) {
+      fold();
+      pending = 0;
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    totr[r] += double(rh[r]) + double(rc[r]);
+    toti[r] += double(ih[r]) + double(ic[r]);
   }
 
   // exchange: every wave's totals, then each wave of a tile (2 parities x KS halves) forms both
@@ -309,7 +383,7 @@ fold_kernel(FoldParams gp) {
   __syncthreads();
 #pragma unroll
   for (int r = 0; r < 16; ++r) ex[(wave * 16 + r) * 64 + lane] = make_double2(totr[r], toti[r]);
-  zs[jq * kFoldFree + lf] = make_double2(zero_re, zero_im);
+  zs[ld.jq * kFoldFree + ld.lf] = make_double2(ld.zero_re, ld.zero_im);
   __syncthreads();
   const int rows = COLS ? a.P : a.F, cols = COLS ? a.F : a.P;
   auto emit = [&](int o, int ff, double re, double im) {
@@ -349,8 +423,116 @@ fold_kernel(FoldParams gp) {
     if (k < a.P - out_half) emit(out_half + k, ff, c.x - sg * s.y, c.y + sg * s.x);
     emit(out_half - k, ff, c.x + sg * s.y, c.y - sg * s.x);
   }
-  if (zero_tile && tid < kFoldFree && f0 + tid < a.F) {
+  if (bx == 0 && tid < kFoldFree && f0 + tid < a.F) {
     double2 z = in0(f0 + tid);
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      const double2 v = zs[q * kFoldFree + tid];
+      z.x += v.x;
+      z.y += v.y;
+    }
+    emit(out_half, f0 + tid, z.x, z.y);
+  }
+}
+
+// The same for at most kShortPairs pairs, where the general kernel's blocks spend their time
+// filling and draining (two stages, then the exchange of the totals). Here the block folds and
+// splits its 32 free indices once, keeps all their pieces in LDS (96 KiB) and its waves walk the
+// output tiles on their own, without barriers: a wave forms both parities of a tile in one float32
+// group, so the outputs of either sign come straight from its registers, and its stores overlap
+// the other waves' products. (256^2 -> 4096^2: 60 us against 120 us on the general kernel.)
+constexpr int kShortPairs = 2 * kFoldStage;
+template <bool COLS>
+__global__ void __launch_bounds__(kFoldThreads) __attribute__((amdgpu_waves_per_eu(2)))
+fold_short_kernel(FoldArgs a, int tiles_per_block) {
+  using Loader = FoldLoader<COLS>;
+  constexpr int kBuf = kFoldPieces * kPieceUnits;
+  __shared__ __attribute__((aligned(16))) uint4 pieces[2 * kBuf];  // [stage][kFoldPieces][kPieceUnits]
+  __shared__ double2 zs[16 * kFoldFree];                           // [group of pairs][free index]
+  __shared__ float2 in0[kFoldFree];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int f0 = blockIdx.y * kFoldFree;
+  const int out_half = a.P / 2, tiles = fold_tiles(a.P), steps = fold_steps(a.Q);
+  Loader ld(a, tid, f0, blockIdx.x == 0);
+  const int used = (ld.half + 31) / 32 * 2;  // steps with a pair, in twos (both stages end on zeros)
+  {
+    typename Loader::Regs r0, r1;
+    if (ld.fits && ld.half == kShortPairs) {
+      ld.load(r0, 0);
+      ld.load(r1, kFoldStage);
+      ld.trim(r1, kFoldStage);
+    } else {
+      ld.load_any(r0, 0);
+      ld.load_any(r1, kFoldStage);
+    }
+    ld.put_re(r0, pieces, true);
+    ld.put_im(r0, pieces, true);
+    ld.put_re(r1, pieces + kBuf, true);
+    ld.put_im(r1, pieces + kBuf, true);
+    if (ld.jq == 0) in0[ld.lf] = *ld.centre;
+    zs[ld.jq * kFoldFree + ld.lf] = make_double2(ld.zero_re, ld.zero_im);
+  }
+  __syncthreads();
+  const double sg = a.sign;
+  auto emit = [&](int o, int ff, double re, double im) { epilogue(a, COLS ? o : ff, COLS ? ff : o, re, im); };
+  const int last = min(tiles, int(blockIdx.x + 1) * tiles_per_block);
+  bf16x8 tb[2][2][3];  // [step parity][parity][piece]
+  auto load_tab = [&](bf16x8 (&b)[2][3], int tile, int step) {
+#pragma unroll
+    for (int q = 0; q < 6; ++q)
+      b[q / 3][q % 3] = reinterpret_cast<const bf16x8 *>(
+          a.table)[(((size_t(q / 3) * tiles + tile) * steps + step) * 3 + q % 3) * 64 + lane];
+  };
+  int tile = blockIdx.x * tiles_per_block + wave;
+  if (tile < last) {
+    load_tab(tb[0], tile, 0);
+    load_tab(tb[1], tile, 1);
+  }
+  for (; tile < last; tile += 8) {
+    const int next = tile + 8 < last ? tile + 8 : tile;
+    floatx16 s[2][4];  // [parity][re hi hi, re corrections, im hi hi, im corrections]
+#pragma unroll
+    for (int q = 0; q < 8; ++q) s[q >> 2][q & 3] = floatx16{0.f};
+    auto multiply = [&](int step, const bf16x8 (&b)[2][3]) {
+      const int g8 = (step & 3) * 2 + (lane >> 5);
+      const uint4 *src = pieces + (step >> 2) * kBuf + fold_unit(g8, lane & 31);
+#pragma unroll
+      for (int par = 0; par < 2; ++par) {
+        bf16x8 d[6];
+#pragma unroll
+        for (int q = 0; q < 6; ++q) d[q] = __builtin_bit_cast(bf16x8, src[(6 * par + q) * kPieceUnits]);
+        fold_step<COLS>(d, b[par], s[par][0], s[par][1], s[par][2], s[par][3]);
+      }
+    };
+    // the last steps load the next tile's first ones: they are on their way before the stores
+    for (int step = 0; step < used; step += 2) {
+      const bool more = step + 2 < used;
+      multiply(step, tb[0]);
+      load_tab(tb[0], more ? tile : next, more ? step + 2 : 0);
+      multiply(step + 1, tb[1]);
+      load_tab(tb[1], more ? tile : next, more ? step + 3 : 1);
+    }
+    int fbase = f0;
+    asm("" : "+s"(fbase));  // the rows' addresses are formed here, not kept across the products
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int trow = (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3), tcol = lane & 31;
+      const int lf = COLS ? tcol : trow, ff = fbase + lf;
+      const int k = tile * 32 + (COLS ? trow : tcol) + 1;
+      if (ff >= a.F || k > out_half) continue;
+      const float2 z = in0[lf];
+      const double cx = double(s[0][0][r]) + double(s[0][1][r]) + double(z.x);
+      const double cy = double(s[0][2][r]) + double(s[0][3][r]) + double(z.y);
+      const double sx = double(s[1][0][r]) + double(s[1][1][r]);
+      const double sy = double(s[1][2][r]) + double(s[1][3][r]);
+      if (k < a.P - out_half) emit(out_half + k, ff, cx - sg * sy, cy + sg * sx);
+      emit(out_half - k, ff, cx + sg * sy, cy - sg * sx);
+      if ((r & 3) == 3) __builtin_amdgcn_sched_barrier(0);  // four items' addresses and loads at a time
+    }
+  }
+  if (blockIdx.x == 0 && tid < kFoldFree && f0 + tid < a.F) {
+    double2 z = make_double2(in0[tid].x, in0[tid].y);
 #pragma unroll
     for (int q = 0; q < 16; ++q) {
       const double2 v = zs[q * kFoldFree + tid];
@@ -382,42 +564,51 @@ __global__ void __launch_bounds__(256) split_reduce(FoldParams gp, int rows, int
 
 int div_up(int x, int y) { return (x + y - 1) / y; }
 
-template <int KT, bool COLS>
+template <bool COLS>
 hipError_t launch_fold_kernel(const FoldParams &gp, hipStream_t stream) {
   const FoldArgs &a = gp.a;
-  const dim3 grid(std::max(div_up(fold_tiles(a.P), KT), 1), div_up(a.F, kFoldFree), gp.split);
-  hipLaunchKernelGGL((fold_kernel<KT, COLS>), grid, dim3(kFoldThreads), 0, stream, gp);
+  const dim3 grid(div_up(fold_tiles(a.P), 2), div_up(a.F, kFoldFree), gp.split);
+  hipLaunchKernelGGL((fold_kernel<COLS>), grid, dim3(kFoldThreads), 0, stream, gp);
   return hipGetLastError();
 }
 
-// 128 outputs per block (the data folded and split half as often) where that gives every compute
-// unit a block; else 64
-bool wide_tile(const FoldArgs &a) { return div_up(fold_tiles(a.P), 4) * div_up(a.F, kFoldFree) >= 256; }
+template <bool COLS>
+hipError_t launch_short_kernel(const FoldArgs &a, hipStream_t stream) {
+  // blocks for every compute unit, each with at least four output tiles (one per SIMD)
+  const int tiles = fold_tiles(a.P), ftiles = div_up(a.F, kFoldFree);
+  const int chunks = std::max(1, std::min(div_up(256, ftiles), tiles / 4));
+  const int per = div_up(tiles, chunks);
+  hipLaunchKernelGGL((fold_short_kernel<COLS>), dim3(div_up(tiles, per), ftiles), dim3(kFoldThreads), 0, stream, a, per);
+  return hipGetLastError();
+}
+
+bool short_pairs(const FoldArgs &a) { return a.Q / 2 <= kShortPairs; }
 
 }  // namespace
 
 // slices of the pairs so that the grid gives every compute unit a block, each slice at least 128
 // pairs deep
 int fold_split_for(const FoldArgs &a) {
-  const int blocks = div_up(fold_tiles(a.P), wide_tile(a) ? 4 : 2) * div_up(a.F, kFoldFree);
+  if (short_pairs(a)) return 1;
+  const int blocks = div_up(fold_tiles(a.P), 2) * div_up(a.F, kFoldFree);
   int s = 1;
   while (blocks * s < 256 && a.Q / 2 / (s * 2) >= 128 && s < kMaxSplit) s *= 2;
   return s;
 }
 
 hipError_t launch_fold(const FoldArgs &a, int split, void *partial, hipStream_t stream, const LaunchHook &hook) {
+  if (short_pairs(a)) split = 1;  // one group of pairs: nothing to slice
   FoldParams gp;
   gp.a = a;
   gp.split = split;
   gp.j_per_split = std::max(div_up(div_up(a.Q / 2, split), kFoldStage), 1) * kFoldStage;
   gp.partial = static_cast<double2 *>(partial);
-  const bool wide = wide_tile(a);
   const int rows = a.cols ? a.P : a.F, cols = a.cols ? a.F : a.P;
   char name[64];
   std::snprintf(name, sizeof name, "fold%s_%dx%dx%d_s%d", a.cols ? "C" : "R", a.F, a.P, a.Q, split);
   hook(stream, name, a.Q, 0);
-  hipError_t e = a.cols ? (wide ? launch_fold_kernel<4, true>(gp, stream) : launch_fold_kernel<2, true>(gp, stream))
-                        : (wide ? launch_fold_kernel<4, false>(gp, stream) : launch_fold_kernel<2, false>(gp, stream));
+  hipError_t e = short_pairs(a) ? (a.cols ? launch_short_kernel<true>(a, stream) : launch_short_kernel<false>(a, stream))
+                                : (a.cols ? launch_fold_kernel<true>(gp, stream) : launch_fold_kernel<false>(gp, stream));
   hook(stream, name, a.Q, 1);
   if (e != hipSuccess || split == 1) return e;
   hook(stream, "split_reduce", a.Q, 0);
