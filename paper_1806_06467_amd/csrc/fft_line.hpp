@@ -32,13 +32,13 @@ struct PassOut {
     const int i0 = (b / P) * (P * R) + (b % P);
     base = lds_pad(i0);
   }
-  // valid when P % 16 == 0 (the pad of i0 + rP is pad(i0) + 17 rP/16), or P == 1 and
-  // 16 % R == 0 with i0 = b R (then (b R + r) / 16 = b R / 16 for r < R)
+  // valid when P % 16 == 0 (the pad of i0 + rP is pad(i0) + 17 rP/16), or P == 1 with i0 = b R and
+  // 16 % R == 0 (then (b R + r) / 16 = b R / 16 for r < R) or R % 16 == 0
   __device__ __forceinline__ static constexpr int off(int r) {
     if constexpr (P % 16 == 0) return r * (P + P / 16);
-    return r;  // P == 1
+    return r + r / 16;  // P == 1
   }
-  static constexpr bool exact = (P % 16 == 0) || (P == 1 && 16 % R == 0);
+  static constexpr bool exact = (P % 16 == 0) || (P == 1 && (16 % R == 0 || R % 16 == 0));
 };
 
 // Twiddles of one pass for the NB butterflies a thread owns: leg r of butterfly b is
@@ -74,36 +74,32 @@ struct FirstOf {
 // Pass with radix R after span P. The twiddles of the next pass are loaded before this
 // pass's LDS exchange, so their latency overlaps the exchange.
 //
-// HALF exchanges move the line through an LDS buffer of N/2 (+ padding) in two rounds: the
-// outputs at positions below N/2 (butterflies b < N/(2R): threads t < T/2 when each thread owns
-// one butterfly, else the first half of each thread's butterflies), then the upper half. Every
-// non-last pass has P R <= N/2, so the N/2 boundary never splits a butterfly's outputs, and the
-// reading slots split the same way (slot m < E/2 is position t + T m < N/2).
-// C: the element type (c32 or c64d); TW: the twiddle table's (float2 or double2)
-template <class C, class TW, bool INV, bool HALF, int N, int E, int P, int R, int... Rest>
-__device__ __forceinline__ void fft_passes(C (&v)[E], C* __restrict__ lds, int t,
+// SPLIT exchanges move the real and then the imaginary parts through one line of reals, half the
+// LDS of a line of complex values: the outputs stay in their registers until their turn, so a
+// thread holds nothing more than its line's elements.
+// C: the element type (c32 or c64d); TW: the twiddle table's (float2 or double2); L: what the LDS
+// line holds (C, or its real type for SPLIT)
+template <class C, class TW, class L, bool INV, bool SPLIT, int N, int E, int P, int R, int... Rest>
+__device__ __forceinline__ void fft_passes(C (&v)[E], L* __restrict__ lds, int t,
                                            const TW* __restrict__ tw,
                                            const PassTw<P, R, E / R, N / E, C, TW>& cur) {
   constexpr int T = N / E;
   constexpr int NB = E / R;
   static_assert(E % R == 0, "radix must divide the elements per thread");
   static_assert(N % (P * R) == 0, "plan does not factor N");
-  static_assert(!HALF || NB == 1 || NB % 2 == 0, "half exchanges split each thread's butterflies in two");
   constexpr bool last = sizeof...(Rest) == 0;
-  constexpr bool lazy = PassTw<P, R, NB, T>::lazy;
-  // outputs of the second half-round, held until the first half has been exchanged
-  constexpr int HOLD = !HALF || last ? 1 : (NB == 1 ? 1 : NB / 2);
-  C hold[HOLD][R];
-  // write output r of butterfly b (positions shifted down by `shift`)
-  auto put = [&](int b, int shift, const C (&u)[R]) {
+  // SPLIT reads each twiddle where it is used: its tables lie in LDS
+  constexpr bool lazy = SPLIT || PassTw<P, R, NB, T>::lazy;
+  // write outputs of butterfly b: value(r) to the position of output r
+  auto put = [&](int b, auto value) {
     if constexpr (PassOut<P, R>::exact) {
-      const PassOut<P, R> o(b - shift / R);
+      const PassOut<P, R> o(b);
 #pragma unroll
-      for (int r = 0; r < R; ++r) lds[o.base + PassOut<P, R>::off(r)] = u[r];
+      for (int r = 0; r < R; ++r) lds[o.base + PassOut<P, R>::off(r)] = value(r);
     } else {
-      const int base = (b / P) * (P * R) + (b % P) - shift;
+      const int base = (b / P) * (P * R) + (b % P);
 #pragma unroll
-      for (int r = 0; r < R; ++r) lds[lds_pad(base + r * P)] = u[r];
+      for (int r = 0; r < R; ++r) lds[lds_pad(base + r * P)] = value(r);
     }
   };
 #pragma unroll
@@ -126,62 +122,42 @@ __device__ __forceinline__ void fft_passes(C (&v)[E], C* __restrict__ lds, int t
       }
     }
     DftDir<R, INV>::run(u);
-    if constexpr (last) {
+    if constexpr (last || SPLIT) {
 #pragma unroll
       for (int r = 0; r < R; ++r) v[j + r * NB] = u[r];
-    } else if constexpr (!HALF) {
-      put(b, 0, u);
-    } else if constexpr (NB == 1) {
-      if (t < T / 2) {
-        put(b, 0, u);
-      } else {
-#pragma unroll
-        for (int r = 0; r < R; ++r) hold[0][r] = u[r];
-      }
     } else {
-      if (j < NB / 2) {
-        put(b, 0, u);
-      } else {
-#pragma unroll
-        for (int r = 0; r < R; ++r) hold[j - NB / 2][r] = u[r];
-      }
+      put(b, [&](int r) { return u[r]; });
     }
   }
   if constexpr (!last) {
     constexpr int R2 = FirstOf<Rest...>::value;
     const TW* tw_next = tw + (P > 1 ? (R - 1) * P : 0);
     PassTw<P * R, R2, E / R2, T, C, TW> nxt;
-    nxt.load(tw_next, t);
-    // read slots [m0, m1), whose positions start at T m0
-    auto get = [&](int m0, int m1) {
-#pragma unroll
-      for (int m = 0; m < E; ++m) {
-        if (m < m0 || m >= m1) continue;
-        if constexpr (T % 16 == 0) {
-          v[m] = lds[lds_pad(t) + (m - m0) * (T + T / 16)];
-        } else {
-          v[m] = lds[lds_pad(t + T * (m - m0))];
-        }
-      }
+    if constexpr (!SPLIT) nxt.load(tw_next, t);
+    auto at = [&](int m) {
+      if constexpr (T % 16 == 0) return lds_pad(t) + m * (T + T / 16);
+      else return lds_pad(t + T * m);
     };
-    __syncthreads();
-    if constexpr (!HALF) {
-      get(0, E);
+    if constexpr (!SPLIT) {
+      __syncthreads();
+#pragma unroll
+      for (int m = 0; m < E; ++m) v[m] = lds[at(m)];
       __syncthreads();
     } else {
-      get(0, E / 2);
-      __syncthreads();
-      if constexpr (NB == 1) {
-        if (t >= T / 2) put(t, N / 2, hold[0]);
-      } else {
 #pragma unroll
-        for (int j = NB / 2; j < NB; ++j) put(t + j * T, N / 2, hold[j - NB / 2]);
-      }
+      for (int j = 0; j < NB; ++j) put(t + j * T, [&](int r) { return v[j + r * NB].x; });
       __syncthreads();
-      get(E / 2, E);
+#pragma unroll
+      for (int m = 0; m < E; ++m) v[m].x = lds[at(m)];
+      __syncthreads();
+#pragma unroll
+      for (int j = 0; j < NB; ++j) put(t + j * T, [&](int r) { return v[j + r * NB].y; });
+      __syncthreads();
+#pragma unroll
+      for (int m = 0; m < E; ++m) v[m].y = lds[at(m)];
       __syncthreads();
     }
-    fft_passes<C, TW, INV, HALF, N, E, P * R, Rest...>(v, lds, t, tw_next, nxt);
+    fft_passes<C, TW, L, INV, SPLIT, N, E, P * R, Rest...>(v, lds, t, tw_next, nxt);
   }
 }
 
@@ -222,18 +198,17 @@ struct Plan {
   template <class TW>
   static void build_twiddles(TW* out) { TwiddleTable<N_, 1, Rs...>::build(out); }
   // unnormalised DFT of the line, kernel exp(-2 pi i nk/N); tw = the plan's twiddle table (float2
-  // for c32 elements, double2 for c64d). HALF: exchanges through an LDS line of N/2
-  // (LdsLine<N/2>), in two rounds each.
-  template <bool HALF = false, class C, class TW>
-  __device__ __forceinline__ static void forward(C (&v)[E_], C* lds, int t, const TW* tw) {
+  // for c32 elements, double2 for c64d). An LDS line of reals selects the split exchanges.
+  template <class C, class L, class TW>
+  __device__ __forceinline__ static void forward(C (&v)[E_], L* lds, int t, const TW* tw) {
     PassTw<1, R0, E_ / R0, N_ / E_, C, TW> none;
-    fft_passes<C, TW, false, HALF, N_, E_, 1, Rs...>(v, lds, t, tw, none);
+    fft_passes<C, TW, L, false, sizeof(L) != sizeof(C), N_, E_, 1, Rs...>(v, lds, t, tw, none);
   }
   // unnormalised inverse DFT, kernel exp(+2 pi i nk/N)
-  template <bool HALF = false, class C, class TW>
-  __device__ __forceinline__ static void inverse(C (&v)[E_], C* lds, int t, const TW* tw) {
+  template <class C, class L, class TW>
+  __device__ __forceinline__ static void inverse(C (&v)[E_], L* lds, int t, const TW* tw) {
     PassTw<1, R0, E_ / R0, N_ / E_, C, TW> none;
-    fft_passes<C, TW, true, HALF, N_, E_, 1, Rs...>(v, lds, t, tw, none);
+    fft_passes<C, TW, L, true, sizeof(L) != sizeof(C), N_, E_, 1, Rs...>(v, lds, t, tw, none);
   }
 };
 

@@ -14,6 +14,8 @@
 // The column tile is LINES columns wide so that a wavefront reads LINES*8-byte contiguous
 // segments; blocks are renumbered so that the blocks resident on one XCD (one L2) work on
 // neighbouring columns at the same time.
+#include <type_traits>
+
 #include "fft_line.hpp"
 #include "fr_internal.h"
 #include "fr_exact.h"
@@ -139,19 +141,29 @@ __device__ __forceinline__ bool pre_optic_row(const PlaneArgs &pa, int n, int y,
   return true;
 }
 
-// post optic exp(2 pi i 2 post_surf / lambda) at rows y = t + T m of column x, for all slots:
-// the map (4-column tiles) is read for every slot before any phasor is formed
-template <int E, int T>
-__device__ __forceinline__ void post_optic_col(const PlaneArgs &pa, int n, int t, int x, c32 (&ph)[E]) {
+// G: slots whose factors are loaded together (the pipelined column sweep holds two tiles' elements
+// and takes a few at a time)
+// v times the post optic exp(2 pi i 2 post_surf / lambda) (its conjugate for the adjoint) at rows
+// y = t + T m of column x: the map (4-column tiles) is read for a group of slots before their
+// phasors are formed
+template <int G, int E, int T>
+__device__ __forceinline__ void post_optic_col(const PlaneArgs &pa, int n, int t, int x, bool adj, c32 (&v)[E]) {
   const MapBuf map(pa.post_surf, unsigned(post_tiled_size(n)) * 4u);
-  float sv[E];
 #pragma unroll
-  for (int m = 0; m < E; ++m) sv[m] = map.load(unsigned(post_tiled_index(n, t + T * m, x)) * 4u, 0u);
+  for (int m0 = 0; m0 < E; m0 += G) {
+    if constexpr (G < E) __builtin_amdgcn_sched_barrier(0);
+    float sv[G];
 #pragma unroll
-  for (int m = 0; m < E; ++m) {
-    float s, c;
-    sincos_turns(2.0f * sv[m] * pa.inv_lambda, &s, &c);
-    ph[m] = {c, s};
+    for (int m = 0; m < G; ++m) sv[m] = map.load(unsigned(post_tiled_index(n, t + T * (m0 + m), x)) * 4u, 0u);
+    c32 ph[G];
+#pragma unroll
+    for (int m = 0; m < G; ++m) {
+      float s, c;
+      sincos_turns(2.0f * sv[m] * pa.inv_lambda, &s, &c);
+      ph[m] = {c, s};
+    }
+#pragma unroll
+    for (int m = 0; m < G; ++m) v[m0 + m] = adj ? cmulc(v[m0 + m], ph[m]) : cmul(v[m0 + m], ph[m]);
   }
 }
 
@@ -248,19 +260,18 @@ row_sweep(BatchArgs args, const float2 *tw) {
   for (int m = 0; m < E; ++m) buf.store(vo, unsigned(T * m) * 8u, v[m]);
 }
 
-// HALF: the FFT exchanges go through half-size LDS lines in two rounds, so that two blocks fit
-// on a compute unit. DIRECT: the column half of the direct Fresnel step: the forward transform,
+// DIRECT: the column half of the direct Fresnel step: the forward transform,
 // then the output quadratic phase of both axes (h holds it per index, with the constant's root).
 // EXACT (with DIRECT): the column sweep of the exact-transfer-function step (fr_exact.h), 1 with
 // H's phase formed per element in float64, 2 in its split form.
-template <class PL, int LINES, bool HALF = false, bool DIRECT = false, int EXACT = 0>
+template <class PL, int LINES, bool DIRECT = false, int EXACT = 0>
 __global__ void __launch_bounds__(PL::T *LINES) col_sweep(BatchArgs args, const float2 *tw) {
-  static_assert(!EXACT || (DIRECT && !HALF), "the exact mode runs on full LDS lines");
+  static_assert(!EXACT || DIRECT, "the exact mode is one of the direct kernel");
   constexpr int N = PL::N, E = PL::E, T = PL::T;
   constexpr int G = N / LINES;  // column groups per plane
   // the lines of the LINES columns start 8 float2 apart in the bank pattern (measured: a
   // 3 % faster sweep than 4, 10 % than 1)
-  constexpr int LINE = (HALF ? LdsLine<N / 2>::size : LdsLine<N>::size) + 8;
+  constexpr int LINE = LdsLine<N>::size + 8;
   __shared__ c32 lds[LINES * LINE];
   const PlaneArgs &pa = args.p[blockIdx.y];
   const int c = threadIdx.x % LINES;
@@ -289,12 +300,7 @@ __global__ void __launch_bounds__(PL::T *LINES) col_sweep(BatchArgs args, const 
 #pragma unroll
     for (int m = 0; m < E; ++m) v[m] = buf.load(vo, unsigned(T * m) * unsigned(N) * 8u);
   }
-  if (adj && post) {
-    c32 ph[E];
-    post_optic_col<E, T>(pa, N, t, x, ph);
-#pragma unroll
-    for (int m = 0; m < E; ++m) v[m] = cmulc(v[m], ph[m]);
-  }
+  if (adj && post) post_optic_col<E, E, T>(pa, N, t, x, true, v);
   c32 *my = lds + c * LINE;
   if constexpr (DIRECT) {
     if constexpr (EXACT) {
@@ -313,7 +319,7 @@ __global__ void __launch_bounds__(PL::T *LINES) col_sweep(BatchArgs args, const 
         const float2 *hp = reinterpret_cast<const float2 *>(prm + 4);
         const float zlf = float(zl), a2f = float(a2);
         const c32 hx = ld2(hp + x);
-        PL::template forward<HALF>(v, my, t, tw);
+        PL::forward(v, my, t, tw);
 #pragma unroll
         for (int m = 0; m < E; ++m) {
           const int k = t + T * m;
@@ -325,12 +331,12 @@ __global__ void __launch_bounds__(PL::T *LINES) col_sweep(BatchArgs args, const 
           const c32 hh = cmul(cmul(hx, ld2(hp + k)), c32{cs, sn});
           v[m] = adj ? cmulc(v[m], hh) : cmul(v[m], hh);
         }
-        PL::template inverse<HALF>(v, my, t, tw);
+        PL::inverse(v, my, t, tw);
 #pragma unroll
         for (int m = 0; m < E; ++m) buf.store(vo, unsigned(T * m) * unsigned(N) * 8u, v[m]);
         return;
       } else {
-        PL::template forward<HALF>(v, my, t, tw);
+        PL::forward(v, my, t, tw);
 #pragma unroll
         for (int m = 0; m < E; ++m) my[t + T * m] = v[m];
         constexpr float inv_n2 = 1.0f / (float(N) * float(N));
@@ -354,7 +360,7 @@ __global__ void __launch_bounds__(PL::T *LINES) col_sweep(BatchArgs args, const 
 #pragma unroll
         for (int m = 0; m < E; ++m) v[m] = my[t + T * m];
         __syncthreads();  // every slot read back before the inverse transform's first exchange
-        PL::template inverse<HALF>(v, my, t, tw);
+        PL::inverse(v, my, t, tw);
 #pragma unroll
         for (int m = 0; m < E; ++m) buf.store(vo, unsigned(T * m) * unsigned(N) * 8u, v[m]);
         return;
@@ -369,8 +375,8 @@ __global__ void __launch_bounds__(PL::T *LINES) col_sweep(BatchArgs args, const 
 #pragma unroll
       for (int m = 0; m < E; ++m) v[m] = cmulc(v[m], cmul(ld2(pa.h + t + T * m), px));
     }
-    if (inv) PL::template inverse<HALF>(v, my, t, tw);
-    else PL::template forward<HALF>(v, my, t, tw);
+    if (inv) PL::inverse(v, my, t, tw);
+    else PL::forward(v, my, t, tw);
     if (!adj) {
 #pragma unroll
       for (int m = 0; m < E; ++m) v[m] = cmul(v[m], cmul(ld2(pa.h + t + T * m), px));
@@ -379,15 +385,10 @@ __global__ void __launch_bounds__(PL::T *LINES) col_sweep(BatchArgs args, const 
     for (int m = 0; m < E; ++m) buf.store(vo, unsigned(T * m) * unsigned(N) * 8u, v[m]);
     return;
   }
-  PL::template forward<HALF>(v, my, t, tw);
+  PL::forward(v, my, t, tw);
   freq_product<E, T>(v, pa.h, t, adj);
-  PL::template inverse<HALF>(v, my, t, tw);
-  if (!adj && post) {
-    c32 ph[E];
-    post_optic_col<E, T>(pa, N, t, x, ph);
-#pragma unroll
-    for (int m = 0; m < E; ++m) v[m] = cmul(v[m], ph[m]);
-  }
+  PL::inverse(v, my, t, tw);
+  if (!adj && post) post_optic_col<E, E, T>(pa, N, t, x, false, v);
   if (adj && (pa.flags & kWindowRowsOnly)) {
     // the row sweep that follows transforms only the rows of the window
     const int off = (N - pa.win) >> 1;
@@ -400,16 +401,175 @@ __global__ void __launch_bounds__(PL::T *LINES) col_sweep(BatchArgs args, const 
   }
 }
 
+// The column sweep of long lines, where a tile fills a compute unit: one block per compute unit
+// walks `tiles` tiles of a plane and loads the next tile while it transforms the current one, so
+// that the loads, the transforms and the stores overlap. Two things make room for that: the
+// exchanges move real and imaginary parts in turn through LDS lines of floats (half the LDS of the
+// tile), and the twiddles and h are copied to the rest of the LDS once per block, which takes
+// their registers and 76 of the 108 vector memory instructions per 16 elements away and leaves no
+// load between a tile's transform and the next tile's (vector loads return in order). It was the
+// address unit that bound the sweep before (busy 75 % of the time at 4096, the vector units 37 %).
+// Measured per plane (forward, adjoint): 4096^2 92 and 115 us to 83 and 100 us, 8192^2 877 us to
+// 705 us (16-byte pieces of rows 64 KiB apart: what the 32 compute units of an XCD have in flight
+// exceeds its L2, so a line is fetched 1.3 times and written in pieces).
+// PF: elements of the next tile loaded before the transform, the others just before the stores.
+template <class PL, int LINES, int PF, bool DIRECT = false, int EXACT = 0>
+__global__ void __launch_bounds__(PL::T *LINES) __attribute__((amdgpu_waves_per_eu(4))) col_sweep_pipe(BatchArgs args, const float2 *tw, int tiles) {
+  static_assert(EXACT != 1, "the float64 phase goes through complex LDS lines");
+  constexpr int N = PL::N, E = PL::E, T = PL::T;
+  constexpr int LINE = LdsLine<N>::size + 8;
+  constexpr bool HTAB = 4 * LINES * LINE + 8 * (PL::twiddles + N) <= 160 * 1024;
+  __shared__ float lds[LINES * LINE];
+  __shared__ __attribute__((aligned(16))) float2 tab[PL::twiddles + (HTAB ? N : 0)];
+  const PlaneArgs &pa = args.p[blockIdx.y];
+  const int c = threadIdx.x % LINES;
+  const int t = threadIdx.x / LINES;
+  const bool adj = pa.flags & FR_ADJOINT;
+  const PlaneBuf buf(pa.field, unsigned(N) * N * 8u);
+  // rows that the forward row sweep did not store (zero rows outside a windowed amplitude) are not
+  // loaded, and rows that the adjoint row sweep does not read are not stored: their offsets are
+  // moved past the buffer, whose range check returns 0 and drops the store
+  const int lwin = !adj && pa.amp ? pa.win : N, swin = adj && (pa.flags & kWindowRowsOnly) ? pa.win : N;
+  auto offset = [](int win, int t, unsigned vo, int m) {
+    return unsigned(t + T * m - ((N - win) >> 1)) < unsigned(win) ? vo : 0x80000000u;
+  };
+  // the thread's place in a tile, formed anew for each tile (kept, it would cost registers that
+  // the two tiles need)
+  auto place = [](int g, int &t, unsigned &vo) {
+    unsigned tid = threadIdx.x;
+    asm("" : "+v"(tid));
+    t = tid / LINES;
+    vo = (unsigned(t) * N + unsigned(g) * LINES + tid % LINES) * 8u;
+  };
+  const double *prm = reinterpret_cast<const double *>(pa.h);
+  const float2 *hg = EXACT ? reinterpret_cast<const float2 *>(prm + 4) : pa.h;
+  // tile i of this block: blocks are dealt round-robin to the 8 XCDs; the blocks of one XCD take
+  // tiles in runs that fill a 128-byte line of each row, and walk from a line to the next (the
+  // adjoint sweep of a 4096^2 plane, which reads from HBM: 100 us, 121-130 us where the lines of
+  // one block are 8 or 64 apart)
+  constexpr int RUN = LINES < 16 ? 16 / LINES : 1;
+  const int slot = blockIdx.x >> 3, q = (blockIdx.x & 7) * ((gridDim.x >> 3) / RUN) + slot / RUN;
+  const int first = q * tiles * RUN + slot % RUN, per = RUN;
+  auto load = [&](c32 *v, int g, auto m0, auto m1) {
+    int tl;
+    unsigned vo;
+    place(g, tl, vo);
+#pragma unroll
+    for (int m = m0; m < m1; ++m) v[m] = buf.load(offset(lwin, tl, vo, m), unsigned(T * m) * unsigned(N) * 8u);
+  };
+  using Zero = std::integral_constant<int, 0>;
+  using Mid = std::integral_constant<int, PF>;
+  using All = std::integral_constant<int, E>;
+  c32 v[E], nxt[E];
+  load(v, first, Zero{}, All{});
+  {
+    static_assert(PL::twiddles % 2 == 0 && N % 2 == 0, "two entries per copy");
+    const float4 *src = reinterpret_cast<const float4 *>(tw);
+    float4 *dst = reinterpret_cast<float4 *>(tab);
+    for (int i = threadIdx.x; i < PL::twiddles / 2; i += PL::T * LINES) dst[i] = src[i];
+    if constexpr (HTAB) {
+      const float4 *hs = reinterpret_cast<const float4 *>(hg);
+      for (int i = threadIdx.x; i < N / 2; i += PL::T * LINES) dst[PL::twiddles / 2 + i] = hs[i];
+    }
+  }
+  __syncthreads();
+  // h at the thread's slot m (where it is not in LDS, one address register serves all slots)
+  const PlaneBuf hb(hg, N * 8u);
+  auto h_at = [&](int m) {
+    if constexpr (HTAB) return ld2(tab + PL::twiddles + t + T * m);
+    else return hb.load(unsigned(t) * 8u, unsigned(T * m) * 8u);
+  };
+  auto h_x = [&](int x) { return ld2((HTAB ? tab + PL::twiddles : hg) + x); };
+  float *my = lds + c * LINE;
+  for (int i = 0; i < tiles; ++i) {
+    const int g = first + i * per;
+    const int x = g * LINES + c;
+    // the post surface's phasor, unless this tile lies where the surface is 0 (the phasor is 1)
+    const int x0 = g * LINES;
+    const bool post = pa.post_surf && !(pa.post_hi > pa.post_lo && (x0 + LINES <= pa.post_lo || x0 >= pa.post_hi));
+    if (adj && post) post_optic_col<4, E, T>(pa, N, t, x, true, v);
+    if (i + 1 < tiles) load(nxt, g + per, Zero{}, Mid{});
+    if constexpr (EXACT) {
+      // the split form of the exact transfer function (see col_sweep)
+      const float zlf = float(prm[0]), a2f = float(prm[1]);
+      const int kx = x < N / 2 ? x : x - N;
+      const c32 hx = h_x(x);
+      PL::forward(v, my, t, tab);
+#pragma unroll
+      for (int m = 0; m < E; ++m) {
+        const int k = t + T * m;
+        const int ky = k < N / 2 ? k : k - N;
+        const float u = a2f * float(kx * kx + ky * ky);
+        const float r = 1.0f + sqrtf(1.0f - u);
+        float sn, cs;
+        sincos_turns(-zlf * u * u / (2.0f * r * r), &sn, &cs);
+        const c32 hh = cmul(cmul(hx, h_at(m)), c32{cs, sn});
+        v[m] = adj ? cmulc(v[m], hh) : cmul(v[m], hh);
+      }
+      PL::inverse(v, my, t, tab);
+    } else if constexpr (DIRECT) {
+      const c32 px = h_x(x);
+      const bool inv = adj != bool(pa.flags & kTowardSource);  // kernel sign, as in the row sweep
+      if (adj) {
+#pragma unroll
+        for (int m = 0; m < E; ++m) v[m] = cmulc(v[m], cmul(h_at(m), px));
+      }
+      if (inv) PL::inverse(v, my, t, tab);
+      else PL::forward(v, my, t, tab);
+      if (!adj) {
+#pragma unroll
+        for (int m = 0; m < E; ++m) v[m] = cmul(v[m], cmul(h_at(m), px));
+      }
+    } else {
+      PL::forward(v, my, t, tab);
+#pragma unroll
+      for (int m = 0; m < E; ++m) {
+        // (a few loads of h at a time: two tiles' elements leave no registers for more)
+        if (!HTAB && m % 4 == 0) __builtin_amdgcn_sched_barrier(0);
+        const c32 q = h_at(m);
+        v[m] = adj ? cmulc(v[m], q) : cmul(v[m], q);
+      }
+      PL::inverse(v, my, t, tab);
+      if (!adj && post) post_optic_col<4, E, T>(pa, N, t, x, false, v);
+    }
+    if constexpr (PF < E) {
+      __builtin_amdgcn_sched_barrier(0);
+      if (i + 1 < tiles) load(nxt, g + per, Mid{}, All{});
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    int ts;
+    unsigned vo;
+    place(g, ts, vo);
+#pragma unroll
+    for (int m = 0; m < E; ++m) buf.store(offset(swin, ts, vo, m), unsigned(T * m) * unsigned(N) * 8u, v[m]);
+#pragma unroll
+    for (int m = 0; m < E; ++m) v[m] = nxt[m];
+  }
+}
+
 // Forward planes run the row sweep first (optic prologue on contiguous rows) and the column
 // sweep second (mirror epilogue); adjoint planes run the column sweep first (conjugate mirror
 // prologue) and the row sweep second (conjugate optic epilogue). The two halves of the
 // angular-spectrum step commute, so only the placement of the optics sets the order, and the
 // amplitude/OPD maps are always read along rows.
-template <class PL, int ROW_LINES, int COL_LINES, class PC = PL, bool CHALF = false, bool DIRECT = false>
+// blocks per plane of the pipelined column sweep: as many as run at once (1024 threads per compute
+// unit at its 128 registers) when `count` planes share the launch, a power of two so that a block's
+// tiles are whole runs of 128-byte lines
+template <class PL, int LINES>
+int pipe_blocks(int count) {
+  constexpr int G = PL::N / LINES, kAtOnce = 256 * 1024 / (PL::T * LINES);
+  constexpr int kLeast = 8 * (LINES < 16 ? 16 / LINES : 1);
+  static_assert(G % kLeast == 0, "a block per XCD and tile of a line");
+  int b = kLeast;
+  while (b < G && b * count < kAtOnce) b *= 2;
+  return b;
+}
+
+// PF > 0: the column sweep is the pipelined one with PF elements of the next tile in flight
+template <class PL, int ROW_LINES, int COL_LINES, int PF = 0, bool DIRECT = false>
 hipError_t launch_sweeps(const BatchArgs &fwd, int nf, const BatchArgs &adj, int na,
                          const float2 *tw, hipStream_t s, const LaunchHook &hook) {
   constexpr int N = PL::N;
-  static_assert(PC::N == N, "row and column plans of one edge");
   static_assert(N % ROW_LINES == 0 && N % COL_LINES == 0, "tile must divide n");
   // timing names carry the direction (the optic maps read differ), tags the planes per launch
   auto rows = [&](const BatchArgs &a, int count, const char *name) {
@@ -422,8 +582,14 @@ hipError_t launch_sweeps(const BatchArgs &fwd, int nf, const BatchArgs &adj, int
   };
   auto cols = [&](const BatchArgs &a, int count, const char *name) {
     hook(s, name, count, 0);
-    hipLaunchKernelGGL((col_sweep<PC, COL_LINES, CHALF, DIRECT>), dim3(N / COL_LINES, count),
-                       dim3(PC::T * COL_LINES), 0, s, a, tw);
+    if constexpr (PF > 0) {
+      const int blocks = pipe_blocks<PL, COL_LINES>(count);
+      hipLaunchKernelGGL((col_sweep_pipe<PL, COL_LINES, PF, DIRECT>), dim3(blocks, count), dim3(PL::T * COL_LINES), 0, s,
+                         a, tw, N / COL_LINES / blocks);
+    } else {
+      hipLaunchKernelGGL((col_sweep<PL, COL_LINES, DIRECT>), dim3(N / COL_LINES, count), dim3(PL::T * COL_LINES), 0, s,
+                         a, tw);
+    }
     hipError_t e = hipGetLastError();
     hook(s, name, count, 1);
     return e;
@@ -487,7 +653,7 @@ hipError_t launch_fresnel_batch(const PlaneArgs *planes, int count, int n, const
     else
       fwd.p[nf++] = planes[i];
   }
-#define FR_SWEEPS(PL, RL, CL) return launch_sweeps<PL, RL, CL>(fwd, nf, adj, na, root, s, hook)
+#define FR_SWEEPS(...) return launch_sweeps<__VA_ARGS__>(fwd, nf, adj, na, root, s, hook)
   switch (n) {
     case 64: {
       using P = Plan<64, 8, 8, 8>;
@@ -511,23 +677,22 @@ hipError_t launch_fresnel_batch(const PlaneArgs *planes, int count, int n, const
     }
     case 2048: {
       using P2 = Plan<2048, 16, 16, 16, 8>;
-      if (variant == 1) FR_SWEEPS(P2, 2, 4);
-      if (variant == 2) FR_SWEEPS(P2, 4, 4);
-      FR_SWEEPS(P2, 2, 8);
+      if (variant == 1) FR_SWEEPS(P2, 2, 4, 12);
+      if (variant == 2) FR_SWEEPS(P2, 2, 8);
+      FR_SWEEPS(P2, 1, 4, 12);
     }
     case 4096: {
       using P4 = Plan<4096, 16, 16, 16, 16>;
-      if (variant == 1) FR_SWEEPS(P4, 1, 2);
-      if (variant == 2) FR_SWEEPS(P4, 2, 2);
-      // column exchanges through half-size LDS lines
-      if (variant == 3) return launch_sweeps<P4, 1, 4, P4, true>(fwd, nf, adj, na, root, s, hook);
-      FR_SWEEPS(P4, 1, 4);
+      if (variant == 1) FR_SWEEPS(P4, 1, 2, 16);
+      if (variant == 2) FR_SWEEPS(P4, 2, 2, 16);
+      if (variant == 3) FR_SWEEPS(P4, 2, 4, 16);
+      FR_SWEEPS(P4, 1, 4, 16);
     }
     case 8192: {
       using P8 = Plan<8192, 16, 16, 16, 16, 2>;
-      if (variant == 1) FR_SWEEPS(P8, 1, 1);
+      if (variant == 1) FR_SWEEPS(P8, 1, 2);
       if (variant == 2) FR_SWEEPS(P8, 2, 1);
-      FR_SWEEPS(P8, 1, 2);
+      FR_SWEEPS(P8, 1, 2, 16);
     }
     default: return hipErrorInvalidValue;
   }
@@ -540,7 +705,7 @@ hipError_t launch_fresnel_batch(const PlaneArgs *planes, int count, int n, const
 // (planes whose bit is set in `split` have H in its split form: their column sweep is the split
 // instance's launch, the others' the float64 one's, so each plane takes the kernels it takes in
 // a call of its own)
-template <class PL, int RL, int CL>
+template <class PL, int RL, int CL, int PF = 0>
 hipError_t launch_exact_sweeps(const PlaneArgs *planes, int count, const float2 *tw, hipStream_t s,
                                const LaunchHook &hook, uint64_t split) {
   constexpr int N = PL::N;
@@ -571,14 +736,20 @@ hipError_t launch_exact_sweeps(const PlaneArgs *planes, int count, const float2 
   if (e != hipSuccess) return e;
   if (ns) {
     hook(s, "exact_cols", ns, 0);
-    hipLaunchKernelGGL((col_sweep<PL, CL, false, true, 2>), dim3(N / CL, ns), dim3(PL::T * CL), 0, s, bs, tw);
+    if constexpr (PF > 0) {
+      const int blocks = pipe_blocks<PL, CL>(ns);
+      hipLaunchKernelGGL((col_sweep_pipe<PL, CL, PF, true, 2>), dim3(blocks, ns), dim3(PL::T * CL), 0, s, bs, tw,
+                         N / CL / blocks);
+    } else {
+      hipLaunchKernelGGL((col_sweep<PL, CL, true, 2>), dim3(N / CL, ns), dim3(PL::T * CL), 0, s, bs, tw);
+    }
     e = hipGetLastError();
     hook(s, "exact_cols", ns, 1);
     if (e != hipSuccess) return e;
   }
   if (nb) {
     hook(s, "exact_cols_f64", nb, 0);
-    hipLaunchKernelGGL((col_sweep<PL, CL, false, true, 1>), dim3(N / CL, nb), dim3(PL::T * CL), 0, s, b, tw);
+    hipLaunchKernelGGL((col_sweep<PL, CL, true, 1>), dim3(N / CL, nb), dim3(PL::T * CL), 0, s, b, tw);
     e = hipGetLastError();
     hook(s, "exact_cols_f64", nb, 1);
   }
@@ -594,9 +765,9 @@ hipError_t launch_exact_batch(const PlaneArgs *planes, int count, int n, const f
     case 256: return launch_exact_sweeps<Plan<256, 16, 16, 16>, 16, 32>(planes, count, root, s, hook, split);
     case 512: return launch_exact_sweeps<Plan<512, 8, 8, 8, 8>, 4, 16>(planes, count, root, s, hook, split);
     case 1024: return launch_exact_sweeps<Plan<1024, 16, 16, 8, 8>, 4, 8>(planes, count, root, s, hook, split);
-    case 2048: return launch_exact_sweeps<Plan<2048, 16, 16, 16, 8>, 2, 8>(planes, count, root, s, hook, split);
-    case 4096: return launch_exact_sweeps<Plan<4096, 16, 16, 16, 16>, 1, 4>(planes, count, root, s, hook, split);
-    case 8192: return launch_exact_sweeps<Plan<8192, 16, 16, 16, 16, 2>, 1, 2>(planes, count, root, s, hook, split);
+    case 2048: return launch_exact_sweeps<Plan<2048, 16, 16, 16, 8>, 1, 4, 12>(planes, count, root, s, hook, split);
+    case 4096: return launch_exact_sweeps<Plan<4096, 16, 16, 16, 16>, 1, 4, 16>(planes, count, root, s, hook, split);
+    case 8192: return launch_exact_sweeps<Plan<8192, 16, 16, 16, 16, 2>, 1, 2, 16>(planes, count, root, s, hook, split);
     default: return hipErrorInvalidValue;
   }
 }
@@ -611,16 +782,16 @@ hipError_t launch_direct_batch(const PlaneArgs *planes, int count, int n, const 
     else
       fwd.p[nf++] = planes[i];
   }
-#define FR_DIRECT(PL, RL, CL) return launch_sweeps<PL, RL, CL, PL, false, true>(fwd, nf, adj, na, root, s, hook)
+#define FR_DIRECT(PL, RL, CL, PF) return launch_sweeps<PL, RL, CL, PF, true>(fwd, nf, adj, na, root, s, hook)
   switch (n) {
-    case 64: { using P = Plan<64, 8, 8, 8>; FR_DIRECT(P, 8, 16); }
-    case 128: { using P = Plan<128, 16, 16, 8>; FR_DIRECT(P, 16, 32); }
-    case 256: { using P = Plan<256, 16, 16, 16>; FR_DIRECT(P, 16, 32); }
-    case 512: { using P = Plan<512, 8, 8, 8, 8>; FR_DIRECT(P, 4, 16); }
-    case 1024: { using P = Plan<1024, 16, 16, 8, 8>; FR_DIRECT(P, 4, 8); }
-    case 2048: { using P = Plan<2048, 16, 16, 16, 8>; FR_DIRECT(P, 2, 8); }
-    case 4096: { using P = Plan<4096, 16, 16, 16, 16>; FR_DIRECT(P, 1, 4); }
-    case 8192: { using P = Plan<8192, 16, 16, 16, 16, 2>; FR_DIRECT(P, 1, 2); }
+    case 64: { using P = Plan<64, 8, 8, 8>; FR_DIRECT(P, 8, 16, 0); }
+    case 128: { using P = Plan<128, 16, 16, 8>; FR_DIRECT(P, 16, 32, 0); }
+    case 256: { using P = Plan<256, 16, 16, 16>; FR_DIRECT(P, 16, 32, 0); }
+    case 512: { using P = Plan<512, 8, 8, 8, 8>; FR_DIRECT(P, 4, 16, 0); }
+    case 1024: { using P = Plan<1024, 16, 16, 8, 8>; FR_DIRECT(P, 4, 8, 0); }
+    case 2048: { using P = Plan<2048, 16, 16, 16, 8>; FR_DIRECT(P, 1, 4, 12); }
+    case 4096: { using P = Plan<4096, 16, 16, 16, 16>; FR_DIRECT(P, 1, 4, 16); }
+    case 8192: { using P = Plan<8192, 16, 16, 16, 16, 2>; FR_DIRECT(P, 1, 2, 16); }
     default: return hipErrorInvalidValue;
   }
 #undef FR_DIRECT

@@ -489,3 +489,22 @@ def test_context_created_with_a_tuning_file(tmp_path):
     with pytest.raises(fb.FrError) as err:
         fb.Context(0, tune_file=str(bad))
     assert err.value.status == fb.FR_EINVAL
+
+
+@pytest.mark.parametrize("n,count", [(2048, 2), (2048, 3), (2048, 5), (8192, 2)])
+def test_pipelined_column_tiles_per_block_agree_bitwise(n, count):
+    """The pipelined column sweep walks more tiles per block the more planes share its launch (from
+    one tile to sixteen); every plane of a batch is the single call's plane bit for bit."""
+    banner(f"pipelined column sweep n={n}: {count} planes")
+    dx, z = 2.5e-5, n / 4096.0
+    lams = [500e-9 + 20e-9 * i for i in range(count)]
+    g = torch.Generator(device="cuda:0").manual_seed(n + count)
+    fields = [torch.randn((n, n), generator=g, device="cuda:0", dtype=torch.complex64) for _ in range(count)]
+    amp = 0.5 + 0.5 * torch.rand((n, n), generator=g, device="cuda:0")
+    for adjoint in (False, True):
+        batch = [f.clone() for f in fields]
+        fb.fresnel_step_batched(batch, dx, lams, z, amps=amp, adjoints=adjoint)
+        for f, lam, got in zip(fields, lams, batch):
+            one = f.clone()
+            fb.fresnel_step(one, dx, lam, z, amp=amp, adjoint=adjoint)
+            assert torch.equal(one, got)
