@@ -653,27 +653,34 @@ hipError_t launch_fresnel_batch(const PlaneArgs *planes, int count, int n, const
     else
       fwd.p[nf++] = planes[i];
   }
+  // Tiles: rows per row block, columns per column tile, elements of the next tile in flight. Small
+  // tiles keep the chip in blocks: a single 256^2 plane took 20 us with 16 rows and 32 columns (16
+  // and 8 blocks) and takes 12 us, a 512^2 plane 27 us with 4 rows and 16 columns and 12 us, 21 of
+  // them 87 us and 51 us, a 1024^2 plane 32 us with 4 and 8 and 23 us. From 2048 the column tile
+  // fills half a compute unit or more and the pipelined sweep wins: a 2048^2 plane 54 us with 2
+  // rows and 8 columns, 45 us; the 4096^2 column sweeps 92 and 115 us to 83 and 100 us (forward,
+  // adjoint), the 8192^2 ones 877 us to 705 us.
 #define FR_SWEEPS(...) return launch_sweeps<__VA_ARGS__>(fwd, nf, adj, na, root, s, hook)
   switch (n) {
     case 64: {
       using P = Plan<64, 8, 8, 8>;
-      FR_SWEEPS(P, 8, 16);
+      FR_SWEEPS(P, 8, 8);
     }
     case 128: {
       using P = Plan<128, 16, 16, 8>;
-      FR_SWEEPS(P, 16, 32);
+      FR_SWEEPS(P, 8, 8);
     }
     case 256: {
       using P = Plan<256, 16, 16, 16>;
-      FR_SWEEPS(P, 16, 32);
+      FR_SWEEPS(P, 4, 4);
     }
     case 512: {
       using P = Plan<512, 8, 8, 8, 8>;
-      FR_SWEEPS(P, 4, 16);
+      FR_SWEEPS(P, 1, 4);
     }
     case 1024: {
       using P = Plan<1024, 16, 16, 8, 8>;
-      FR_SWEEPS(P, 4, 8);
+      FR_SWEEPS(P, 1, 4);
     }
     case 2048: {
       using P2 = Plan<2048, 16, 16, 16, 8>;
@@ -760,11 +767,11 @@ hipError_t launch_exact_sweeps(const PlaneArgs *planes, int count, const float2 
 hipError_t launch_exact_batch(const PlaneArgs *planes, int count, int n, const float2 *root, hipStream_t s,
                               const LaunchHook &hook, uint64_t split) {
   switch (n) {
-    case 64: return launch_exact_sweeps<Plan<64, 8, 8, 8>, 8, 16>(planes, count, root, s, hook, split);
-    case 128: return launch_exact_sweeps<Plan<128, 16, 16, 8>, 16, 32>(planes, count, root, s, hook, split);
-    case 256: return launch_exact_sweeps<Plan<256, 16, 16, 16>, 16, 32>(planes, count, root, s, hook, split);
-    case 512: return launch_exact_sweeps<Plan<512, 8, 8, 8, 8>, 4, 16>(planes, count, root, s, hook, split);
-    case 1024: return launch_exact_sweeps<Plan<1024, 16, 16, 8, 8>, 4, 8>(planes, count, root, s, hook, split);
+    case 64: return launch_exact_sweeps<Plan<64, 8, 8, 8>, 8, 8>(planes, count, root, s, hook, split);
+    case 128: return launch_exact_sweeps<Plan<128, 16, 16, 8>, 8, 8>(planes, count, root, s, hook, split);
+    case 256: return launch_exact_sweeps<Plan<256, 16, 16, 16>, 4, 4>(planes, count, root, s, hook, split);
+    case 512: return launch_exact_sweeps<Plan<512, 8, 8, 8, 8>, 1, 4>(planes, count, root, s, hook, split);
+    case 1024: return launch_exact_sweeps<Plan<1024, 16, 16, 8, 8>, 1, 4>(planes, count, root, s, hook, split);
     case 2048: return launch_exact_sweeps<Plan<2048, 16, 16, 16, 8>, 1, 4, 12>(planes, count, root, s, hook, split);
     case 4096: return launch_exact_sweeps<Plan<4096, 16, 16, 16, 16>, 1, 4, 16>(planes, count, root, s, hook, split);
     case 8192: return launch_exact_sweeps<Plan<8192, 16, 16, 16, 16, 2>, 1, 2, 16>(planes, count, root, s, hook, split);
@@ -784,11 +791,11 @@ hipError_t launch_direct_batch(const PlaneArgs *planes, int count, int n, const 
   }
 #define FR_DIRECT(PL, RL, CL, PF) return launch_sweeps<PL, RL, CL, PF, true>(fwd, nf, adj, na, root, s, hook)
   switch (n) {
-    case 64: { using P = Plan<64, 8, 8, 8>; FR_DIRECT(P, 8, 16, 0); }
-    case 128: { using P = Plan<128, 16, 16, 8>; FR_DIRECT(P, 16, 32, 0); }
-    case 256: { using P = Plan<256, 16, 16, 16>; FR_DIRECT(P, 16, 32, 0); }
-    case 512: { using P = Plan<512, 8, 8, 8, 8>; FR_DIRECT(P, 4, 16, 0); }
-    case 1024: { using P = Plan<1024, 16, 16, 8, 8>; FR_DIRECT(P, 4, 8, 0); }
+    case 64: { using P = Plan<64, 8, 8, 8>; FR_DIRECT(P, 8, 8, 0); }
+    case 128: { using P = Plan<128, 16, 16, 8>; FR_DIRECT(P, 8, 8, 0); }
+    case 256: { using P = Plan<256, 16, 16, 16>; FR_DIRECT(P, 4, 4, 0); }
+    case 512: { using P = Plan<512, 8, 8, 8, 8>; FR_DIRECT(P, 1, 4, 0); }
+    case 1024: { using P = Plan<1024, 16, 16, 8, 8>; FR_DIRECT(P, 1, 4, 0); }
     case 2048: { using P = Plan<2048, 16, 16, 16, 8>; FR_DIRECT(P, 1, 4, 12); }
     case 4096: { using P = Plan<4096, 16, 16, 16, 16>; FR_DIRECT(P, 1, 4, 16); }
     case 8192: { using P = Plan<8192, 16, 16, 16, 16, 2>; FR_DIRECT(P, 1, 2, 16); }
