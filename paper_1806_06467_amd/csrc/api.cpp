@@ -557,7 +557,9 @@ int run_planes(Ctx *ctx, PlaneArgs *args, int count, hipStream_t s) {
   }
   const int nr = int(rest.size());
   for (int i = 0; i < nr;) {
-    const int j = group_end(rest.data(), nr, i, kMrMaxBatch);
+    int j = group_end(rest.data(), nr, i, kMrMaxBatch);
+    // one class per launch: a plane's kernels do not depend on its company
+    while (mr_class(rest[j - 1].n) != mr_class(rest[i].n)) --j;
     MrBatch b;
     b.count = j - i;
     b.total = 0;

@@ -11,30 +11,54 @@
 
 namespace fr {
 
+// A table of float2 as a raw buffer: one per-lane byte offset and a wave-uniform one, so the legs of
+// a butterfly share an address register.
+struct MrTable {
+  __amdgpu_buffer_rsrc_t r;
+  __device__ __forceinline__ explicit MrTable(const float2 *p)
+      : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<float2 *>(p), (short)0, 0x7fffffff, 0x00020000)) {}
+  __device__ __forceinline__ c32 load(unsigned vo, unsigned so) const {
+    const float2 q = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(r, vo, so, 0));
+    return {q.x, q.y};
+  }
+};
+
+// b / P for 0 <= b < 4096 and 1 <= P <= 4096 from rp = 1 / P rounded: (b + 1/2) / P is at least
+// 1 / (2 P) from an integer, its float32 error below 0.002 / P
+__device__ __forceinline__ int mr_div(int b, float rp) { return int((float(b) + 0.5f) * rp); }
+
 template <int R, bool INV, int T, int MAXN>
 __device__ __forceinline__ void mr_pass_r(c32 *lds, int n, int P, const float2 *__restrict__ tw, int t,
                                           const float2 *__restrict__ h, bool hconj) {
   const int nr = n / R;
   constexpr int NBMAX = (MAXN / R + T - 1) / T;
+  const float rp = 1.0f / float(P);
+  const MrTable tt(tw), ht(h);
   c32 u[NBMAX][R];
 #pragma unroll
   for (int i = 0; i < NBMAX; ++i) {
     const int b = t + i * T;
     if (b < nr) {
+      if (h) {
+        c32 q[R];
 #pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const int e = b + r * nr;
-        c32 x = lds[lds_pad(e)];
-        if (h) x = hconj ? cmulc(x, c32{h[e].x, h[e].y}) : cmul(x, c32{h[e].x, h[e].y});
-        u[i][r] = x;
+        for (int r = 0; r < R; ++r) q[r] = ht.load(unsigned(b) * 8u, unsigned(r * nr) * 8u);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          const c32 x = lds[lds_pad(b + r * nr)];
+          u[i][r] = hconj ? cmulc(x, q[r]) : cmul(x, q[r]);
+        }
+      } else {
+#pragma unroll
+        for (int r = 0; r < R; ++r) u[i][r] = lds[lds_pad(b + r * nr)];
       }
       if (P > 1) {
-        const int k = b % P;
+        const int k = b - mr_div(b, rp) * P;
+        c32 q[R];
 #pragma unroll
-        for (int r = 1; r < R; ++r) {
-          const float2 q = tw[(r - 1) * P + k];
-          u[i][r] = INV ? cmulc(u[i][r], c32{q.x, q.y}) : cmul(u[i][r], c32{q.x, q.y});
-        }
+        for (int r = 1; r < R; ++r) q[r] = tt.load(unsigned(k) * 8u, unsigned((r - 1) * P) * 8u);
+#pragma unroll
+        for (int r = 1; r < R; ++r) u[i][r] = INV ? cmulc(u[i][r], q[r]) : cmul(u[i][r], q[r]);
       }
       DftDir<R, INV>::run(u[i]);
     }
@@ -44,7 +68,7 @@ __device__ __forceinline__ void mr_pass_r(c32 *lds, int n, int P, const float2 *
   for (int i = 0; i < NBMAX; ++i) {
     const int b = t + i * T;
     if (b < nr) {
-      const int base = (b / P) * (P * R) + (b % P);
+      const int base = b + mr_div(b, rp) * P * (R - 1);  // (b / P) P R + b mod P
 #pragma unroll
       for (int r = 0; r < R; ++r) lds[lds_pad(base + r * P)] = u[i][r];
     }

@@ -83,7 +83,6 @@ bool plane_size_supported(int n);    // those or any mixed-radix edge
 // ---- mixed-radix sweeps (any edge up to kMrMaxN that factors into radices <= 16) ----------
 constexpr int kMrMaxN = 4096;
 constexpr int kMrMaxPass = 6;
-constexpr int kMrThreads = 256;
 constexpr int kMrMaxBatch = 24;
 struct MrPlane {
   PlaneArgs pa;
@@ -104,13 +103,17 @@ void mr_twiddle_build(int npass, const int *radix, float2 *out);  // host
 // rows then columns for forward planes, columns then rows for adjoint planes; persistent grids
 // of cus x the resident blocks per compute unit of the instance that runs them (a compile-time
 // plan when every plane has the same edge and one of the broadband grids' plans, else the
-// runtime plan)
+// runtime plan of the largest edge's class; a caller that gives each class a launch of its own
+// gets the same instance for a plane in any batch)
 hipError_t launch_mr_batch(const MrBatch &all, const int *rows_per_cu, const int *cols_per_cu, int cus,
                            hipStream_t s, const LaunchHook &hook);
+// classes of the runtime plan's instances by the longest line they hold: 256, 512, 1024, 2048, 4096
+constexpr int kMrClasses = 5;
+int mr_class(int n);
 // blocks of each instance of the two persistent sweeps that one compute unit holds at once
-// (index 0 the runtime plan, then the compile-time plans); a device query, made at context
+// (the runtime plan's classes, then the compile-time plans); a device query, made at context
 // creation
-constexpr int kMrPolicies = 8;
+constexpr int kMrPolicies = 12;
 void mr_resident(int *rows_per_cu, int *cols_per_cu);
 
 // ---- MFT: one product with the Fourier matrix, folded about its axis, on MFMA ------------

@@ -35,7 +35,7 @@ struct Ctx {
   int device = 0;
   int cus = 256;  // compute units of the device
   // resident blocks per compute unit of the mixed-radix sweep instances (mr_resident)
-  int mr_rows_per_cu[kMrPolicies] = {2, 2, 2, 2, 2, 2, 2, 2}, mr_cols_per_cu[kMrPolicies] = {1, 1, 1, 1, 1, 1, 1, 1};
+  int mr_rows_per_cu[kMrPolicies], mr_cols_per_cu[kMrPolicies];  // set at creation
   std::map<TableKey, void *> tables;
   size_t max_tables = 4096;  // fr_set_cache_limit
   // start of an entry point that may fetch tables (before the first fetch): trims the cache

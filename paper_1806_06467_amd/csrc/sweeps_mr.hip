@@ -28,8 +28,6 @@ namespace fr {
 
 namespace {
 
-constexpr int kT = kMrThreads;    // threads per line
-constexpr int kEM = kMrMaxN / kT;  // slots per thread for the global load / store
 
 struct Buf64 {
   __amdgpu_buffer_rsrc_t r;
@@ -107,18 +105,41 @@ __device__ __forceinline__ bool mr_has_pre(const PlaneArgs &pa) {
   return pa.amp || pa.opd || pa.pre_surf || pa.lens;
 }
 
-// The plan policy of a sweep instance: MrRuntime takes each plane's packed plan (any edge),
-// MrCt<N, Rs...> one compile-time plan (every plane of the launch has edge N and that plan).
+// The plan policy of a sweep instance: MrRuntime<C> takes each plane's packed plan (any edge of
+// class C: at most C, more than C / 2 above the smallest class), MrCt<N, Rs...> one compile-time
+// plan (every plane of the launch has edge N and that plan). A class sets the threads per line:
+// an eighth of its longest line, so that a radix-8 or larger pass runs one butterfly per thread
+// and few slots of the load, the optic and the store lie past the line's end (with 256 threads and
+// 16 slots for every edge a 1000^2 plane took 69 us, with 64 and 16 for its class 64 us, with 128
+// and 8 39 us); a sixteenth for the largest class, where 512 threads a row are slower (a 3000^2
+// row sweep 206 us against 133 us) and would leave no room for four columns.
+template <int C>
 struct MrRuntime {
   static constexpr int N = 0;
+  static constexpr int MAXN = C;
+};
+template <class F>
+struct MrDims {
+  static constexpr int MAXN = F::MAXN;
+  static constexpr int E = MAXN <= 2048 ? 8 : 16;     // slots per thread for the global load / store
+  static constexpr int T = MAXN / E;                  // threads per line
+  static constexpr int RL = T < 64 ? 64 / T : 1;      // rows per row block: at least one wavefront
+};
+template <int N, int... Rs>
+struct MrDims<MrCt<N, Rs...>> {
+  static constexpr int MAXN = kMrMaxN;
+  static constexpr int E = 16;
+  static constexpr int T = MAXN / E;
+  static constexpr int RL = 1;
 };
 
 template <class F, bool INV>
 __device__ __forceinline__ void plane_fft(c32 *lds, const MrPlane &mp, int t, const float2 *h, bool hconj) {
+  using D = MrDims<F>;
   if constexpr (F::N == 0)
-    mr_fft<INV, kT, kMrMaxN>(lds, mp.n, mp.npass, mp.plan, mp.tw, t, h, hconj);
+    mr_fft<INV, D::T, D::MAXN>(lds, mp.n, mp.npass, mp.plan, mp.tw, t, h, hconj);
   else
-    F::template fft<INV, kT>(lds, mp.tw, mr_opaque(t), h, hconj);
+    F::template fft<INV, D::T>(lds, mp.tw, mr_opaque(t), h, hconj);
 }
 
 // The batch is the kernel's only argument, so it sits at offset 0 of the kernel-argument
@@ -146,9 +167,9 @@ __device__ __forceinline__ int mr_item(int round) {
 // slots of the global load / store handled per batch of optic loads
 constexpr int kOptBatch = 8;
 
-// multiplies v[0..kEM) of row y by the pre optic (conjugated when CONJ), in batches of
+// multiplies v[0..E) of row y by the pre optic (conjugated when CONJ), in batches of
 // kOptBatch slots whose loads are issued together
-template <bool CONJ>
+template <bool CONJ, int kT, int kEM>
 __device__ __forceinline__ void apply_pre(c32 (&v)[kEM], const PlaneArgs &pa, int n, int y, int t, bool source) {
   const PreMaps pm(pa, n);
   const c32 ly = pm.lens.load(unsigned(y) * 8u);
@@ -166,17 +187,20 @@ __device__ __forceinline__ void apply_pre(c32 (&v)[kEM], const PlaneArgs &pa, in
 }
 
 template <class F>
-__global__ void __launch_bounds__(kT) mr_row_sweep(MrBatch) {
+__global__ void __launch_bounds__(MrDims<F>::T *MrDims<F>::RL) mr_row_sweep(MrBatch) {
+  constexpr int kT = MrDims<F>::T, kEM = MrDims<F>::E, RL = MrDims<F>::RL, LINE = LdsLine<MrDims<F>::MAXN>::size;
   const MrBatch &args = kernarg_batch();
-  __shared__ c32 lds[LdsLine<kMrMaxN>::size];
-  const int t0 = threadIdx.x;
+  __shared__ c32 lines[RL * LINE];
+  const int line = threadIdx.x / kT, t0 = threadIdx.x % kT;
+  c32 *lds = lines + line * LINE;
   for (int round = 0;; ++round) {
     const int item = mr_item(round);
     if (round * int(gridDim.x) >= args.total) break;
     if (item < args.total) {
       const MrPlane &mp = args.p[mr_find(args, item)];
       const PlaneArgs &pa = mp.pa;
-      const int n = F::N ? F::N : mp.n, y = item - mp.first;
+      const int n = F::N ? F::N : mp.n, y0 = (item - mp.first) * RL + line;
+      const int y = RL > 1 ? min(y0, n - 1) : y0;  // a last block's lines past the plane repeat its last row, unstored
       const int t = mr_opaque(t0);
       const bool adj = pa.flags & FR_ADJOINT;
       const bool source = pa.flags & kSourceOptic;
@@ -188,9 +212,9 @@ __global__ void __launch_bounds__(kT) mr_row_sweep(MrBatch) {
         for (int m = 0; m < kEM; ++m) v[m] = {1.0f, 0.0f};
       } else {
 #pragma unroll
-        for (int m = 0; m < kEM; ++m) v[m] = fb.load(unsigned(y * n + min(t + kT * m, n - 1)) * 8u);
+        for (int m = 0; m < kEM; ++m) v[m] = fb.load(unsigned(y * n + t + kT * m) * 8u);  // past the line: unused, past the plane: 0
       }
-      if (!adj && pre) apply_pre<false>(v, pa, n, y, t, source);
+      if (!adj && pre) apply_pre<false, kT, kEM>(v, pa, n, y, t, source);
 #pragma unroll
       for (int m = 0; m < kEM; ++m)
         if (t + kT * m < n) lds[lds_pad(t + kT * m)] = v[m];
@@ -199,10 +223,10 @@ __global__ void __launch_bounds__(kT) mr_row_sweep(MrBatch) {
       plane_fft<F, true>(lds, mp, t, pa.h, adj);
 #pragma unroll
       for (int m = 0; m < kEM; ++m) v[m] = lds[lds_pad(min(t + kT * m, n - 1))];
-      if (adj && pre) apply_pre<true>(v, pa, n, y, t, false);
+      if (adj && pre) apply_pre<true, kT, kEM>(v, pa, n, y, t, false);
 #pragma unroll
       for (int m = 0; m < kEM; ++m)
-        if (t + kT * m < n) fb.store(unsigned(y * n + t + kT * m) * 8u, v[m]);
+        if (t + kT * m < n && (RL == 1 || y0 < n)) fb.store(unsigned(y * n + t + kT * m) * 8u, v[m]);
       __syncthreads();
     }
   }
@@ -210,11 +234,12 @@ __global__ void __launch_bounds__(kT) mr_row_sweep(MrBatch) {
 
 // 4 adjacent columns per item (32-byte row segments), one line of kT threads per column
 template <class F>
-__global__ void __launch_bounds__(kT * 4) mr_col_sweep(MrBatch) {
+__global__ void __launch_bounds__(MrDims<F>::T * 4) mr_col_sweep(MrBatch) {
+  constexpr int kT = MrDims<F>::T, kEM = MrDims<F>::E, LINE = LdsLine<MrDims<F>::MAXN>::size + 4;
   const MrBatch &args = kernarg_batch();
-  __shared__ c32 lds[4 * (LdsLine<kMrMaxN>::size + 4)];
+  __shared__ c32 lds[4 * LINE];
   const int c = threadIdx.x & 3, t0 = threadIdx.x >> 2;
-  c32 *my = lds + c * (LdsLine<kMrMaxN>::size + 4);
+  c32 *my = lds + c * LINE;
   for (int round = 0;; ++round) {
     const int item = mr_item(round);
     if (round * int(gridDim.x) >= args.total) break;
@@ -462,42 +487,65 @@ unsigned mr_reg_plan(int n) {
 // calls f(policy) for the instance that runs planes of edge n with packed plan `plan` (the
 // runtime policy when no compile-time plan matches)
 template <class Fn, int I = 0>
-auto with_mr_policy(int n, unsigned plan, Fn &&f) {
+auto with_mr_policy(int n, unsigned plan, int cls, Fn &&f) {
   if constexpr (I == kMrCt) {
-    return f(MrRuntime{});
+    switch (cls) {
+      case 0: return f(MrRuntime<256>{});
+      case 1: return f(MrRuntime<512>{});
+      case 2: return f(MrRuntime<1024>{});
+      case 3: return f(MrRuntime<2048>{});
+      default: return f(MrRuntime<4096>{});
+    }
   } else {
     using P = std::tuple_element_t<I, MrCtPlans>;
     if (n == P::N && plan == P::packed()) return f(P{});
-    return with_mr_policy<Fn, I + 1>(n, plan, std::forward<Fn>(f));
+    return with_mr_policy<Fn, I + 1>(n, plan, cls, std::forward<Fn>(f));
   }
 }
 
+template <class P>
+void resident_of(int *rows, int *cols) {
+  using D = MrDims<P>;
+  *rows = resident_blocks(mr_row_sweep<P>, D::T * D::RL, 2);
+  *cols = resident_blocks(mr_col_sweep<P>, 4 * D::T, 1);
+}
 template <int I = 0>
 void resident_all(int *rows, int *cols) {
-  if constexpr (I <= kMrCt) {
-    using P = std::conditional_t<I == 0, MrRuntime, std::tuple_element_t<(I > 0 ? I - 1 : 0), MrCtPlans>>;
-    rows[I] = resident_blocks(mr_row_sweep<P>, kT, 2);
-    cols[I] = resident_blocks(mr_col_sweep<P>, 4 * kT, 1);
+  if constexpr (I == 0) {
+    resident_of<MrRuntime<256>>(rows + 0, cols + 0);
+    resident_of<MrRuntime<512>>(rows + 1, cols + 1);
+    resident_of<MrRuntime<1024>>(rows + 2, cols + 2);
+    resident_of<MrRuntime<2048>>(rows + 3, cols + 3);
+    resident_of<MrRuntime<4096>>(rows + 4, cols + 4);
+  }
+  if constexpr (I < kMrCt) {
+    resident_of<std::tuple_element_t<I, MrCtPlans>>(rows + kMrClasses + I, cols + kMrClasses + I);
     resident_all<I + 1>(rows, cols);
   }
 }
 
-// 0 for the runtime plan, 1 + the index of the matching compile-time plan
+// -1 for the runtime plan, else the index of the matching compile-time plan
 template <int I = 0>
 int mr_policy_index(int n, unsigned plan) {
   if constexpr (I == kMrCt) {
-    return 0;
+    return -1;
   } else {
     using P = std::tuple_element_t<I, MrCtPlans>;
-    if (n == P::N && plan == P::packed()) return I + 1;
+    if (n == P::N && plan == P::packed()) return I;
     return mr_policy_index<I + 1>(n, plan);
   }
 }
 
 unsigned mr_default_plan(int n) { return mr_reg_plan(n); }
 
+int mr_class(int n) {
+  int c = 0;
+  while (c + 1 < kMrClasses && n > (256 << c)) ++c;
+  return c;
+}
+
 void mr_resident(int *rows_per_cu, int *cols_per_cu) {
-  static_assert(kMrCt + 1 <= kMrPolicies, "residency table size");
+  static_assert(kMrClasses + kMrCt <= kMrPolicies, "residency table size");
   resident_all(rows_per_cu, cols_per_cu);
 }
 
@@ -512,11 +560,11 @@ hipError_t launch_mr_batch(const MrBatch &all, const int *rows_per_cu, const int
     MrBatch &dst = (all.p[i].pa.flags & FR_ADJOINT) ? adj : fwd;
     dst.p[dst.count++] = all.p[i];
   }
-  auto rows_list = [](MrBatch &b) {
+  auto rows_list = [](MrBatch &b, int rows_per_item) {
     int acc = 0;
     for (int i = 0; i < b.count; ++i) {
       b.p[i].first = acc;
-      acc += b.p[i].n;
+      acc += (b.p[i].n + rows_per_item - 1) / rows_per_item;
     }
     b.total = acc;
   };
@@ -529,29 +577,34 @@ hipError_t launch_mr_batch(const MrBatch &all, const int *rows_per_cu, const int
     b.total = acc;
   };
   // one compile-time instance when every plane of the batch has the same edge and its plan
-  int pol = all.count ? mr_policy_index(all.p[0].n, all.p[0].plan) : 0;
-  for (int i = 1; i < all.count && pol; ++i)
-    if (all.p[i].n != all.p[0].n || all.p[i].plan != all.p[0].plan) pol = 0;
+  int pol = all.count ? mr_policy_index(all.p[0].n, all.p[0].plan) : -1;
+  int cls = 0;
+  for (int i = 0; i < all.count; ++i) {
+    if (all.p[i].n != all.p[0].n || all.p[i].plan != all.p[0].plan) pol = -1;
+    cls = std::max(cls, mr_class(all.p[i].n));
+  }
   // one register-resident instance when every plane has the same edge and its plan
   bool same = all.count > 0;
   for (int i = 1; i < all.count && same; ++i)
     if (all.p[i].n != all.p[0].n || all.p[i].plan != all.p[0].plan) same = false;
   const int nr = same ? all.p[0].n : 0;
   const unsigned planr = same ? all.p[0].plan : 0u;
-  const int n0 = pol ? all.p[0].n : 0;
-  const unsigned plan0 = pol ? all.p[0].plan : 0u;
-  const int blocks_rows = cus * rows_per_cu[pol], blocks_cols = cus * cols_per_cu[pol];
+  const int n0 = pol >= 0 ? all.p[0].n : 0;
+  const unsigned plan0 = pol >= 0 ? all.p[0].plan : 0u;
+  const int idx = pol >= 0 ? kMrClasses + pol : cls;
+  const int blocks_rows = cus * rows_per_cu[idx], blocks_cols = cus * cols_per_cu[idx];
   auto rows = [&](MrBatch b, const char *name) {
-    rows_list(b);
     hook(s, name, b.count, 0);
     const bool reg = with_mr_reg(nr, planr, [&](auto p) {
       using P = decltype(p);
       hipLaunchKernelGGL((mrr_row_sweep<P>), dim3(P::N, b.count), dim3(P::T), 0, s, b);
     });
     if (!reg)
-      with_mr_policy(n0, plan0, [&](auto p) {
+      with_mr_policy(n0, plan0, cls, [&](auto p) {
+        using D = MrDims<decltype(p)>;
+        rows_list(b, D::RL);
         hipLaunchKernelGGL((mr_row_sweep<decltype(p)>), dim3(std::max(1, std::min(blocks_rows, b.total))),
-                           dim3(kT), 0, s, b);
+                           dim3(D::T * D::RL), 0, s, b);
       });
     hipError_t e = hipGetLastError();
     hook(s, name, b.count, 1);
@@ -565,9 +618,9 @@ hipError_t launch_mr_batch(const MrBatch &all, const int *rows_per_cu, const int
       hipLaunchKernelGGL((mrr_col_sweep<P>), dim3(P::N / 4, b.count), dim3(4 * P::T), 0, s, b);
     });
     if (!reg)
-      with_mr_policy(n0, plan0, [&](auto p) {
+      with_mr_policy(n0, plan0, cls, [&](auto p) {
         hipLaunchKernelGGL((mr_col_sweep<decltype(p)>), dim3(std::max(1, std::min(blocks_cols, b.total))),
-                           dim3(4 * kT), 0, s, b);
+                           dim3(4 * MrDims<decltype(p)>::T), 0, s, b);
       });
     hipError_t e = hipGetLastError();
     hook(s, name, b.count, 1);

@@ -508,3 +508,17 @@ def test_pipelined_column_tiles_per_block_agree_bitwise(n, count):
             one = f.clone()
             fb.fresnel_step(one, dx, lam, z, amp=amp, adjoint=adjoint)
             assert torch.equal(one, got)
+
+
+@pytest.mark.parametrize("adjoint", [False, True])
+@pytest.mark.parametrize("n", [2, 255, 256 + 14, 511 - 7, 525, 1023 - 15, 1029, 2025, 2058])
+def test_mixed_radix_class_edges(n, adjoint):
+    """Edges just below and above the classes of the runtime mixed-radix sweeps (256, 512, 1024,
+    2048 points per line), odd ones among them, row blocks that end past the plane included."""
+    if not fb.lib().fr_fft_size_supported(n):
+        n = max(m for m in range(2, n) if fb.lib().fr_fft_size_supported(m))
+    banner(f"mixed-radix class edge n={n} adjoint={adjoint}")
+    field, amp, opd, dx, lam, z, f = _case(n, 3 * n + adjoint)
+    got = _run_gpu(field, amp, opd, dx, lam, z, f, adjoint)
+    ref = oracle.fresnel_step(f32(field), dx, lam, z, amp=f32(amp), opd=f32(opd), lens_focal=f, adjoint=adjoint)
+    assert rel_l2(got, ref) <= TOL

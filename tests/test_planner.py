@@ -4,6 +4,7 @@ carries a field between two planes, and the pitch on each side, for every near /
 import ctypes
 import math
 
+import numpy as np
 import pytest
 
 from paper_1806_06467_amd import fresnel as fb
@@ -63,3 +64,12 @@ def test_argument_errors():
     assert L.fr_plan_route(W0, 0.0, LAM, N, DX, float("nan"), 1.0, steps, 2) == fb.FR_EINVAL
     assert L.fr_plan_route(W0, 0.0, LAM, N, DX, 0.0, 1.0, steps, 1) == fb.FR_EINVAL
     assert L.fr_plan_route(W0, 0.0, LAM, N, DX, 0.0, 1.0, None, 2) == fb.FR_EINVAL
+
+
+def test_mixed_radix_division_is_exact():
+    # the sweeps divide a butterfly's index by the pass's span through a float32 reciprocal
+    b = np.arange(4096, dtype=np.float32)
+    for p in range(1, 4097):
+        rp = np.float32(1.0) / np.float32(p)
+        for r in (rp, np.nextafter(rp, np.float32(0)), np.nextafter(rp, np.float32(2))):
+            assert np.array_equal(((b + np.float32(0.5)) * r).astype(np.int32), np.arange(4096) // p), p
