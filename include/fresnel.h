@@ -396,8 +396,9 @@ int propagate_train(fr_ctx *ctx, const fr_train_desc *desc, int32_t n_lambda,
  * a hot loop or a graph capture. Errors: FR_EINVAL, FR_EUNSUPPORTED, FR_ENOMEM, FR_EHIP.
  * fr_autotune_save / fr_autotune_load write / read the tuned choices as a text file (one
  * "sweep n variant [planes]" (planes: the power-of-two sweeps' planes per launch in batched calls,
- * 1..64, or 0 = as many as fit the last-level cache together), "plan n packed_order" (radices
- * 2-10, 12, 14, 15 or 16, 5 bits each from the first pass up, at most 6, product n),
+ * 1..64, or 0 = as many as fit the last-level cache together), "plan n packed_order" (the
+ * edge's default plan, or radices 2-10, 12, 14, 15 or 16, 5 bits each from the first pass up, at most
+ * 6, product n),
  * "gemm M N K transA transB tile [split]" or
  * "gemm_default tile split" per line: an MFT product's output rows and columns, input length, 0 and
  * 1 for a product along rows or 0 for one along columns, a tile number 0-6 that is kept but selects

@@ -175,9 +175,10 @@ int tune_mft(Ctx *ctx, int n, int m, hipStream_t s) {
   return record_hip(hipStreamSynchronize(s));
 }
 
-// a pass order read back from a file: radices the sweeps support (2-10, 12, 14, 15, 16), at
-// most kMrMaxPass of them, whose product is the edge
+// a pass order read back from a file: the edge's default plan, or radices every sweep supports
+// (2-10, 12, 14, 15, 16), at most kMrMaxPass of them, whose product is the edge
 bool valid_plan(int n, unsigned plan) {
+  if (plan != 0 && plan == mr_default_plan(n)) return true;
   int np = 0, greedy[kMrMaxPass];
   if (!mr_plan(n, &np, greedy)) return false;
   long long prod = 1;

@@ -1,4 +1,4 @@
-// Register-resident small DFTs (radix 2, 3, 4, 5, 6, 7, 8, 9, 10, 12, 14, 15, 16) and
+// Register-resident small DFTs (radix 2-10, 12, 14-16, 18, 20, 24, 28) and
 // compile-time twiddles.
 //
 // These are the butterflies of the Cooley-Tukey FFT that the paper relies on for its
@@ -296,7 +296,13 @@ struct Dft<8> : DftComposite<2, 4> {};
 template <>
 struct Dft<16> : DftComposite<4, 4> {};
 template <>
-struct Dft<32> : DftComposite<4, 8> {};
+struct Dft<18> : DftComposite<3, 6> {};
+template <>
+struct Dft<20> : DftComposite<4, 5> {};
+template <>
+struct Dft<24> : DftComposite<4, 6> {};
+template <>
+struct Dft<28> : DftComposite<4, 7> {};
 
 // Inverse-direction DFT (kernel exp(+2 pi i nk/R)): X_inv[k] = X_fwd[(R - k) mod R], so the
 // forward butterfly is reused and its outputs are renamed (no arithmetic).

@@ -207,6 +207,7 @@ template <int N, int R, int P, bool INV, int T>
 __device__ __forceinline__ void mrr_mid_pass(c32 *lds, const float2 *__restrict__ tw, int t) {
   constexpr int NR = N / R;
   constexpr int NB = (NR + T - 1) / T;
+  const MrTable tt(tw);
   c32 u[NB][R];
 #pragma unroll
   for (int i = 0; i < NB; ++i) {
@@ -224,8 +225,8 @@ __device__ __forceinline__ void mrr_mid_pass(c32 *lds, const float2 *__restrict_
       const int k = b % P;
 #pragma unroll
       for (int r = 1; r < R; ++r) {
-        const float2 q = tw[(r - 1) * P + k];
-        u[i][r] = INV ? cmulc(u[i][r], c32{q.x, q.y}) : cmul(u[i][r], c32{q.x, q.y});
+        const c32 q = tt.load(unsigned(k) * 8u, unsigned((r - 1) * P) * 8u);
+        u[i][r] = INV ? cmulc(u[i][r], q) : cmul(u[i][r], q);
       }
       DftDir<R, INV>::run(u[i]);
       const int base = (b / P) * (P * R) + k;
@@ -247,6 +248,7 @@ __device__ __forceinline__ void mrr_passes(c32 (&v)[E], c32 *lds, int t, const f
     // and leaves output r in the same slot
     static_assert(P * R == N && E % R == 0, "the last radix must divide the elements per thread");
     constexpr int NB = E / R;
+    const MrTable tt(tw);
     c32 u[NB][R];
 #pragma unroll
     for (int j = 0; j < NB; ++j)
@@ -258,8 +260,8 @@ __device__ __forceinline__ void mrr_passes(c32 (&v)[E], c32 *lds, int t, const f
       const int k = t + j * T;
 #pragma unroll
       for (int r = 1; r < R; ++r) {
-        const float2 q = tw[(r - 1) * P + k];
-        u[j][r] = INV ? cmulc(u[j][r], c32{q.x, q.y}) : cmul(u[j][r], c32{q.x, q.y});
+        const c32 q = tt.load(unsigned(k) * 8u, unsigned((r - 1) * P) * 8u);
+        u[j][r] = INV ? cmulc(u[j][r], q) : cmul(u[j][r], q);
       }
       DftDir<R, INV>::run(u[j]);
 #pragma unroll

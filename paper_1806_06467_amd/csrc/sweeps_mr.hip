@@ -328,15 +328,18 @@ __device__ __forceinline__ void apply_pre_reg(c32 (&v)[E], const PlaneArgs &pa, 
 // the frequency product with h (conj(h) for the adjoint); slot m holds frequency t + T m
 template <int E, int T>
 __device__ __forceinline__ void freq_reg(c32 (&v)[E], const float2 *h, int t, bool adj) {
+  const MrTable ht(h);
 #pragma unroll
   for (int m = 0; m < E; ++m) {
-    const float2 q = h[t + T * m];
-    v[m] = adj ? cmulc(v[m], c32{q.x, q.y}) : cmul(v[m], c32{q.x, q.y});
+    if (m % 8 == 0) __builtin_amdgcn_sched_barrier(0);  // eight loads at a time beside the line
+    const c32 q = ht.load(unsigned(t) * 8u, unsigned(T * m) * 8u);
+    v[m] = adj ? cmulc(v[m], q) : cmul(v[m], q);
   }
 }
 
+// (three waves per SIMD: left alone the 3920 plan takes 183 registers, which allow two: 197 us)
 template <class F>
-__global__ void __launch_bounds__(F::T) mrr_row_sweep(MrBatch) {
+__global__ void __launch_bounds__(F::T) __attribute__((amdgpu_waves_per_eu(3))) mrr_row_sweep(MrBatch) {
   constexpr int N = F::N, E = F::E, T = F::T;
   const MrBatch &args = kernarg_batch();
   __shared__ c32 lds[LdsLine<N>::size];
@@ -446,17 +449,21 @@ using MrCtPlans = std::tuple<MrCt<3584, 16, 16, 14>, MrCt<3600, 16, 15, 15>, MrC
 constexpr int kMrCt = std::tuple_size<MrCtPlans>::value;
 
 // register-resident plans of the same edges: factorisations whose first and last radices divide
-// the elements per thread (E), T = N / E threads per line, 4 T per column tile. With E = 14 or 15
-// and every middle radix 16 a middle pass's butterflies fit the threads (one each), so 3584, 3600
-// and 3840 run as the power-of-two sweeps do (measured per plane, rows / columns: 3584 81 / 109 us
-// against 113 / 124 us for the greedy compile-time plan, 3600 96 / 104 against 117 / 129, 3840
-// 99 / 119 against 118 / 134); for 4032 the middle passes take two rounds and the column sweep
-// spills at its 128 registers (152 / 179 against 181 / 166 us: still ahead over both sweeps).
-// 3888, 3920 and 4000 have no such factorisation under the 256-thread lines of a 4-column tile
-// and keep the greedy compile-time plans. These orders are the edges' default plans
-// (mr_default_plan); a tuning file may choose another.
+// the elements per thread (E), T = N / E threads per line, 4 T per column tile, and whose middle
+// passes leave few threads idle. With E = 14 or 15 and every middle radix 16 a middle pass's
+// butterflies fit the threads, so 3584, 3600 and 3840 run as the power-of-two sweeps do (measured
+// per plane, rows / columns: 3584 81 / 109 us against 113 / 124 us for the greedy compile-time
+// plan, 3600 96 / 104 against 117 / 129, 3840 99 / 119 against 118 / 134). 3888, 3920, 4000 and
+// 4032 take three passes with two or three butterflies per thread in the middle one (324 on 216
+// threads, 392 on 140, 400 on 200, 288 on 168) and large first and last radices: 3888 120 / 121 us
+// against 159 / 147 for the greedy compile-time plan, 3920 169 / 130 against 174 / 183, 4000 179 /
+// 135 against 180 / 159, 4032 132 / 133 against 165 / 204 for 9.16.14.2.
+// These orders are the edges' default plans (mr_default_plan; the last entry of 4032 is the one
+// that older tuning files name); a tuning file may choose another.
 using MrRegPlans = std::tuple<MrReg<3584, 14, 7, 16, 16, 2>, MrReg<3600, 15, 15, 16, 15>,
-                              MrReg<3840, 15, 3, 16, 16, 5>, MrReg<4032, 18, 9, 16, 14, 2>>;
+                              MrReg<3840, 15, 3, 16, 16, 5>, MrReg<3888, 18, 18, 12, 18>,
+                              MrReg<3920, 28, 14, 10, 28>, MrReg<4000, 20, 20, 10, 20>,
+                              MrReg<4032, 24, 24, 14, 12>, MrReg<4032, 18, 9, 16, 14, 2>>;
 constexpr int kMrReg = std::tuple_size<MrRegPlans>::value;
 
 // calls f(policy) and returns true when a register-resident plan runs edge n with plan `plan`

@@ -522,3 +522,33 @@ def test_mixed_radix_class_edges(n, adjoint):
     got = _run_gpu(field, amp, opd, dx, lam, z, f, adjoint)
     ref = oracle.fresnel_step(f32(field), dx, lam, z, amp=f32(amp), opd=f32(opd), lens_focal=f, adjoint=adjoint)
     assert rel_l2(got, ref) <= TOL
+
+
+@pytest.mark.parametrize("n,plan", [(3888, (18, 12, 18)), (3920, (14, 10, 28)), (4000, (20, 10, 20)),
+                                    (4032, (24, 14, 12))])
+def test_three_pass_plans_in_any_company(n, plan, tmp_path):
+    """The three-pass register-resident plans (radices past 16, named by a tuning file) against
+    the oracle's separable form on sampled columns, and bit for bit the same in a batch with edges
+    of other plans."""
+    banner(f"three-pass plan n={n}")
+    dx, lam, z = 2.5e-5, 550e-9, 0.9
+    saved = tmp_path / "saved.txt"
+    fb.autotune_save(str(saved))
+    (tmp_path / "plan.txt").write_text("plan %d %d\n" % (n, plan[0] | plan[1] << 5 | plan[2] << 10))
+    try:
+        fb.autotune_load(str(tmp_path / "plan.txt"))
+        field = synth.random_field(n, n)
+        one = to_gpu(field)
+        fb.fresnel_step(one, dx, lam, z)
+        others = [to_gpu(synth.random_field(m, m)) for m in (250, 1000, 2500)]
+        batch = [others[2], to_gpu(field), others[0], to_gpu(field), others[1]]
+        fb.fresnel_step_batched(batch, dx, lam, z)
+        assert torch.equal(batch[1], one) and torch.equal(batch[3], one)
+    finally:
+        fb.autotune_load(str(saved))
+    # sampled columns: the row pass of every row, then the column pass of a few columns
+    k = np.fft.fftfreq(n, d=1.0 / n)
+    h = np.exp(-1j * np.pi * lam * z * (k / (n * dx)) ** 2)
+    rows = np.fft.ifft(np.fft.fft(f32(field), axis=1) * h, axis=1)[:, [0, 1, n // 2, n - 1]]
+    want = np.fft.ifft(np.fft.fft(rows, axis=0) * h[:, None], axis=0)
+    assert rel_l2(to_np(one)[:, [0, 1, n // 2, n - 1]], want) <= TOL
