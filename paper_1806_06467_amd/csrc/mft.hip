@@ -582,7 +582,12 @@ hipError_t launch_short_kernel(const FoldArgs &a, hipStream_t stream) {
   return hipGetLastError();
 }
 
-bool short_pairs(const FoldArgs &a) { return a.Q / 2 <= kShortPairs; }
+// short sums over an output large enough that every wave walks tiles: below that the general
+// kernel's two halves of every stage on different waves are faster (256^2 -> 1024^2 with mask and
+// background 16 us against 37 us, 256^2 -> 2048^2 43 us against 25 us)
+bool short_pairs(const FoldArgs &a) {
+  return a.Q / 2 <= kShortPairs && (long long)fold_tiles(a.P) * div_up(a.F, kFoldFree) >= 1024;
+}
 
 }  // namespace
 
