@@ -14,8 +14,8 @@
 // exp(-i pi c(i)^2 dx^2 / (lambda f)) and the twiddles, every phase formed from an exact integer
 // times a float64 constant and reduced to a fraction of a turn before the float64 cos / sin.
 // A complex float64 line of n elements takes 16 n bytes of LDS (plus the padding of
-// fft_line.hpp), so the tiles hold half the lines of the float32 sweeps' (2048 and 4096: one row
-// per row block, two columns per column tile, 32-byte row pieces; 8192: one of each). From 1024
+// fft_line.hpp), so the tiles of 2048 and 4096 hold one row per row block and two columns per
+// column tile (32-byte row pieces), those of 8192 one of each. From 1024
 // to 4096 the plans hold 8 elements per thread (radix-8 passes) where the float32 sweeps hold 16:
 // twice the threads per line, under 128 VGPRs, so a compute unit runs 16 waves of the column
 // sweep instead of 8 (measured at 4096: 200 us against 247 us per row sweep).
@@ -139,6 +139,59 @@ __global__ void __launch_bounds__(PL::T *LINES) col_sweep64(Batch64 args, const 
   for (int m = 0; m < E; ++m) col[size_t(t + T * m) * N] = make_double2(v[m].x, v[m].y);
 }
 
+// The column sweep from 2048: as the float32 one (col_sweep_pipe in sweeps.hip), one block per
+// compute unit walks the tiles of the plane and loads the next one while it transforms the current
+// one; the exchanges move real and imaginary parts in turn through lines of doubles and the
+// twiddles lie in LDS. Measured at 4096^2: 235 us to 225 us (the 4 MiB that an XCD has in flight exceed its L2).
+template <class PL, int LINES>
+__global__ void __launch_bounds__(PL::T *LINES) __attribute__((amdgpu_waves_per_eu(4)))
+col_sweep64_pipe(Batch64 args, const double2 *tw, int tiles) {
+  constexpr int N = PL::N, E = PL::E, T = PL::T;
+  constexpr int LINE = LdsLine<N>::size + 8;
+  __shared__ double lds[LINES * LINE];
+  __shared__ double2 tab[PL::twiddles];
+  const Plane64 &pa = args.p[blockIdx.y];
+  const int c = threadIdx.x % LINES, t = threadIdx.x / LINES;
+  // the blocks of one XCD take tiles in runs that fill a 128-byte line of each row, and walk from a
+  // line to the next
+  constexpr int RUN = LINES < 8 ? 8 / LINES : 1;
+  const int slot = blockIdx.x >> 3, q = (blockIdx.x & 7) * ((gridDim.x >> 3) / RUN) + slot / RUN;
+  const int first = q * tiles * RUN + slot % RUN;
+  // (the thread's place is formed anew for each tile: kept, it would cost registers)
+  auto at = [&](int g) {
+    unsigned tid = threadIdx.x;
+    asm("" : "+v"(tid));
+    return pa.field + size_t(tid / LINES) * N + unsigned(g) * LINES + tid % LINES;
+  };
+  auto load = [&](c64d (&v)[E], int g) {
+    const double2 *col = at(g);
+#pragma unroll
+    for (int m = 0; m < E; ++m) v[m] = ldz(col + size_t(T * m) * N);
+  };
+  c64d v[E], nxt[E];
+  load(v, first);
+  for (int i = threadIdx.x; i < PL::twiddles; i += PL::T * LINES) tab[i] = tw[i];
+  __syncthreads();
+  double *my = lds + c * LINE;
+  for (int i = 0; i < tiles; ++i) {
+    const int g = first + i * RUN;
+    if (i + 1 < tiles) load(nxt, g + RUN);
+    PL::forward(v, my, t, tab);
+#pragma unroll
+    for (int m = 0; m < E; ++m) {
+      if (m % 4 == 0) __builtin_amdgcn_sched_barrier(0);
+      const c64d h = ldz(pa.h + t + T * m);
+      v[m] = pa.adjoint ? cmulc(v[m], h) : cmul(v[m], h);
+    }
+    PL::inverse(v, my, t, tab);
+    double2 *col = at(g);
+#pragma unroll
+    for (int m = 0; m < E; ++m) col[size_t(T * m) * N] = make_double2(v[m].x, v[m].y);
+#pragma unroll
+    for (int m = 0; m < E; ++m) v[m] = nxt[m];
+  }
+}
+
 template <class PL, int RL, int CL>
 hipError_t launch64(const Batch64 &b, int count, bool adjoint, const double2 *tw, hipStream_t s,
                     const LaunchHook &hook) {
@@ -153,7 +206,13 @@ hipError_t launch64(const Batch64 &b, int count, bool adjoint, const double2 *tw
   };
   auto cols = [&]() {
     hook(s, adjoint ? "col_sweep64_adj" : "col_sweep64", count, 0);
-    hipLaunchKernelGGL((col_sweep64<PL, CL>), dim3(N / CL, count), dim3(PL::T * CL), 0, s, b, tw);
+    if constexpr (N == 2048 || N == 4096) {
+      // as many blocks as run at once (1024 threads per compute unit at 128 registers)
+      constexpr int kAtOnce = 256 * 1024 / (PL::T * CL), B = N / CL < kAtOnce ? N / CL : kAtOnce;
+      hipLaunchKernelGGL((col_sweep64_pipe<PL, CL>), dim3(B, count), dim3(PL::T * CL), 0, s, b, tw, N / CL / B);
+    } else {
+      hipLaunchKernelGGL((col_sweep64<PL, CL>), dim3(N / CL, count), dim3(PL::T * CL), 0, s, b, tw);
+    }
     hipError_t e = hipGetLastError();
     hook(s, adjoint ? "col_sweep64_adj" : "col_sweep64", count, 1);
     return e;
@@ -163,16 +222,16 @@ hipError_t launch64(const Batch64 &b, int count, bool adjoint, const double2 *tw
   return adjoint ? rows() : cols();
 }
 
-// the float32 sweeps' edges and tiles, halved for 16-byte elements (8 elements per thread from
-// 1024 to 4096)
+// the float32 sweeps' edges (8 elements per thread from 1024 to 4096); tiles as small as theirs up to
+// 1024, so that a plane fills the chip (a 256^2 plane ran 32 row blocks and 16 column blocks)
 template <class F>
 auto with_plan64(int n, F &&f) {
   switch (n) {
-    case 64: return f(Plan<64, 8, 8, 8>{}, std::integral_constant<int, 8>{}, std::integral_constant<int, 16>{});
-    case 128: return f(Plan<128, 16, 16, 8>{}, std::integral_constant<int, 8>{}, std::integral_constant<int, 16>{});
-    case 256: return f(Plan<256, 16, 16, 16>{}, std::integral_constant<int, 8>{}, std::integral_constant<int, 16>{});
-    case 512: return f(Plan<512, 8, 8, 8, 8>{}, std::integral_constant<int, 2>{}, std::integral_constant<int, 8>{});
-    case 1024: return f(Plan<1024, 8, 8, 8, 8, 2>{}, std::integral_constant<int, 2>{}, std::integral_constant<int, 4>{});
+    case 64: return f(Plan<64, 8, 8, 8>{}, std::integral_constant<int, 8>{}, std::integral_constant<int, 8>{});
+    case 128: return f(Plan<128, 16, 16, 8>{}, std::integral_constant<int, 8>{}, std::integral_constant<int, 8>{});
+    case 256: return f(Plan<256, 16, 16, 16>{}, std::integral_constant<int, 4>{}, std::integral_constant<int, 4>{});
+    case 512: return f(Plan<512, 8, 8, 8, 8>{}, std::integral_constant<int, 1>{}, std::integral_constant<int, 4>{});
+    case 1024: return f(Plan<1024, 8, 8, 8, 8, 2>{}, std::integral_constant<int, 1>{}, std::integral_constant<int, 2>{});
     case 2048: return f(Plan<2048, 8, 8, 8, 8, 4>{}, std::integral_constant<int, 1>{}, std::integral_constant<int, 2>{});
     case 4096: return f(Plan<4096, 8, 8, 8, 8, 8>{}, std::integral_constant<int, 1>{}, std::integral_constant<int, 2>{});
     default: return f(Plan<8192, 16, 16, 16, 16, 2>{}, std::integral_constant<int, 1>{}, std::integral_constant<int, 1>{});
