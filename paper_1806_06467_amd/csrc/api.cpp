@@ -310,10 +310,13 @@ int Ctx::lens(int n, double dx, double lam, double f, hipStream_t s, const float
 // factor squaring to 1 over the two axes) and the two roots make the constant dx^2/(i lambda z).
 // With `inverse` the output phases of the two axes carry dx2 / dx each: the factor (dx2 / dx)^2
 // that turns the adjoint into the inverse step.
+// A thin lens before the inverse step (focal length f_in, on the far plane) is folded into the output
+// phases, which the inverse step applies conjugated: post times conj(exp(-i pi r^2 / (lambda f_in))).
 int Ctx::direct_phases(int n, double dx, double lam, double z, double f, hipStream_t s, const float2 **pre,
-                       const float2 **post, bool inverse) {
+                       const float2 **post, bool inverse, double f_in) {
   const TableKey kpre{kDirectPre, n, bits(dx), bits(lam), bits(z), bits(f)};
-  const TableKey kpost{kDirectPost, n, bits(dx), bits(lam), bits(z), inverse ? 1u : 0u};
+  // (a focal length never has the bits of 0 or 1 that mark the step itself)
+  const TableKey kpost{kDirectPost, n, bits(dx), bits(lam), bits(z), f_in != 0.0 ? bits(f_in) : inverse ? 1u : 0u};
   auto build = [&](const TableKey &key, bool input, const float2 **out) -> int {
     if (auto it = tables.find(key); it != tables.end()) {
       *out = static_cast<const float2 *>(it->second);
@@ -322,7 +325,7 @@ int Ctx::direct_phases(int n, double dx, double lam, double z, double f, hipStre
     std::vector<float2> h(n);
     const double dx2 = lam * std::fabs(z) / (double(n) * dx);
     const double coef = input ? dx * dx * (1.0 / z - (f != 0.0 ? 1.0 / f : 0.0)) / (2.0 * lam)
-                              : dx2 * dx2 / (2.0 * lam * z);
+                              : dx2 * dx2 * (1.0 / z + (f_in != 0.0 ? 1.0 / f_in : 0.0)) / (2.0 * lam);
     // (the inverse's (dx2 / dx)^2 is split over the two axes' tables)
     const double scale = input ? 1.0 : dx / std::sqrt(lam * std::fabs(z)) * (inverse ? dx2 / dx : 1.0);
     // the root of dx^2 / (i lambda z) is (dx / sqrt(lambda |z|)) exp(-i pi sign(z) / 4)
@@ -787,9 +790,9 @@ int fr_plan_route(double w0_m, double z_waist_m, double wavelength_m, int32_t n,
   return k;
 }
 
-int fresnel_direct(fr_ctx *ctx_, fr_c64 *field, int32_t n, double dx_m, double wavelength_m, double z_m,
-                   const float *amp, const float *opd_m, double lens_focal_m, int32_t flags, double *dx_out_m,
-                   void *stream) {
+static int direct_call(fr_ctx *ctx_, fr_c64 *field, int32_t n, double dx_m, double wavelength_m, double z_m,
+                       const float *amp, const float *opd_m, double lens_focal_m, double lens_in_m, int32_t flags,
+                       double *dx_out_m, void *stream) {
   if (!field || !dx_out_m || n <= 0 || (flags & ~(FR_ADJOINT | FR_INVERSE)) || flags == (FR_ADJOINT | FR_INVERSE))
     return FR_EINVAL;
   const bool inverse = flags & FR_INVERSE;
@@ -813,7 +816,7 @@ int fresnel_direct(fr_ctx *ctx_, fr_c64 *field, int32_t n, double dx_m, double w
   a.win = n;
   a.inv_lambda = float(1.0 / wavelength_m);
   a.flags = (inverse ? FR_ADJOINT : flags) | (z_m < 0 ? fr::kTowardSource : 0);
-  int st = ctx->direct_phases(n, dx_m, wavelength_m, z_m, lens_focal_m, s, &a.lens, &a.h, inverse);
+  int st = ctx->direct_phases(n, dx_m, wavelength_m, z_m, lens_focal_m, s, &a.lens, &a.h, inverse, lens_in_m);
   if (st != FR_OK) return st;
   const float2 *root;
   st = ctx->twiddles(n, s, &root);
@@ -824,7 +827,21 @@ int fresnel_direct(fr_ctx *ctx_, fr_c64 *field, int32_t n, double dx_m, double w
   return std::fabs(z_m) < double(n) * dx_m * dx_m / wavelength_m ? FR_W_DIRECT_UNDERSAMPLED : FR_OK;
 }
 
+int fresnel_direct(fr_ctx *ctx_, fr_c64 *field, int32_t n, double dx_m, double wavelength_m, double z_m,
+                   const float *amp, const float *opd_m, double lens_focal_m, int32_t flags, double *dx_out_m,
+                   void *stream) {
+  return direct_call(ctx_, field, n, dx_m, wavelength_m, z_m, amp, opd_m, lens_focal_m, 0.0, flags, dx_out_m, stream);
+}
+
 }  // extern "C"
+
+namespace fr {
+int direct_inverse_with_lens(fr_ctx *ctx, fr_c64 *field, int32_t n, double dx_m, double wavelength_m, double z_m,
+                             double lens_in_m, double *dx_out_m, void *stream) {
+  return direct_call(ctx, field, n, dx_m, wavelength_m, z_m, nullptr, nullptr, 0.0, lens_in_m, FR_INVERSE, dx_out_m,
+                     stream);
+}
+}  // namespace fr
 
 // ============================================================================================
 // MFT entry points

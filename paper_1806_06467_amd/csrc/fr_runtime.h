@@ -98,7 +98,7 @@ struct Ctx {
   int transfer(int n, double dx, double lam, double z, hipStream_t s, const float2 **out);
   int lens(int n, double dx, double lam, double f, hipStream_t s, const float2 **out);
   int direct_phases(int n, double dx, double lam, double z, double f, hipStream_t s, const float2 **pre,
-                    const float2 **post, bool inverse = false);
+                    const float2 **post, bool inverse = false, double f_in = 0.0);
   int mft_table(int p, int q, double n_d, double du, hipStream_t s, const void **out);
   int dm_influence(int n, int n_d, int n_act, hipStream_t s, const float **out);
   // the rows [lo, hi) of that table with a nonzero entry (the Gaussians underflow float32 to

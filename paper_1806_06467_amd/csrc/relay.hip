@@ -11,8 +11,10 @@
 // and the number of 2-D transforms (two per angular-spectrum step, one per direct step).
 //
 // The optic of a plane rides in the prologue of the plane's first step when that step is an
-// angular-spectrum or direct step; before an inverse direct step, and at the last plane, an
-// elementwise kernel applies it (the same float32 arithmetic as the sweeps' prologue).
+// angular-spectrum or direct step. Before an inverse direct step a lens alone is folded into that
+// step's phase table (built in float64); a mask or an OPD there, and the last plane's optic, take an
+// elementwise kernel (the same float32 arithmetic as the sweeps' prologue; 15 us on a 2048^2 plane,
+// of which the relay of nine optics had four and keeps one).
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -26,6 +28,9 @@
 #include "fr_runtime.h"
 
 namespace fr {
+// the inverse direct step after a thin lens of focal length lens_in_m (0 for none) on its far plane
+int direct_inverse_with_lens(fr_ctx *ctx, fr_c64 *field, int32_t n, double dx_m, double wavelength_m, double z_m,
+                             double lens_in_m, double *dx_out_m, void *stream);
 namespace {
 
 // field[y][x] *= amp exp(2 pi i opd / lambda) lens[x] lens[y] (amp, opd, lens each optional)
@@ -161,7 +166,11 @@ int propagate_system(fr_ctx *ctx_, fr_c64 *field, int32_t n, double dx_m, double
     const fr_optic &o = optics[i];
     const auto &steps = P.steps[i];
     bool fused = false;
-    if (steps.empty() || steps[0].kind == FR_ROUTE_DIRECT_INVERSE) {
+    const bool inverse_first = !steps.empty() && steps[0].kind == FR_ROUTE_DIRECT_INVERSE;
+    const double lens_in = inverse_first && !o.amp && !o.opd_m ? o.lens_focal_m : 0.0;
+    if (lens_in != 0.0) {
+      fused = true;
+    } else if (steps.empty() || inverse_first) {
       if ((st = apply_optic(i)) != FR_OK) return st;
       fused = true;
     }
@@ -177,8 +186,8 @@ int propagate_system(fr_ctx *ctx_, fr_c64 *field, int32_t n, double dx_m, double
       } else if (r.kind == FR_ROUTE_DIRECT) {
         st = fresnel_direct(ctx_, field, n, r.dx_in_m, wavelength_m, r.z_m, amp, opd, f, 0, &dx_out, stream);
       } else {
-        st = fresnel_direct(ctx_, field, n, r.dx_out_m, wavelength_m, r.z_m, nullptr, nullptr, 0.0, FR_INVERSE,
-                            &dx_out, stream);
+        st = fr::direct_inverse_with_lens(ctx_, field, n, r.dx_out_m, wavelength_m, r.z_m, j == 0 ? lens_in : 0.0,
+                                          &dx_out, stream);
       }
       if (st < 0) return st;
       warn |= st;
