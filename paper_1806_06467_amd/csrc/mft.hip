@@ -314,7 +314,8 @@ fold_kernel(FoldParams gp) {
   typename Loader::Regs r0, r1;
   bf16x8 tb[2][2][3];
   const int step0 = jbeg / 16 + 2 * ks;  // the steps are padded to whole stages
-  const int nfull = ld.fits ? (jend - jbeg) / kFoldStage : 0;
+  // (a slice past the last pair, where whole stages leave too few for every slice, has no stage)
+  const int nfull = ld.fits ? max(jend - jbeg, 0) / kFoldStage : 0;
   int pending = 0;
   if (nfull > 0) {
     ld.load(r0, jbeg);

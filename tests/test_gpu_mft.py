@@ -169,3 +169,14 @@ def test_folded_products_at_tile_edges(n, m):
     assert rel_l2(got, oracle.mft(f32(e), n_d, m, du)) <= 1.5e-6
     got = to_np(fb.mft_adjoint(to_gpu(eb), n_d, n, du))
     assert rel_l2(got, oracle.mft_adjoint(f32(eb), n_d, n, du)) <= 1.5e-6
+
+
+# eight slices of 192 pairs, whole 64-pair stages, leave the last two (2200: 1100 pairs) or the last
+# one (2600: 1300 pairs) without a pair
+@pytest.mark.parametrize("n", [2200, 2600])
+def test_slices_without_pairs(n):
+    banner(f"folded mft {n} -> 96, empty slices")
+    n_d, m, du = 0.4 * n, 96, 0.37
+    e = synth.random_field(n, n)
+    got = to_np(fb.mft_forward(to_gpu(e), n_d, m, du))
+    assert rel_l2(got, oracle.mft(f32(e), n_d, m, du)) <= 1.5e-6
