@@ -176,8 +176,8 @@ def main():
     stream = torch.cuda.current_stream(dev)
     t_wall0 = time.perf_counter()
 
-    # autotune (untimed): sweep tiles for the plane edges, GEMM tiles (and split-K factors) for
-    # the train's MFT shapes; or the choices of an earlier run
+    # autotune (untimed): sweep tiles for the plane edges, split factors of the MFT
+    # products for the train's shapes; or the choices of an earlier run
     t_tune = time.perf_counter()
     if args.tune_file:
         fb.autotune_load(args.tune_file)
@@ -548,7 +548,7 @@ def train_step(args, fb, synth, np, torch, dev, timed, profiled, lams):
     after the 1 m step), occulter MFT to 256^2 (3 lambda/D spot), Babinet MFT back, Lyot stop
     0.9 D, detector MFT to 512^2, 21 wavelengths; broadband PSF plus the gradient of the mean
     dark-hole contrast with respect to both DMs. Batched + graph and plain forms, the per-kernel
-    breakdown, and the GEMM tiles priced against the peak of the precision they execute in."""
+    breakdown, and the MFT products priced against the peak of the precision they execute in."""
 
     def f(a):
         return torch.from_numpy(np.ascontiguousarray(a, dtype=np.float32)).to(dev)
@@ -626,7 +626,7 @@ def train_8192(fb, synth, np, torch, dev, timed, profiled, tune=True):
     dark-hole contrast with respect to the 8192 actuators, batched + graph, plain, and in two
     calls through the caller's checkpoint (forward save, then backward)."""
     nd, n, nl, na = 2048, 8192, 8, 64
-    # tuned (untimed) for its own shapes: the 8192 sweeps and the MFT GEMMs of its planes (unless
+    # tuned (untimed) for its own shapes: the 8192 sweeps and the MFT products of its planes (unless
     # the choices were loaded from a file)
     t0 = time.perf_counter()
     if tune:

@@ -47,12 +47,9 @@ struct PassOut {
 // entries (the table is built in float64 on the host; each entry is within half an ulp).
 template <int P, int R, int NB, int T, class C = c32, class TW = float2>
 struct PassTw {
-  // with several butterflies per thread and long lines (32 elements per thread) the twiddles
-  // are read per butterfly inside the pass instead (register budget)
-  static constexpr bool lazy = NB > 1 && NB * R >= 32;
-  C w[lazy ? 1 : NB][R > 1 ? R - 1 : 1];
+  C w[NB][R > 1 ? R - 1 : 1];
   __device__ __forceinline__ void load(const TW* __restrict__ tw, int t) {
-    if constexpr (P > 1 && !lazy) {
+    if constexpr (P > 1) {
 #pragma unroll
       for (int j = 0; j < NB; ++j) {
         const int k = (t + j * T) % P;
@@ -88,8 +85,6 @@ __device__ __forceinline__ void fft_passes(C (&v)[E], L* __restrict__ lds, int t
   static_assert(E % R == 0, "radix must divide the elements per thread");
   static_assert(N % (P * R) == 0, "plan does not factor N");
   constexpr bool last = sizeof...(Rest) == 0;
-  // SPLIT reads each twiddle where it is used: its tables lie in LDS
-  constexpr bool lazy = SPLIT || PassTw<P, R, NB, T>::lazy;
   // write outputs of butterfly b: value(r) to the position of output r
   auto put = [&](int b, auto value) {
     if constexpr (PassOut<P, R>::exact) {
@@ -109,7 +104,7 @@ __device__ __forceinline__ void fft_passes(C (&v)[E], L* __restrict__ lds, int t
     for (int r = 0; r < R; ++r) u[r] = v[j + r * NB];
     const int b = t + j * T;
     if constexpr (P > 1) {
-      if constexpr (lazy) {
+      if constexpr (SPLIT) {  // each twiddle read where it is used: the table lies in LDS
         const int k = b % P;
 #pragma unroll
         for (int r = 1; r < R; ++r) {

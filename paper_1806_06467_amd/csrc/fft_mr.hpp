@@ -1,5 +1,6 @@
 // Runtime-planned Stockham FFT of one line held in LDS, for line lengths that factor into
-// radices up to 16 (2-10, 12, 14, 15, 16).
+// radices up to 16 (2-10, 12, 14, 15, 16); and, below, register-resident plans (MrReg) of chosen
+// edges, whose radices go up to 28.
 //
 // Pass with radix R after span P (P = product of earlier radices), over L = n / R butterflies
 // dealt round-robin to the T threads of the line: butterfly b reads elements b + r L, twiddles

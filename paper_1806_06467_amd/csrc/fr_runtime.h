@@ -123,7 +123,7 @@ struct MftOut {
 // and reduced to fit `partial_elems` float64 complex partial sums
 hipError_t run_fold(Ctx *ctx, const FoldArgs &g, void *partial, size_t partial_elems, hipStream_t s, int split = 0);
 // partial_cap: float64 complex split-K partial sums that fit ws after the n_in x m_out product
-// (the split factor is reduced to fit; 0 runs every GEMM unsplit)
+// (the split factor is reduced to fit; 0 runs every product unsplit)
 int mft_forward_impl(Ctx *ctx, const float2 *in, int n_in, int ld_in, int m_out, double n_d,
                      double du, const MftOut &o, void *ws, hipStream_t s, size_t partial_cap = SIZE_MAX);
 size_t mft_t_bytes(int n, int m);  // the product T of an MFT pair, 256-byte aligned

@@ -1,5 +1,5 @@
 // The allocation-free entry point: mft_forward with its working memory (the n_in x m_out
-// product T of the first GEMM and the split-K partial sums) in a file-scope device array instead
+// product T of the first pass and the split-K partial sums) in a file-scope device array instead
 // of a caller workspace, for callers that cannot allocate device memory. Its kernels are those of
 // mft_forward (Sec. 1.1: the matrix Fourier transform after Soummer et al.).
 //
@@ -8,7 +8,7 @@
 // fetched once, with that device current, by hipGetSymbolAddress (noalloc_setup, called from
 // fr_create) and kept per device; only that address is used. Every call on one device shares the
 // array: calls that overlap on one device (two streams, two threads) race, so they must be
-// ordered by the caller. Nothing in it needs clearing between calls: the first GEMM writes all of
+// ordered by the caller. Nothing in it needs clearing between calls: the first pass writes all of
 // T and every split slice writes all of its partial sums before they are read.
 #include <hip/hip_runtime.h>
 

@@ -10,7 +10,9 @@
 //               OPD and mirror phasors of Eq. 3, thin-lens chirp), FFT, * h (scaled 1/n),
 //               inverse FFT, store.
 //   col_sweep : load a tile of adjacent columns, FFT, * h, inverse FFT, epilogue (the mirror
-//               after the step, or the conjugate optic for the adjoint), store.
+//               after the step, or the conjugate optic for the adjoint), store. From 2048 rows
+//               (col_sweep_pipe) a block walks several tiles and loads the next one while it
+//               transforms the present one.
 // The column tile is LINES columns wide so that a wavefront reads LINES*8-byte contiguous
 // segments; blocks are renumbered so that the blocks resident on one XCD (one L2) work on
 // neighbouring columns at the same time.

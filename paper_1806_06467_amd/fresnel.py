@@ -538,7 +538,7 @@ def autotune_fresnel(n, device=None, stream=None):
 
 
 def autotune_mft(n, m, device=None, stream=None):
-    """Time the GEMM tile configurations of the n <-> m MFTs and keep the fastest."""
+    """Time the split factors of the n <-> m MFTs' products and keep the fastest."""
     dev = torch.cuda.current_device() if device is None else device
     _check(lib().fr_autotune(context(dev).handle, FR_TUNE_MFT, int(n), int(m), _stream_handle(dev, stream)),
            "fr_autotune")
