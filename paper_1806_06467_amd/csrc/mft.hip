@@ -553,7 +553,20 @@ __global__ void __launch_bounds__(256) split_reduce(FoldParams gp, int rows, int
     for (int j = blockIdx.x * 256 + threadIdx.x; j < cols; j += gridDim.x * 256) {
       const size_t e = size_t(i) * cols + j;
       double sr = 0.0, si = 0.0;
-      for (int s = 0; s < gp.split; ++s) {
+      // four slices' loads at a time: one by one they are a chain of waits where the output is small
+      // (sixteen slices of 256 x 256: 8.6 us, 6.6 us)
+      int s = 0;
+      for (; s + 4 <= gp.split; s += 4) {
+        double2 v[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[q] = gp.partial[size_t(s + q) * total + e];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          sr += v[q].x;
+          si += v[q].y;
+        }
+      }
+      for (; s < gp.split; ++s) {
         const double2 v = gp.partial[size_t(s) * total + e];
         sr += v.x;
         si += v.y;
