@@ -74,6 +74,34 @@ __device__ __forceinline__ void epilogue(const FoldArgs &a, int i, int j, double
   }
 }
 
+// the same in two steps, what result (i, j) reads and the result: a block that forms several issues
+// all their loads ahead of the first store
+struct EpilogueIn {
+  float2 old;
+  float mask;
+  double intensity;
+  __device__ __forceinline__ void load(const FoldArgs &a, int i, int j) {
+    if (a.beta != 0.f) old = a.Cin ? a.Cin[size_t(i) * a.ldcin + j] : a.C[size_t(i) * a.ldc + j];
+    if (a.mask) mask = a.mask[size_t(i) * a.ldm + j];
+    if (a.intensity) intensity = a.intensity[size_t(i) * a.ldi + j];
+  }
+  __device__ __forceinline__ void store(const FoldArgs &a, int i, int j, double cr, double ci) const {
+    double orr = a.alpha * cr;
+    double oi = a.alpha * ci;
+    if (a.beta != 0.f) {
+      orr += double(a.beta) * double(old.x);
+      oi += double(a.beta) * double(old.y);
+    }
+    if (a.mask) {
+      const double mk = mask;
+      orr *= mk;
+      oi *= mk;
+    }
+    if (!a.skip_c) a.C[size_t(i) * a.ldc + j] = make_float2(float(orr), float(oi));
+    if (a.intensity) a.intensity[size_t(i) * a.ldi + j] = intensity + a.weight * (orr * orr + oi * oi);
+  }
+};
+
 // Blocks are dealt round-robin to the 8 XCDs (each with its own L2). Renumber them so that each
 // XCD runs a contiguous range of tiles; inside a slice the range is walked in groups of
 // kGroupRows tile rows, column by column, so that the blocks resident on an XCD at one time share
@@ -258,6 +286,7 @@ fold_kernel(FoldParams gp) {
   using Loader = FoldLoader<COLS>;
   const FoldArgs &a = gp.a;
   __shared__ __attribute__((aligned(16))) unsigned char lds[8 * 16 * 64 * 16 + 16 * kFoldFree * 16];
+  __shared__ float2 in0[kFoldFree];  // the unpaired element of each free index (slice 0 adds it)
   uint4 *pieces = reinterpret_cast<uint4 *>(lds);  // [2][kFoldPieces][kPieceUnits]
   constexpr int kBuf = kFoldPieces * kPieceUnits;
   static_assert(2 * kBuf * 16 <= 8 * 16 * 64 * 16, "stage buffers fit the exchange area");
@@ -381,25 +410,52 @@ fold_kernel(FoldParams gp) {
   // signs of its share of the tile's outputs
   double2 *ex = reinterpret_cast<double2 *>(lds);
   double2 *zs = ex + 8 * 16 * 64;  // [16 groups of pairs][free index]
+  float2 unpaired = make_float2(0.f, 0.f);
+  if (bz == 0 && tid < kFoldFree) {
+    // (the address is formed here: kept across the products it costs registers they need)
+    unsigned f = tid;
+    asm("" : "+v"(f));
+    f = min(f0 + int(f), a.F - 1);
+    unpaired = COLS ? a.data[size_t(half) * a.ldd + f] : a.data[size_t(f) * a.ldd + half];
+  }
   __syncthreads();
 #pragma unroll
   for (int r = 0; r < 16; ++r) ex[(wave * 16 + r) * 64 + lane] = make_double2(totr[r], toti[r]);
   zs[ld.jq * kFoldFree + ld.lf] = make_double2(ld.zero_re, ld.zero_im);
+  if (tid < kFoldFree) in0[tid] = unpaired;
   __syncthreads();
   const int rows = COLS ? a.P : a.F, cols = COLS ? a.F : a.P;
-  auto emit = [&](int o, int ff, double re, double im) {
+  // A column product, the second of a transform, may add a background and apply a mask: its eight
+  // results' loads go out ahead of the stores (one after the other, each behind the last one's wait,
+  // they were up to 2 us of the 1024-edge products: the 21-wavelength train 12.58 ms, 12.40 ms). A row product
+  // only stores, and there the two steps cost 1 us.
+  auto load_in = [&](EpilogueIn &in, int o, int ff) {
+    if (COLS && gp.split == 1) in.load(a, o, ff);
+  };
+  auto emit = [&](int o, int ff, double re, double im, const EpilogueIn &in) {
     const int i = COLS ? o : ff, j = COLS ? ff : o;
     if (gp.split > 1) gp.partial[(size_t(bz) * rows + i) * cols + j] = make_double2(re, im);
+    else if (COLS) in.store(a, i, j, re, im);
     else epilogue(a, i, j, re, im);
-  };
-  auto in0 = [&](int ff) {
-    if (bz != 0) return make_double2(0.0, 0.0);
-    const float2 v = COLS ? a.data[size_t(half) * a.ldd + ff] : a.data[size_t(ff) * a.ldd + half];
-    return make_double2(double(v.x), double(v.y));
   };
   constexpr int SHARE = 16 / (2 * KS);
   const int share = (par * KS + ks) * SHARE;
   const double sg = a.sign;
+  // item r of lane l sits at row (r/4)*8 + (l/32)*4 + r%4, column l%32 of a 32 x 32 tile
+  auto item = [&](int rr, int &lf, int &k) {
+    const int r = share + rr, trow = (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3), tcol = lane & 31;
+    lf = COLS ? tcol : trow;
+    k = ktile * 32 + (COLS ? trow : tcol) + 1;
+    return f0 + lf < a.F && k <= out_half;
+  };
+  EpilogueIn plus[SHARE], minus[SHARE];
+#pragma unroll
+  for (int rr = 0; rr < SHARE; ++rr) {
+    int lf, k;
+    if (!item(rr, lf, k)) continue;
+    if (k < a.P - out_half) load_in(plus[rr], out_half + k, f0 + lf);
+    load_in(minus[rr], out_half - k, f0 + lf);
+  }
 #pragma unroll
   for (int rr = 0; rr < SHARE; ++rr) {
     const int r = share + rr;
@@ -413,26 +469,25 @@ fold_kernel(FoldParams gp) {
       s.x += sv.x;
       s.y += sv.y;
     }
-    // item r of lane l sits at row (r/4)*8 + (l/32)*4 + r%4, column l%32 of a 32 x 32 tile
-    const int trow = (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3), tcol = lane & 31;
-    const int ff = f0 + (COLS ? tcol : trow);
-    const int k = ktile * 32 + (COLS ? trow : tcol) + 1;
-    if (ff >= a.F || k > out_half) continue;
-    const double2 z = in0(ff);
-    c.x += z.x;
-    c.y += z.y;
-    if (k < a.P - out_half) emit(out_half + k, ff, c.x - sg * s.y, c.y + sg * s.x);
-    emit(out_half - k, ff, c.x + sg * s.y, c.y - sg * s.x);
+    int lf, k;
+    if (!item(rr, lf, k)) continue;
+    const float2 z = in0[lf];
+    c.x += double(z.x);
+    c.y += double(z.y);
+    if (k < a.P - out_half) emit(out_half + k, f0 + lf, c.x - sg * s.y, c.y + sg * s.x, plus[rr]);
+    emit(out_half - k, f0 + lf, c.x + sg * s.y, c.y - sg * s.x, minus[rr]);
   }
   if (bx == 0 && tid < kFoldFree && f0 + tid < a.F) {
-    double2 z = in0(f0 + tid);
+    EpilogueIn in;
+    load_in(in, out_half, f0 + tid);
+    double2 z = make_double2(in0[tid].x, in0[tid].y);
 #pragma unroll
     for (int q = 0; q < 16; ++q) {
       const double2 v = zs[q * kFoldFree + tid];
       z.x += v.x;
       z.y += v.y;
     }
-    emit(out_half, f0 + tid, z.x, z.y);
+    emit(out_half, f0 + tid, z.x, z.y, in);
   }
 }
 
