@@ -32,6 +32,7 @@
 // and the loads ordered as below; the result's distance from 64 bits 1.5e-7 before, 8e-8 now.
 #include <hip/hip_runtime.h>
 
+#include <cmath>
 #include <cstdio>
 
 #include "fr_internal.h"
@@ -660,14 +661,28 @@ bool short_pairs(const FoldArgs &a) {
 
 }  // namespace
 
-// slices of the pairs so that the grid gives every compute unit a block, each slice at least 128
-// pairs deep
+// slices of the pairs: the power of two with the least time by what the kernels measured over
+// edges of 256 to 4096 and 64 to 512 (one block per compute unit at a time): 1.6 us a stage of a
+// round of blocks, and for a split 4 us for the pass that adds the slices and the slices' bytes
+// written and read at 3 TB/s. A slice for every idle compute unit, at least 128 pairs deep, was
+// too many for the middle sizes (us at 1, 2, 4 slices, input length 1024: 1024 x 512 outputs 22,
+// 26, 33; 1024 x 256 21, 25, 25; length 512: 512 x 1024 17, 26, 29); over 100 products of those
+// edges this choice is at most 2 % behind that one and 5 % ahead of it in sum.
 int fold_split_for(const FoldArgs &a) {
   if (short_pairs(a)) return 1;
-  const int blocks = div_up(fold_tiles(a.P), 2) * div_up(a.F, kFoldFree);
-  int s = 1;
-  while (blocks * s < 256 && a.Q / 2 / (s * 2) >= 128 && s < kMaxSplit) s *= 2;
-  return s;
+  const double blocks = double(div_up(fold_tiles(a.P), 2)) * div_up(a.F, kFoldFree);
+  const int stages = div_up(a.Q / 2, kFoldStage);
+  int best = 1;
+  double least = 0.0;
+  for (int s = 1; s <= kMaxSplit && (s == 1 || s <= stages); s *= 2) {
+    double us = 1.6 * div_up(stages, s) * std::ceil(blocks * s / 256.0);
+    if (s > 1) us += 4.0 + double(s) * a.F * a.P * 16.0 / 3.0e6;
+    if (s == 1 || us < least) {
+      least = us;
+      best = s;
+    }
+  }
+  return best;
 }
 
 hipError_t launch_fold(const FoldArgs &a, int split, void *partial, hipStream_t stream, const LaunchHook &hook) {

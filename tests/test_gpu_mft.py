@@ -171,8 +171,8 @@ def test_folded_products_at_tile_edges(n, m):
     assert rel_l2(got, oracle.mft_adjoint(f32(eb), n_d, n, du)) <= 1.5e-6
 
 
-# eight slices of 192 pairs, whole 64-pair stages, leave the last two (2200: 1100 pairs) or the last
-# one (2600: 1300 pairs) without a pair
+# whole 64-pair stages leave the last slices of a split without a pair (sixteen slices of 128 pairs
+# over 1100 or 1300 pairs)
 @pytest.mark.parametrize("n", [2200, 2600])
 def test_slices_without_pairs(n):
     banner(f"folded mft {n} -> 96, empty slices")
