@@ -375,7 +375,8 @@ int Ctx::mft_table(int p, int q, double n_d, double du, hipStream_t s, const voi
       const int tile = (k - 1) / 32, step = (j - 1) / 16, lane = (k - 1) % 32 + 32 * ((j - 1) % 16 / 8);
       for (int par = 0; par < 2; ++par) {
         uint16_t b[3];
-        bf16_pieces(par ? std::sin(t) : std::cos(t), b);
+        const double w = par ? std::sin(t) : std::cos(t);
+        bf16_pieces(fold_negated(step) ? -w : w, b);
         const size_t at = ((size_t(par) * tiles + tile) * steps + step) * 3;
         for (int piece = 0; piece < 3; ++piece) h[((at + piece) * 64 + lane) * 8 + (j - 1) % 8] = b[piece];
       }

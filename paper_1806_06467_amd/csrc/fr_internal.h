@@ -145,6 +145,9 @@ struct FoldArgs {
 // steps are padded to whole stages of four.
 __host__ __device__ inline int fold_tiles(int P) { return (P / 2 + 31) / 32 > 0 ? (P / 2 + 31) / 32 : 1; }
 __host__ __device__ inline int fold_steps(int Q) { return (Q / 2 + 63) / 64 > 0 ? (Q / 2 + 63) / 64 * 4 : 4; }
+// every second pair of steps holds the entries with the opposite sign: the pairs that one of the two
+// halves of the general kernel's waves sums, so that the rounding bias of the halves cancels
+__host__ __device__ inline bool fold_negated(int step) { return step & 2; }
 inline size_t fold_table_bytes(int P, int Q) { return size_t(2) * fold_tiles(P) * fold_steps(Q) * 3 * 64 * 8 * 2; }
 // split > 1 slices the pairs; the slices' partial sums go to `partial` (split x output complex
 // float64, 16-byte aligned) and are added in a fixed order by a second kernel.

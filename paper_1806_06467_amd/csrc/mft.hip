@@ -225,6 +225,13 @@ struct FoldLoader {
       r.m[q] = j + q <= half ? centre[-(j + q) * step] : make_float2(0.f, 0.f);
     }
   }
+  __device__ __forceinline__ void scale(Regs &r, float w) const {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      r.p[q] = make_float2(w * r.p[q].x, w * r.p[q].y);
+      r.m[q] = make_float2(w * r.m[q].x, w * r.m[q].y);
+    }
+  }
   __device__ __forceinline__ void put_part(uint4 *dst, float v0, float v1, float v2, float v3) const {
     unsigned h[2], m[2], l[2];
     bf_split2(v0, v1, h[0], m[0], l[0]);
@@ -465,10 +472,11 @@ fold_kernel(FoldParams gp) {
     for (int h = 0; h < KS; ++h) {
       const double2 cv = ex[(((h * KT + kt) * 2) * 16 + r) * 64 + lane];
       const double2 sv = ex[(((h * KT + kt) * 2 + 1) * 16 + r) * 64 + lane];
-      c.x += cv.x;
-      c.y += cv.y;
-      s.x += sv.x;
-      s.y += sv.y;
+      const double w = fold_negated(2 * h) ? -1.0 : 1.0;  // (the sign of the half's matrix entries)
+      c.x += w * cv.x;
+      c.y += w * cv.y;
+      s.x += w * sv.x;
+      s.y += w * sv.y;
     }
     int lf, k;
     if (!item(rr, lf, k)) continue;
@@ -490,6 +498,14 @@ fold_kernel(FoldParams gp) {
     }
     emit(out_half, f0 + tid, z.x, z.y, in);
   }
+}
+
+// the sign with which a free index's data go through the short kernel (see the head of this file),
+// mixed so that it has no frequency of its own
+__device__ __forceinline__ float short_sign(int f) {
+  unsigned h = unsigned(f) * 0x9e3779b1u;
+  h = (h ^ (h >> 15)) * 0x2c1b3c6du;
+  return h >> 31 ? -1.f : 1.f;
 }
 
 // The same for at most kShortPairs pairs, where the general kernel's blocks spend their time
@@ -523,12 +539,16 @@ fold_short_kernel(FoldArgs a, int tiles_per_block) {
       ld.load_any(r0, 0);
       ld.load_any(r1, kFoldStage);
     }
+    // the sign of the free index, and of the matrix entries of the thread's step
+    const float sgn = short_sign(f0 + ld.lf) * (fold_negated(ld.jq >> 2) ? -1.f : 1.f);
+    ld.scale(r0, sgn);
+    ld.scale(r1, sgn);
     ld.put_re(r0, pieces, true);
     ld.put_im(r0, pieces, true);
     ld.put_re(r1, pieces + kBuf, true);
     ld.put_im(r1, pieces + kBuf, true);
     if (ld.jq == 0) in0[ld.lf] = *ld.centre;
-    zs[ld.jq * kFoldFree + ld.lf] = make_double2(ld.zero_re, ld.zero_im);
+    zs[ld.jq * kFoldFree + ld.lf] = make_double2(double(sgn) * ld.zero_re, double(sgn) * ld.zero_im);
   }
   __syncthreads();
   const double sg = a.sign;
@@ -579,10 +599,11 @@ fold_short_kernel(FoldArgs a, int tiles_per_block) {
       const int k = tile * 32 + (COLS ? trow : tcol) + 1;
       if (ff >= a.F || k > out_half) continue;
       const float2 z = in0[lf];
-      const double cx = double(s[0][0][r]) + double(s[0][1][r]) + double(z.x);
-      const double cy = double(s[0][2][r]) + double(s[0][3][r]) + double(z.y);
-      const double sx = double(s[1][0][r]) + double(s[1][1][r]);
-      const double sy = double(s[1][2][r]) + double(s[1][3][r]);
+      const double w = short_sign(ff);
+      const double cx = w * (double(s[0][0][r]) + double(s[0][1][r])) + double(z.x);
+      const double cy = w * (double(s[0][2][r]) + double(s[0][3][r])) + double(z.y);
+      const double sx = w * (double(s[1][0][r]) + double(s[1][1][r]));
+      const double sy = w * (double(s[1][2][r]) + double(s[1][3][r]));
       if (k < a.P - out_half) emit(out_half + k, ff, cx - sg * sy, cy + sg * sx);
       emit(out_half - k, ff, cx + sg * sy, cy - sg * sx);
       if ((r & 3) == 3) __builtin_amdgcn_sched_barrier(0);  // four items' addresses and loads at a time

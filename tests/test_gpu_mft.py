@@ -180,3 +180,16 @@ def test_slices_without_pairs(n):
     e = synth.random_field(n, n)
     got = to_np(fb.mft_forward(to_gpu(e), n_d, m, du))
     assert rel_l2(got, oracle.mft(f32(e), n_d, m, du)) <= 1.5e-6
+
+
+def test_rounding_errors_do_not_gather_on_the_axis():
+    # Rounding errors are independent from output to output, so the rms of one row's 64 errors is
+    # within 1 / sqrt(128) of any other row's, one standard deviation: a factor of 2 is eleven. The
+    # sum of a matrix product that rounds with a bias puts that bias of all 4095 rows on the axis.
+    n, m, n_d, du = 4095, 64, 0.4 * 4095, 0.11
+    banner("mft 4095 -> 64, errors on the axis")
+    rng = np.random.default_rng(7)
+    e = np.exp(2j * np.pi * rng.random((n, n))) * 10.0 ** (-12.0 * rng.random((n, n)))
+    d = to_np(fb.mft_forward(to_gpu(e), n_d, m, du)) - oracle.mft(f32(e), n_d, m, du)
+    rows, cols = (np.sqrt(np.mean(np.abs(d) ** 2, axis=a)) for a in (1, 0))
+    assert rows[m // 2] <= 2.0 * np.median(rows) and cols[m // 2] <= 2.0 * np.median(cols)
