@@ -22,9 +22,12 @@
 // down to 2^-16 (hi hi, hi mid, mid hi, mid mid, hi lo, lo hi); the three left out are below
 // 2^-23 together and, as round-to-nearest residuals, of either sign. The hi hi products and the
 // correction products go to separate float32 sums, so that the corrections are never rounded at
-// the scale of the running total; every kFoldDepth pairs the sums are added into float64 totals
+// the scale of the running total; every kFoldDepth pairs the hi hi sums are added into float64 totals
 // (the long Fourier sums of the coronagraph cancel to tiny values in the dark hole, so their
-// rounding must not grow with the length). The epilogue (alpha, beta, mask, intensity) runs in
+// rounding must not grow with the length). The correction sums stay in float32 to the end of a slice:
+// their terms are below 2^-7 of the products', so of N pairs they leave about 2^-31 sqrt(5 N / 8) of
+// the largest term (2^-26 for 8192 inputs), and taking them along in every fold cost 2 to 5 % of the
+// products from 512 outputs on and changed no error by more than 2 %. The epilogue (alpha, beta, mask, intensity) runs in
 // float64. Products with few tiles and long sums are split over j; the float64 partial sums go
 // to the workspace and split_reduce adds them in a fixed order (deterministic).
 // Measured (MI355X, 4096^2 -> 256^2 and back): 765 us with the complex products on float32 MFMA
@@ -135,7 +138,7 @@ __device__ __forceinline__ void bf_split2(float x0, float x1, unsigned &hi, unsi
 constexpr int kFoldFree = 32;      // free indices (rows or columns of the data) per block
 constexpr int kFoldStage = 64;     // pairs per stage: four 16-deep MFMA steps
 constexpr int kFoldThreads = 512;  // eight waves
-constexpr int kFoldDepth = 128;    // pairs a float32 sum runs over before it goes to float64
+constexpr int kFoldDepth = 64;     // pairs a float32 sum runs over before it goes to float64
 constexpr int kFoldPieces = 12;    // P.re, P.im, M.re, M.im, each hi, mid, lo
 // a piece of one stage in LDS: 16-byte units of eight consecutive pairs of one free index, unit
 // (pair / 8) * 32 + free index, so that a wave's fragment read is 1 KiB contiguous; the free
@@ -323,8 +326,8 @@ fold_kernel(FoldParams gp) {
       for (int q = 0; q < 3; ++q) b[t][q] = tab[(size_t(step + t) * 3 + q) * 64];
   };
 
-  // float32 sums of the current group (re and im, each as hi hi and correction sums; the
-  // corrections are at most 2^-7 of the sum, so theirs run on to the end)
+  // float32 sums of the current group (re and im, each as hi hi and correction sums; the corrections'
+  // run on to the end, see the head of this file)
   floatx16 rh = floatx16{0.f}, rc = floatx16{0.f}, ih = floatx16{0.f}, ic = floatx16{0.f};
   double totr[16], toti[16];
 #pragma unroll
@@ -529,6 +532,7 @@ fold_short_kernel(FoldArgs a, int tiles_per_block) {
   const int out_half = a.P / 2, tiles = fold_tiles(a.P), steps = fold_steps(a.Q);
   Loader ld(a, tid, f0, blockIdx.x == 0);
   const int used = (ld.half + 31) / 32 * 2;  // steps with a pair, in twos (both stages end on zeros)
+  const int top = max(used - 2, 0);          // the first two that are summed
   {
     typename Loader::Regs r0, r1;
     if (ld.fits && ld.half == kShortPairs) {
@@ -563,8 +567,8 @@ fold_short_kernel(FoldArgs a, int tiles_per_block) {
   };
   int tile = blockIdx.x * tiles_per_block + wave;
   if (tile < last) {
-    load_tab(tb[0], tile, 0);
-    load_tab(tb[1], tile, 1);
+    load_tab(tb[0], tile, top);
+    load_tab(tb[1], tile, top + 1);
   }
   for (; tile < last; tile += 8) {
     const int next = tile + 8 < last ? tile + 8 : tile;
@@ -582,13 +586,16 @@ fold_short_kernel(FoldArgs a, int tiles_per_block) {
         fold_step<COLS>(d, b[par], s[par][0], s[par][1], s[par][2], s[par][3]);
       }
     };
-    // the last steps load the next tile's first ones: they are on their way before the stores
-    for (int step = 0; step < used; step += 2) {
-      const bool more = step + 2 < used;
+    // from the outermost pairs inward: a focal field is largest about the axis, and what is added after
+    // its peak is rounded at the peak's scale (256^2 -> 4096^2, largest error over the largest result of
+    // a field falling off as 1 / r^2: outward 3.3e-7, inward 1.1e-7, the float32 matrix unit 1.8e-7).
+    // The last steps load the next tile's first ones: they are on their way before the stores
+    for (int step = used - 2; step >= 0; step -= 2) {
+      const bool more = step > 0;
       multiply(step, tb[0]);
-      load_tab(tb[0], more ? tile : next, more ? step + 2 : 0);
+      load_tab(tb[0], more ? tile : next, more ? step - 2 : top);
       multiply(step + 1, tb[1]);
-      load_tab(tb[1], more ? tile : next, more ? step + 3 : 1);
+      load_tab(tb[1], more ? tile : next, more ? step - 1 : top + 1);
     }
     int fbase = f0;
     asm("" : "+s"(fbase));  // the rows' addresses are formed here, not kept across the products

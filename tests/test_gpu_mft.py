@@ -193,3 +193,18 @@ def test_rounding_errors_do_not_gather_on_the_axis():
     d = to_np(fb.mft_forward(to_gpu(e), n_d, m, du)) - oracle.mft(f32(e), n_d, m, du)
     rows, cols = (np.sqrt(np.mean(np.abs(d) ** 2, axis=a)) for a in (1, 0))
     assert rows[m // 2] <= 2.0 * np.median(rows) and cols[m // 2] <= 2.0 * np.median(cols)
+
+
+@pytest.mark.parametrize("m,n", [(256, 4096), (255, 1500), (300, 2048), (512, 700)])
+def test_peaked_fields_keep_their_peak(m, n):
+    # a focal field falling off as 1 / r^2 from a point off the axis. Largest error over the largest
+    # result: the rounding of the intermediate product and of the result (2^-24 each), of the matrix
+    # entries along both axes (2^-25 each) and of the sums, which may add as much again: 4 x 2^-24
+    banner(f"mft_adjoint {m} -> {n}, peaked field")
+    n_d, du = 0.4 * n, 0.37 if n < 1000 else 0.11
+    rng = np.random.default_rng(m + n)
+    x = np.arange(m) - m // 2
+    r2 = (x[:, None] + 0.13 * m) ** 2 + (x[None, :] - 0.17 * m) ** 2
+    eb = np.exp(1j * rng.normal(size=(m, m))) / (1.0 + r2 / 9.0)
+    got, ref = to_np(fb.mft_adjoint(to_gpu(eb), n_d, n, du)), oracle.mft_adjoint(f32(eb), n_d, n, du)
+    assert np.max(np.abs(got - ref)) <= 4 * 2.0 ** -24 * np.max(np.abs(ref))
