@@ -263,6 +263,8 @@ int fresnel_step_exact_batched(fr_ctx *ctx, const fr_plane *planes, int32_t coun
  *   mft_adjoint: out = alpha (du/n_d) W^H in conj(W) + beta out, then out *= out_mask;
  *                the exact adjoint of mft_forward for alpha = 1, beta = 0; alpha = -1,
  *                beta = 1 is the Babinet subtraction of an occulting spot.
+ * The field may hold any finite float32 values; the product along the rows is rounded to float32,
+ * and one that is not finite leaves no finite result behind it.
  * ld_in / ld_out: row strides in elements (>= width), so a window of a larger plane can be
  * read or updated in place. out_mask: float, same shape as out, or NULL.
  * ws: device workspace of at least mft_workspace_bytes(n_in, m_out) bytes (forward) or

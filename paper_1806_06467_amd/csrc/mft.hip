@@ -235,6 +235,15 @@ struct FoldLoader {
       r.m[q] = make_float2(w * r.m[q].x, w * r.m[q].y);
     }
   }
+  // the largest magnitude's bits
+  __device__ __forceinline__ unsigned peak(const Regs &r) const {
+    unsigned k = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      k = max(max(max(k, __float_as_uint(r.p[q].x) & 0x7fffffffu), __float_as_uint(r.p[q].y) & 0x7fffffffu),
+              max(__float_as_uint(r.m[q].x) & 0x7fffffffu, __float_as_uint(r.m[q].y) & 0x7fffffffu));
+    return k;
+  }
   __device__ __forceinline__ void put_part(uint4 *dst, float v0, float v1, float v2, float v3) const {
     unsigned h[2], m[2], l[2];
     bf_split2(v0, v1, h[0], m[0], l[0]);
@@ -283,6 +292,20 @@ __device__ __forceinline__ void fold_step(const bf16x8 (&d)[6], const bf16x8 (&b
   ih = fold_mfma<COLS>(d[3], b[0], ih);
 }
 
+// What a block's magnitudes are, from the largest bit pattern each lane saw: flags per wave, and after a
+// barrier those of the block
+enum { kSmall = 1, kWithin = 2, kBeyond = 4 };  // some not zero, some from `low` on, some from `high` on
+__device__ __forceinline__ void range_mark(int *range, int wave, int lane, unsigned peak, unsigned low, unsigned high) {
+  const int mine = (__any(peak != 0u) ? kSmall : 0) | (__any(peak >= low) ? kWithin : 0) | (__any(peak >= high) ? kBeyond : 0);
+  if (lane == 0) range[wave] = mine;
+}
+__device__ __forceinline__ int range_seen(const int *range) {
+  int all = 0;
+#pragma unroll
+  for (int w = 0; w < kFoldThreads / 64; ++w) all |= range[w];
+  return __builtin_amdgcn_readfirstlane(all);
+}
+
 // One folded product. A block forms 32 free indices by 64 positive outputs (both signs of each):
 // eight waves, each one parity (cosine or sine), one 32-wide output tile and one half of every
 // stage's pairs (the halves are added in the epilogue). The data are loaded two stages ahead,
@@ -298,6 +321,7 @@ fold_kernel(FoldParams gp) {
   const FoldArgs &a = gp.a;
   __shared__ __attribute__((aligned(16))) unsigned char lds[8 * 16 * 64 * 16 + 16 * kFoldFree * 16];
   __shared__ float2 in0[kFoldFree];  // the unpaired element of each free index (slice 0 adds it)
+  __shared__ __attribute__((aligned(16))) int range[kFoldThreads / 64];
   uint4 *pieces = reinterpret_cast<uint4 *>(lds);  // [2][kFoldPieces][kPieceUnits]
   constexpr int kBuf = kFoldPieces * kPieceUnits;
   static_assert(2 * kBuf * 16 <= 8 * 16 * 64 * 16, "stage buffers fit the exchange area");
@@ -396,29 +420,13 @@ fold_kernel(FoldParams gp) {
     }
     if (s < nfull) stage(s, 0, r0, r1);
   }
-  // a last partial stage (every stage where the data's bytes do not fit 32-bit offsets)
-  for (int s = nfull; s < nst; ++s) {
-    ld.load_any(r0, jbeg + s * kFoldStage);
-    load_tab(tb[0], step0 + 4 * s);
-    ld.put_re(r0, pieces, true);
-    ld.put_im(r0, pieces, true);
-    __syncthreads();
-    multiply(0, 2 * ks, tb[0][0]);
-    multiply(0, 2 * ks + 1, tb[0][1]);
-    if (++pending == kStagesPerFold) {
-      fold();
-      pending = 0;
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    totr[r] += double(rh[r]) + double(rc[r]);
-    toti[r] += double(ih[r]) + double(ic[r]);
-  }
-
-  // exchange: every wave's totals, then each wave of a tile (2 parities x KS halves) forms both
-  // signs of its share of the tile's outputs
+  // The ends of float32's range lie outside the pieces': a value from 2^128 - 2^119 on rounds to an
+  // infinite piece and a sum of two may be infinite from 2^127 on, so that the totals are not finite;
+  // below 2^-110 the last piece is cut. A block whose totals are not finite, or all below 2^-100,
+  // repeats its sums on data scaled by 2^-16 or 2^32 (unscaled again if that was too much, where larger
+  // values had cancelled). The look at the totals costs at most 1 % of a transform.
+  constexpr float kDown = 0x1p-16f, kUp = 0x1p32f;
+  float scale = 1.f;
   double2 *ex = reinterpret_cast<double2 *>(lds);
   double2 *zs = ex + 8 * 16 * 64;  // [16 groups of pairs][free index]
   float2 unpaired = make_float2(0.f, 0.f);
@@ -429,12 +437,52 @@ fold_kernel(FoldParams gp) {
     f = min(f0 + int(f), a.F - 1);
     unpaired = COLS ? a.data[size_t(half) * a.ldd + f] : a.data[size_t(f) * a.ldd + half];
   }
-  __syncthreads();
+  for (int first = nfull, repeats = 0;; first = 0, ++repeats) {
+    // a last partial stage (every stage where the data's bytes do not fit 32-bit offsets, or repeated)
+    for (int s = first; s < nst; ++s) {
+      ld.load_any(r0, jbeg + s * kFoldStage);
+      if (scale != 1.f) ld.scale(r0, scale);
+      load_tab(tb[0], step0 + 4 * s);
+      ld.put_re(r0, pieces, true);
+      ld.put_im(r0, pieces, true);
+      __syncthreads();
+      multiply(0, 2 * ks, tb[0][0]);
+      multiply(0, 2 * ks + 1, tb[0][1]);
+      if (++pending == kStagesPerFold) {
+        fold();
+        pending = 0;
+      }
+      __syncthreads();
+    }
+    // exchange: every wave's totals, then each wave of a tile (2 parities x KS halves) forms both
+    // signs of its share of the tile's outputs (every stage ended on a barrier: the buffers are free)
+    double sum[2] = {0.0, 0.0};
 #pragma unroll
-  for (int r = 0; r < 16; ++r) ex[(wave * 16 + r) * 64 + lane] = make_double2(totr[r], toti[r]);
-  zs[ld.jq * kFoldFree + ld.lf] = make_double2(ld.zero_re, ld.zero_im);
-  if (tid < kFoldFree) in0[tid] = unpaired;
-  __syncthreads();
+    for (int r = 0; r < 16; ++r) {
+      totr[r] += double(rh[r]) + double(rc[r]);
+      toti[r] += double(ih[r]) + double(ic[r]);
+      ex[(wave * 16 + r) * 64 + lane] = make_double2(totr[r], toti[r]);
+      sum[0] += fabs(totr[r]);
+      sum[1] += fabs(toti[r]);
+    }
+    zs[ld.jq * kFoldFree + ld.lf] = make_double2(ld.zero_re, ld.zero_im);
+    if (tid < kFoldFree) in0[tid] = unpaired;
+    range_mark(range, wave, lane, unsigned(__double2hiint(sum[0] + sum[1])), unsigned(1023 - 100) << 20, 0x7ff00000u);
+    __syncthreads();
+    const int seen = range_seen(range);
+    float next = scale;
+    if (repeats == 0) next = seen & kBeyond ? kDown : seen == kSmall ? kUp : 1.f;
+    else if (scale == kUp && (seen & kBeyond)) next = 1.f;
+    if (next == scale) break;
+    __syncthreads();
+    scale = next;
+    pending = 0;
+    ld.zero_re = ld.zero_im = 0.0;
+    rh = rc = ih = ic = floatx16{0.f};
+#pragma unroll
+    for (int r = 0; r < 16; ++r) totr[r] = toti[r] = 0.0;
+  }
+  const double back = 1.0 / double(scale);
   const int rows = COLS ? a.P : a.F, cols = COLS ? a.F : a.P;
   // A column product, the second of a transform, may add a background and apply a mask: its eight
   // results' loads go out ahead of the stores (one after the other, each behind the last one's wait,
@@ -475,7 +523,7 @@ fold_kernel(FoldParams gp) {
     for (int h = 0; h < KS; ++h) {
       const double2 cv = ex[(((h * KT + kt) * 2) * 16 + r) * 64 + lane];
       const double2 sv = ex[(((h * KT + kt) * 2 + 1) * 16 + r) * 64 + lane];
-      const double w = fold_negated(2 * h) ? -1.0 : 1.0;  // (the sign of the half's matrix entries)
+      const double w = fold_negated(2 * h) ? -back : back;  // (the sign of the half's matrix entries)
       c.x += w * cv.x;
       c.y += w * cv.y;
       s.x += w * sv.x;
@@ -496,8 +544,8 @@ fold_kernel(FoldParams gp) {
 #pragma unroll
     for (int q = 0; q < 16; ++q) {
       const double2 v = zs[q * kFoldFree + tid];
-      z.x += v.x;
-      z.y += v.y;
+      z.x += back * v.x;
+      z.y += back * v.y;
     }
     emit(out_half, f0 + tid, z.x, z.y, in);
   }
@@ -526,6 +574,7 @@ fold_short_kernel(FoldArgs a, int tiles_per_block) {
   __shared__ __attribute__((aligned(16))) uint4 pieces[2 * kBuf];  // [stage][kFoldPieces][kPieceUnits]
   __shared__ double2 zs[16 * kFoldFree];                           // [group of pairs][free index]
   __shared__ float2 in0[kFoldFree];
+  __shared__ __attribute__((aligned(16))) int range[kFoldThreads / 64];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int f0 = blockIdx.y * kFoldFree;
@@ -533,6 +582,7 @@ fold_short_kernel(FoldArgs a, int tiles_per_block) {
   Loader ld(a, tid, f0, blockIdx.x == 0);
   const int used = (ld.half + 31) / 32 * 2;  // steps with a pair, in twos (both stages end on zeros)
   const int top = max(used - 2, 0);          // the first two that are summed
+  double back = 1.0;
   {
     typename Loader::Regs r0, r1;
     if (ld.fits && ld.half == kShortPairs) {
@@ -543,16 +593,23 @@ fold_short_kernel(FoldArgs a, int tiles_per_block) {
       ld.load_any(r0, 0);
       ld.load_any(r1, kFoldStage);
     }
+    // the block's data in the range of the pieces (see fold_kernel; here the values themselves tell)
+    const unsigned peak = max(ld.peak(r0), ld.peak(r1));
+    range_mark(range, wave, lane, peak, unsigned(127 - 70) << 23, unsigned(127 + 100) << 23);
+    __syncthreads();
+    const int seen = range_seen(range);
+    const float scale = seen & kBeyond ? 0x1p-32f : seen == kSmall ? 0x1p64f : 1.f;
+    back = 1.0 / double(scale);
     // the sign of the free index, and of the matrix entries of the thread's step
     const float sgn = short_sign(f0 + ld.lf) * (fold_negated(ld.jq >> 2) ? -1.f : 1.f);
-    ld.scale(r0, sgn);
-    ld.scale(r1, sgn);
+    ld.scale(r0, sgn * scale);
+    ld.scale(r1, sgn * scale);
     ld.put_re(r0, pieces, true);
     ld.put_im(r0, pieces, true);
     ld.put_re(r1, pieces + kBuf, true);
     ld.put_im(r1, pieces + kBuf, true);
     if (ld.jq == 0) in0[ld.lf] = *ld.centre;
-    zs[ld.jq * kFoldFree + ld.lf] = make_double2(double(sgn) * ld.zero_re, double(sgn) * ld.zero_im);
+    zs[ld.jq * kFoldFree + ld.lf] = make_double2(sgn * back * ld.zero_re, sgn * back * ld.zero_im);
   }
   __syncthreads();
   const double sg = a.sign;
@@ -606,7 +663,7 @@ fold_short_kernel(FoldArgs a, int tiles_per_block) {
       const int k = tile * 32 + (COLS ? trow : tcol) + 1;
       if (ff >= a.F || k > out_half) continue;
       const float2 z = in0[lf];
-      const double w = short_sign(ff);
+      const double w = short_sign(ff) * back;
       const double cx = w * (double(s[0][0][r]) + double(s[0][1][r])) + double(z.x);
       const double cy = w * (double(s[0][2][r]) + double(s[0][3][r])) + double(z.y);
       const double sx = w * (double(s[1][0][r]) + double(s[1][1][r]));

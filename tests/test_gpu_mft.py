@@ -208,3 +208,38 @@ def test_peaked_fields_keep_their_peak(m, n):
     eb = np.exp(1j * rng.normal(size=(m, m))) / (1.0 + r2 / 9.0)
     got, ref = to_np(fb.mft_adjoint(to_gpu(eb), n_d, n, du)), oracle.mft_adjoint(f32(eb), n_d, n, du)
     assert np.max(np.abs(got - ref)) <= 4 * 2.0 ** -24 * np.max(np.abs(ref))
+
+
+# a large and a small output of either kernel: sums over all pairs, and short sums of a large output
+@pytest.mark.parametrize("n,m", [(333, 77), (1030, 256), (2050, 65)])
+@pytest.mark.parametrize("scale", [1e-36, 1e-34, 1e-30, 1e30, 1e35])
+def test_float32_range(n, m, scale):
+    # the bar of the products at ordinary magnitudes (test_folded_products_at_tile_edges) holds as long
+    # as the results are ordinary float32 numbers
+    banner(f"mft {n} <-> {m} of fields about {scale:g}")
+    n_d, du = 0.4 * n, 0.11
+    e, eb = scale * synth.random_field(n, n + m), scale * synth.random_field(m, n + m + 1)
+    got, ref = to_np(fb.mft_forward(to_gpu(e), n_d, m, du)) / scale, oracle.mft(f32(e) / scale, n_d, m, du)
+    assert rel_l2(got, ref) <= 1.5e-6
+    got, ref = to_np(fb.mft_adjoint(to_gpu(eb), n_d, n, du)) / scale, oracle.mft_adjoint(f32(eb) / scale, n_d, n, du)
+    assert rel_l2(got, ref) <= 1.5e-6
+
+
+@pytest.mark.parametrize("n,m", [(333, 77), (1030, 256), (2050, 65)])
+def test_float32_range_at_its_upper_end(n, m):
+    # one value that rounds to an infinite bfloat16, and two whose difference is infinite in float32
+    # while the sums they enter are not: their sine stays below sin(0.55)
+    banner(f"mft {n} <-> {m} of fields at the end of float32's range")
+    big, off = float(np.float32(3.398e38)), 4
+    n_d = 1.2 * n
+    du = 0.55 / (2 * np.pi * off * (n // 2)) * n_d
+    for size, run, ref in ((n, lambda t: fb.mft_forward(t, n_d, m, du), lambda e: oracle.mft(e, n_d, m, du)),
+                           (m, lambda t: fb.mft_adjoint(t, n_d, n, du), lambda e: oracle.mft_adjoint(e, n_d, n, du))):
+        e = np.zeros((size, size), dtype=np.complex64)
+        e[size // 2 + 1, size // 2 - off] = big
+        got, want = to_np(run(to_gpu(e))), ref(e.astype(np.complex128))
+        assert rel_l2(got / big, want / big) <= 1.5e-6
+        e[:] = 0
+        e[size // 2, size // 2 - off], e[size // 2, size // 2 + off] = -2.5e38, 2.5e38
+        got, want = to_np(run(to_gpu(e))), ref(e.astype(np.complex128))
+        assert rel_l2(got / big, want / big) <= 1.5e-6
