@@ -156,6 +156,7 @@ constexpr int kMaxSplit = 16;
 // picks its tile by shape, has replaced; the split factor beside them is used)
 constexpr int kGemmTiles = 7;
 int fold_split_for(const FoldArgs &a);
+int fold_short_tiles(int tiles, int ftiles);
 hipError_t launch_fold(const FoldArgs &a, int split, void *partial, hipStream_t stream, const LaunchHook &hook);
 
 }  // namespace fr
