@@ -79,3 +79,19 @@ def test_folded_products_at_tile_edges(n, m):
     assert rel_l2(got, oracle.mft(e.astype(np.complex128), n_d, m, du)) <= 1e-12
     got = fb.mft_f64(torch.from_numpy(eb.astype(np.complex128)).cuda(), n_d, n, du, adjoint=True).cpu().numpy()
     assert rel_l2(got, oracle.mft_adjoint(eb.astype(np.complex128), n_d, n, du)) <= 1e-12
+
+
+# column products of at most eight pairs (the adjoint of at most 17 focal samples): one to eight pairs,
+# odd and even, outputs without a positive index, around a wave's 16 and a block's 64 outputs and 64
+# columns, and the first length with nine pairs
+@pytest.mark.parametrize("m", [1, 2, 3, 8, 15, 16, 17, 18])
+@pytest.mark.parametrize("n", [1, 2, 31, 34, 64, 127, 130, 1025])
+def test_short_column_products(n, m):
+    # the bar of test_folded_products_at_tile_edges: sums of at most 18 terms, twice
+    n_d, du = max(1.0, 0.4 * n), 0.37
+    eb = synth.random_field(m, n + m).astype(np.complex128)
+    got = _host(fb.mft_f64(_dev(eb), n_d, n, du, adjoint=True))
+    assert rel_l2(got, oracle.mft_adjoint(eb, n_d, n, du)) <= 1e-12
+    e = synth.random_field(m, n + m + 1).astype(np.complex128)
+    got = _host(fb.mft_f64(_dev(e), n_d, n, du))
+    assert rel_l2(got, oracle.mft(e, n_d, n, du)) <= 1e-12
