@@ -702,6 +702,133 @@ fold_short_kernel(FoldArgs a, int tiles_per_block) {
   }
 }
 
+// Products of at most kFewPairs pairs (one matrix step) with a small output, where the kernels above are a
+// chain of waits around one stage. Here the loads of the data and of the matrix go out together, then come
+// vector multiply-adds in float64 on the folded pairs and the entries (the sum of their pieces, rounded to
+// float32), and the stores. Along columns a lane holds a column's pairs and a wave walks `per_wave` (at most
+// kFewOut) positive outputs, their entries in LDS; along rows a lane holds an output's entries and a wave a
+// row, its pairs in LDS. (Both products of a transform in a recorded graph: 16^2 -> 512^2 14.4 us above, 6.3 us
+// here, 10.1 us as complex products of 64 x 64 tiles; 33^2 -> 512^2 14.7, 7.7 and 17.4 us.)
+constexpr int kFewPairs = 16;
+constexpr int kFewOut = 8;
+// four entries from their pieces' words
+__device__ __forceinline__ float4 few_entries(uint2 hi, uint2 mid, uint2 lo) {
+  auto sum = [](unsigned h, unsigned m, unsigned l) {
+    return (__uint_as_float(h) + __uint_as_float(m)) + __uint_as_float(l);
+  };
+  constexpr unsigned kTop = 0xffff0000u;
+  return make_float4(sum(hi.x << 16, mid.x << 16, lo.x << 16), sum(hi.x & kTop, mid.x & kTop, lo.x & kTop),
+                     sum(hi.y << 16, mid.y << 16, lo.y << 16), sum(hi.y & kTop, mid.y & kTop, lo.y & kTop));
+}
+struct FewPair {
+  double px, py, mx, my;  // folded pair
+};
+template <bool COLS, int PAIRS>
+__global__ void __launch_bounds__(256) fold_few_kernel(FoldArgs a, int per_wave) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int half = a.Q / 2, full_pairs = a.Q - 1 - half, out_half = a.P / 2;
+  const int tiles = fold_tiles(a.P), steps = fold_steps(a.Q);
+  const double sg = a.sign;
+  // words of four pieces of pairs 4 q + 1 .. 4 q + 4 of positive output k + 1
+  auto entries = [&](int par, int k, int q) {
+    const int kc = min(k, tiles * 32 - 1);
+    const uint2 *t = static_cast<const uint2 *>(a.table) +
+                     ((size_t(par * tiles + kc / 32) * steps * 3 * 64) + kc % 32 + 32 * (q >> 1)) * 2 + (q & 1);
+    return few_entries(t[0], t[128], t[256]);
+  };
+  auto fold = [](float2 p, float2 m) {
+    return FewPair{double(p.x) + double(m.x), double(p.y) + double(m.y), double(p.x) - double(m.x), double(p.y) - double(m.y)};
+  };
+  struct Sums {
+    double cx, cy, sx, sy;
+    __device__ __forceinline__ void add(const FewPair &v, float c, float s) {
+      cx = fma(v.px, double(c), cx);
+      cy = fma(v.py, double(c), cy);
+      sx = fma(v.mx, double(s), sx);
+      sy = fma(v.my, double(s), sy);
+    }
+  };
+  auto emit = [&](int o, int f, double re, double im) { epilogue(a, COLS ? o : f, COLS ? f : o, re, im); };
+  auto both = [&](int k, int f, const Sums &v) {
+    if (k + 1 < a.P - out_half) emit(out_half + k + 1, f, v.cx - sg * v.sy, v.cy + sg * v.sx);
+    emit(out_half - k - 1, f, v.cx + sg * v.sy, v.cy - sg * v.sx);
+  };
+  if constexpr (COLS) {
+    __shared__ float4 w[4 * kFewOut][2][PAIRS / 4];
+    const int f = blockIdx.y * 64 + lane, first = (blockIdx.x * 4 + wave) * per_wave;
+    const float2 *c = a.data + size_t(half) * a.ldd + min(f, a.F - 1);
+    const float2 in0 = *c;
+    float2 p[PAIRS], m[PAIRS];
+#pragma unroll
+    for (int j = 1; j <= PAIRS; ++j) {
+      p[j - 1] = c[ptrdiff_t(min(j, full_pairs)) * a.ldd];
+      m[j - 1] = c[-ptrdiff_t(min(j, half)) * a.ldd];
+    }
+    constexpr int QUADS = PAIRS / 4;
+    if (tid < 8 * QUADS * per_wave) {
+      const int q = tid % QUADS, par = tid / QUADS % 2, i = tid / (2 * QUADS);
+      w[i][par][q] = entries(par, blockIdx.x * 4 * per_wave + i, q);
+    }
+    FewPair v[PAIRS];
+#pragma unroll
+    for (int j = 1; j <= PAIRS; ++j)
+      v[j - 1] = fold(j <= full_pairs ? p[j - 1] : make_float2(0.f, 0.f), j <= half ? m[j - 1] : make_float2(0.f, 0.f));
+    __syncthreads();
+    if (f >= a.F) return;
+    for (int k = first; k < min(out_half, first + per_wave); ++k) {
+      Sums s{in0.x, in0.y, 0.0, 0.0};
+#pragma unroll
+      for (int q = 0; q < PAIRS / 4; ++q) {
+        const float4 cw = w[wave * per_wave + k - first][0][q], sw = w[wave * per_wave + k - first][1][q];
+        s.add(v[4 * q], cw.x, sw.x);
+        s.add(v[4 * q + 1], cw.y, sw.y);
+        s.add(v[4 * q + 2], cw.z, sw.z);
+        s.add(v[4 * q + 3], cw.w, sw.w);
+      }
+      both(k, f, s);
+    }
+    if (first == 0) {
+      double zx = in0.x, zy = in0.y;
+#pragma unroll
+      for (int j = 0; j < PAIRS; ++j) {
+        zx += v[j].px;
+        zy += v[j].py;
+      }
+      emit(out_half, f, zx, zy);
+    }
+  } else {
+    __shared__ FewPair v[4][PAIRS];
+    const int f = blockIdx.y * 4 + wave, k = blockIdx.x * 64 + lane, j = (lane & (PAIRS - 1)) + 1;
+    const float2 *c = a.data + size_t(min(f, a.F - 1)) * a.ldd + half;
+    const float2 in0 = *c, p = c[min(j, full_pairs)], m = c[-min(j, half)];
+    float4 cw[PAIRS / 4], sw[PAIRS / 4];
+#pragma unroll
+    for (int q = 0; q < PAIRS / 4; ++q) {
+      cw[q] = entries(0, k, q);
+      sw[q] = entries(1, k, q);
+    }
+    if (lane < PAIRS) v[wave][lane] = fold(j <= full_pairs ? p : make_float2(0.f, 0.f), j <= half ? m : make_float2(0.f, 0.f));
+    __syncthreads();
+    if (f >= a.F) return;
+    Sums s{in0.x, in0.y, 0.0, 0.0};
+    double zx = in0.x, zy = in0.y;
+#pragma unroll
+    for (int q = 0; q < PAIRS / 4; ++q) {
+      s.add(v[wave][4 * q], cw[q].x, sw[q].x);
+      s.add(v[wave][4 * q + 1], cw[q].y, sw[q].y);
+      s.add(v[wave][4 * q + 2], cw[q].z, sw[q].z);
+      s.add(v[wave][4 * q + 3], cw[q].w, sw[q].w);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        zx += v[wave][4 * q + i].px;
+        zy += v[wave][4 * q + i].py;
+      }
+    }
+    if (k < out_half) both(k, f, s);
+    if (k == 0) emit(out_half, f, zx, zy);
+  }
+}
+
 // output rows over blockIdx.y, columns over blockIdx.x and the threads (no index division),
 // the partials added in slice order
 __global__ void __launch_bounds__(256) split_reduce(FoldParams gp, int rows, int cols) {
@@ -751,12 +878,27 @@ hipError_t launch_short_kernel(const FoldArgs &a, hipStream_t stream) {
   return hipGetLastError();
 }
 
+template <bool COLS>
+hipError_t launch_few_kernel(const FoldArgs &a, hipStream_t stream) {
+  // along columns as many outputs per wave as leave every compute unit a block (33^2 -> 1400^2 with 8, 4 and 2
+  // outputs 14.7, 17.0 and 21.5 us; 33^2 -> 512^2 with 2, a block per compute unit, and 4 7.8 and 8.6 us)
+  int per = kFewOut;
+  while (per > 1 && div_up(a.P / 2, 4 * per) * div_up(a.F, 64) < 256) per /= 2;
+  const dim3 grid(std::max(div_up(a.P / 2, COLS ? 4 * per : 64), 1), div_up(a.F, COLS ? 64 : 4));
+  if (a.Q / 2 <= kFewPairs / 2) hipLaunchKernelGGL((fold_few_kernel<COLS, kFewPairs / 2>), grid, dim3(256), 0, stream, a, per);
+  else hipLaunchKernelGGL((fold_few_kernel<COLS, kFewPairs>), grid, dim3(256), 0, stream, a, per);
+  return hipGetLastError();
+}
+
 // short sums over an output large enough that every wave walks tiles: below that the general
 // kernel's two halves of every stage on different waves are faster (256^2 -> 1024^2 with mask and
 // background 16 us against 37 us, 256^2 -> 2048^2 43 us against 25 us)
 bool short_pairs(const FoldArgs &a) {
   return a.Q / 2 <= kShortPairs && (long long)fold_tiles(a.P) * div_up(a.F, kFoldFree) >= 1024;
 }
+// one matrix step over a smaller output (from there on the short kernel is the faster: the matrix unit's
+// work hides behind the stores)
+bool few_pairs(const FoldArgs &a) { return a.Q / 2 <= kFewPairs && !short_pairs(a); }
 
 }  // namespace
 
@@ -768,7 +910,7 @@ bool short_pairs(const FoldArgs &a) {
 // 26, 33; 1024 x 256 21, 25, 25; length 512: 512 x 1024 17, 26, 29); over 100 products of those
 // edges this choice is at most 2 % behind that one and 5 % ahead of it in sum.
 int fold_split_for(const FoldArgs &a) {
-  if (short_pairs(a)) return 1;
+  if (short_pairs(a) || few_pairs(a)) return 1;
   const double blocks = double(div_up(fold_tiles(a.P), 2)) * div_up(a.F, kFoldFree);
   const int stages = div_up(a.Q / 2, kFoldStage);
   int best = 1;
@@ -785,7 +927,7 @@ int fold_split_for(const FoldArgs &a) {
 }
 
 hipError_t launch_fold(const FoldArgs &a, int split, void *partial, hipStream_t stream, const LaunchHook &hook) {
-  if (short_pairs(a)) split = 1;  // one group of pairs: nothing to slice
+  if (short_pairs(a) || few_pairs(a)) split = 1;  // one group of pairs: nothing to slice
   FoldParams gp;
   gp.a = a;
   gp.split = split;
@@ -796,6 +938,7 @@ hipError_t launch_fold(const FoldArgs &a, int split, void *partial, hipStream_t 
   std::snprintf(name, sizeof name, "fold%s_%dx%dx%d_s%d", a.cols ? "C" : "R", a.F, a.P, a.Q, split);
   hook(stream, name, a.Q, 0);
   hipError_t e = short_pairs(a) ? (a.cols ? launch_short_kernel<true>(a, stream) : launch_short_kernel<false>(a, stream))
+                 : few_pairs(a) ? (a.cols ? launch_few_kernel<true>(a, stream) : launch_few_kernel<false>(a, stream))
                                 : (a.cols ? launch_fold_kernel<true>(gp, stream) : launch_fold_kernel<false>(gp, stream));
   hook(stream, name, a.Q, 1);
   if (e != hipSuccess || split == 1) return e;

@@ -243,3 +243,36 @@ def test_float32_range_at_its_upper_end(n, m):
         e[size // 2, size // 2 - off], e[size // 2, size // 2 + off] = -2.5e38, 2.5e38
         got, want = to_np(run(to_gpu(e))), ref(e.astype(np.complex128))
         assert rel_l2(got / big, want / big) <= 1.5e-6
+
+
+# products of at most 16 pairs with a small output: no pair to 16, the two kernels' last lengths and the
+# next, odd and even; outputs without a positive index, around a wave's 64 outputs (rows) and columns, a
+# block's 4 rows and 32 outputs, and enough of them for eight outputs a wave
+@pytest.mark.parametrize("m", [1, 2, 3, 16, 17, 18, 32, 33, 34])
+@pytest.mark.parametrize("n", [1, 2, 31, 63, 66, 127, 130, 1025])
+def test_products_of_few_pairs(n, m):
+    # the bar of test_folded_products_at_tile_edges: fewer roundings than there
+    n_d, du = max(1.0, 0.4 * n), 0.37
+    eb, e = synth.random_field(m, n + m), synth.random_field(m, n + m + 1)
+    got = to_np(fb.mft_adjoint(to_gpu(eb), n_d, n, du))
+    assert rel_l2(got, oracle.mft_adjoint(f32(eb), n_d, n, du)) <= 1.5e-6
+    got = to_np(fb.mft_forward(to_gpu(e), n_d, n, du))
+    assert rel_l2(got, oracle.mft(f32(e), n_d, n, du)) <= 1.5e-6
+
+
+@pytest.mark.parametrize("m", [16, 33])
+def test_few_pairs_with_mask_background_and_range(m):
+    # the epilogue of the products of few pairs into a window, and fields at both ends of float32's range
+    n, nd, du = 300, 130, 0.37
+    plane, eb, lyot = synth.random_field(n, 13), synth.random_field(m, 14), synth.lyot_stop(nd, 0.9)
+    off = (n - nd) // 2
+    t = to_gpu(plane)
+    fb.mft_adjoint(to_gpu(eb), float(nd), nd, du, alpha=-1.0, beta=1.0, mask=to_gpu(lyot, torch.float32),
+                   out=t[off:off + nd, off:off + nd])
+    want = f32(plane).copy()
+    want[off:off + nd, off:off + nd] = lyot * (want[off:off + nd, off:off + nd]
+                                               - oracle.mft_adjoint(f32(eb), float(nd), nd, du))
+    assert rel_l2(to_np(t), want) <= 1.5e-6
+    for scale in (1e-35, 1e35):
+        got = to_np(fb.mft_adjoint(to_gpu(scale * eb), float(nd), nd, du)) / scale
+        assert rel_l2(got, oracle.mft_adjoint(f32(scale * eb) / scale, float(nd), nd, du)) <= 1.5e-6
