@@ -242,56 +242,106 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2
   }
 }
 
-// A column product of at most kShortPairs pairs, where a stage of the kernel above is mostly padding
-// (three of its four steps from 16 inputs down) and the exchange comes with every 64 outputs. Bound by
-// the output's bytes: a lane holds the folded pairs of one column and forms 16 outputs of either sign
-// with vector multiply-adds, the matrix entries wave-uniform. Measured (16^2 -> 4096^2, both products of the
-// transform): 80 us above, 52 us here; 57 us as complex products of 64 x 64 tiles.
-constexpr int kShortPairs = 8;
-constexpr int kShortK = 16;  // positive outputs per wave
-__global__ void __launch_bounds__(256) zshort_kernel(ZFold a, const z64 *__restrict__ data, const d2 *__restrict__ table,
-                                                     z64 *__restrict__ out) {
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int f = blockIdx.y * 64 + lane, half = a.Q / 2, full_pairs = a.Q - 1 - half, out_half = a.P / 2;
-  const z64 *c = data + size_t(half) * a.ldd + min(f, a.F - 1);
-  z64 sum[kShortPairs], diff[kShortPairs], in0 = *c, zero = in0;
-#pragma unroll
-  for (int j = 1; j <= kShortPairs; ++j) {
-    const z64 p = j <= full_pairs ? c[size_t(j) * a.ldd] : z64{0.0, 0.0};
-    const z64 m = j <= half ? c[-ptrdiff_t(j) * a.ldd] : z64{0.0, 0.0};
-    sum[j - 1] = {p.x + m.x, p.y + m.y};
-    diff[j - 1] = {p.x - m.x, p.y - m.y};
-  }
-  const int first = (blockIdx.x * 4 + wave) * kShortK, last = min(out_half, first + kShortK);
-  const int steps = zsteps(a.Q);
+// Products of at most kFewPairs pairs, where a stage of the kernel above is mostly padding (three of its four
+// steps) and its exchange comes with every 64 outputs. A large output along columns is bound by its bytes,
+// the others by the chain of loads, sums and stores. Along columns a lane holds a column's folded pairs and
+// a wave forms `per_wave` (at most kFewOut) outputs of either sign by vector multiply-adds, their matrix
+// entries in LDS; along rows a lane holds an output's entries and a wave a row, its pairs in LDS. (Both
+// products of a transform in a recorded graph: 16^2 -> 4096^2 80 us above, 48 us here, 57 us as complex
+// products of 64 x 64 tiles; 16^2 -> 200^2 12.1, 5.5 and 9.7 us.)
+constexpr int kFewPairs = 8;
+constexpr int kFewOut = 16;
+struct ZPair {
+  z64 sum, diff;
+};
+template <bool COLS>
+__global__ void __launch_bounds__(256) zfew_kernel(ZFold a, int per_wave) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int half = a.Q / 2, full_pairs = a.Q - 1 - half, out_half = a.P / 2;
+  const int steps = zsteps(a.Q), kmax = ztiles(a.P) * 32 - 1;
   const size_t par = size_t(ztiles(a.P)) * steps * 128;
-  auto emit = [&](int o, double x, double y) {
-    if (f < a.F) out[size_t(o) * a.ldc + f] = {a.scale * x, a.scale * y};
+  // entries of pairs i + 1 and i + 5 of positive output k + 1
+  auto entry = [&](int sine, int k, int i) {
+    const int kc = min(k, kmax);
+    return a.table[sine * par + (size_t(kc / 32) * steps * 2 + kc % 32 / 16) * 64 + kc % 16 + 16 * i];
   };
-  for (int k = first; k < last; ++k) {
-    const d2 *t = table + (size_t(k / 32) * steps * 2 + k % 32 / 16) * 64 + k % 16;
-    z64 cs = in0, sn = {0.0, 0.0};
+  auto fold = [](z64 p, z64 m) { return ZPair{{p.x + m.x, p.y + m.y}, {p.x - m.x, p.y - m.y}}; };
+  struct Sums {
+    z64 c, s;
+    __device__ __forceinline__ void add(const ZPair &v, double wc, double ws) {
+      c.x = fma(v.sum.x, wc, c.x);
+      c.y = fma(v.sum.y, wc, c.y);
+      s.x = fma(v.diff.x, ws, s.x);
+      s.y = fma(v.diff.y, ws, s.y);
+    }
+  };
+  auto emit = [&](int o, int f, double x, double y) {
+    a.out[COLS ? size_t(o) * a.ldc + f : size_t(f) * a.ldc + o] = {a.scale * x, a.scale * y};
+  };
+  auto both = [&](int k, int f, const Sums &v) {
+    if (k + 1 < a.P - out_half) emit(out_half + k + 1, f, v.c.x - a.sign * v.s.y, v.c.y + a.sign * v.s.x);
+    emit(out_half - k - 1, f, v.c.x + a.sign * v.s.y, v.c.y - a.sign * v.s.x);
+  };
+  constexpr z64 none = {0.0, 0.0};
+  if constexpr (COLS) {
+    __shared__ d2 w[4 * kFewOut][2][kFewPairs / 2];
+    const int f = blockIdx.y * 64 + lane, first = (blockIdx.x * 4 + wave) * per_wave;
+    const z64 *c = a.data + size_t(half) * a.ldd + min(f, a.F - 1);
+    z64 p[kFewPairs], m[kFewPairs];
+    const z64 in0 = *c;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const d2 w[2] = {t[16 * i], t[par + 16 * i]};  // pairs i + 1 and i + 5: cosines, sines
+    for (int j = 1; j <= kFewPairs; ++j) {
+      p[j - 1] = c[ptrdiff_t(min(j, full_pairs)) * a.ldd];
+      m[j - 1] = c[-ptrdiff_t(min(j, half)) * a.ldd];
+    }
+    for (int i = tid; i < 32 * per_wave; i += 256)
+      w[i >> 3][(i >> 2) & 1][i & 3] = entry((i >> 2) & 1, blockIdx.x * 4 * per_wave + (i >> 3), i & 3);
+    ZPair v[kFewPairs];
 #pragma unroll
-      for (int e = 0; e < 2; ++e) {
-        cs.x = fma(sum[i + 4 * e].x, w[0][e], cs.x);
-        cs.y = fma(sum[i + 4 * e].y, w[0][e], cs.y);
-        sn.x = fma(diff[i + 4 * e].x, w[1][e], sn.x);
-        sn.y = fma(diff[i + 4 * e].y, w[1][e], sn.y);
+    for (int j = 1; j <= kFewPairs; ++j) v[j - 1] = fold(j <= full_pairs ? p[j - 1] : none, j <= half ? m[j - 1] : none);
+    __syncthreads();
+    if (f >= a.F) return;
+    for (int k = first; k < min(out_half, first + per_wave); ++k) {
+      Sums s{in0, none};
+#pragma unroll
+      for (int i = 0; i < kFewPairs / 2; ++i) {
+        const d2 wc = w[wave * per_wave + k - first][0][i], ws = w[wave * per_wave + k - first][1][i];
+        s.add(v[i], wc[0], ws[0]);
+        s.add(v[i + 4], wc[1], ws[1]);
       }
+      both(k, f, s);
     }
-    if (k + 1 < a.P - out_half) emit(out_half + k + 1, cs.x - a.sign * sn.y, cs.y + a.sign * sn.x);
-    emit(out_half - k - 1, cs.x + a.sign * sn.y, cs.y - a.sign * sn.x);
-  }
-  if (first == 0) {
+    if (first == 0) {
+      z64 z = in0;
 #pragma unroll
-    for (int j = 0; j < kShortPairs; ++j) {
-      zero.x += sum[j].x;
-      zero.y += sum[j].y;
+      for (int j = 0; j < kFewPairs; ++j) z = {z.x + v[j].sum.x, z.y + v[j].sum.y};
+      emit(out_half, f, z.x, z.y);
     }
-    emit(out_half, zero.x, zero.y);
+  } else {
+    __shared__ ZPair v[4][kFewPairs];
+    const int f = blockIdx.y * 4 + wave, k = blockIdx.x * 64 + lane, j = (lane & (kFewPairs - 1)) + 1;
+    const z64 *c = a.data + size_t(min(f, a.F - 1)) * a.ldd + half;
+    const z64 in0 = *c, p = c[min(j, full_pairs)], m = c[-min(j, half)];
+    d2 wc[kFewPairs / 2], ws[kFewPairs / 2];
+#pragma unroll
+    for (int i = 0; i < kFewPairs / 2; ++i) {
+      wc[i] = entry(0, k, i);
+      ws[i] = entry(1, k, i);
+    }
+    if (lane < kFewPairs) v[wave][lane] = fold(j <= full_pairs ? p : none, j <= half ? m : none);
+    __syncthreads();
+    if (f >= a.F) return;
+    Sums s{in0, none};
+    z64 z = in0;
+#pragma unroll
+    for (int i = 0; i < kFewPairs / 2; ++i) {
+      s.add(v[wave][i], wc[i][0], ws[i][0]);
+      s.add(v[wave][i + 4], wc[i][1], ws[i][1]);
+    }
+#pragma unroll
+    for (int i = 0; i < kFewPairs; ++i) z = {z.x + v[wave][i].sum.x, z.y + v[wave][i].sum.y};
+    if (k < out_half) both(k, f, s);
+    if (k == 0) emit(out_half, f, z.x, z.y);
   }
 }
 
@@ -359,10 +409,13 @@ hipError_t zfold(ZFold a, hipStream_t st, const LaunchHook &hook, const char *na
   hook(st, name, 1, 0);
   a.j_per_split = std::max(div_up(div_up(a.Q / 2, split), kStage), 1) * kStage;
   const int ftiles = div_up(a.F, kFree);
-  if (COLS && a.Q / 2 <= kShortPairs)
-    hipLaunchKernelGGL(zshort_kernel, dim3(std::max(div_up(a.P / 2, 4 * kShortK), 1), div_up(a.F, 64)), dim3(256), 0, st, a,
-                       a.data, a.table, a.out);
-  else if (zblocks(a, 2) * split >= 512)
+  if (a.Q / 2 <= kFewPairs) {
+    // along columns as many outputs per wave as leave every compute unit two blocks
+    int per = kFewOut;
+    while (per > 1 && div_up(a.P / 2, 4 * per) * div_up(a.F, 64) < 512) per /= 2;
+    const dim3 grid(std::max(div_up(a.P / 2, COLS ? 4 * per : 64), 1), div_up(a.F, COLS ? 64 : 4));
+    hipLaunchKernelGGL((zfew_kernel<COLS>), grid, dim3(256), 0, st, a, per);
+  } else if (zblocks(a, 2) * split >= 512)
     hipLaunchKernelGGL((zfold_kernel<2, COLS>), dim3(div_up(ztiles(a.P), 2), ftiles, split), dim3(kThreads), 0, st, a);
   else
     hipLaunchKernelGGL((zfold_kernel<1, COLS>), dim3(ztiles(a.P), ftiles, split), dim3(kThreads), 0, st, a);

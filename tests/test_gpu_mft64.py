@@ -81,9 +81,9 @@ def test_folded_products_at_tile_edges(n, m):
     assert rel_l2(got, oracle.mft_adjoint(eb.astype(np.complex128), n_d, n, du)) <= 1e-12
 
 
-# column products of at most eight pairs (the adjoint of at most 17 focal samples): one to eight pairs,
-# odd and even, outputs without a positive index, around a wave's 16 and a block's 64 outputs and 64
-# columns, and the first length with nine pairs
+# products of at most eight pairs (the adjoint of at most 17 focal samples, the forward transform of at most
+# 17 pupil samples): no pair to eight, odd and even, outputs without a positive index, around a wave's 64
+# outputs (rows) and columns, a block's 4 rows and 64 outputs, and the first length with nine pairs
 @pytest.mark.parametrize("m", [1, 2, 3, 8, 15, 16, 17, 18])
 @pytest.mark.parametrize("n", [1, 2, 31, 34, 64, 127, 130, 1025])
 def test_short_column_products(n, m):
