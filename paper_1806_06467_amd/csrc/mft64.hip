@@ -431,29 +431,46 @@ uint64_t dbits(double v) {
 }
 
 // the table of ztiles / zsteps for an output of length p and an input of length q; the index
-// product is an exact integer, its turns reduced to [-1/2, 1/2] before the cosine and sine
+// product is an exact integer, its turns reduced to [-1/2, 1/2] before the cosine and sine. A
+// transform and its adjoint read the same entries in two orders: both are built with the first of
+// them, so that the other can be recorded into a graph, where no table can be built.
 int mft64_table(Ctx *ctx, int p, int q, double n_d, double du, hipStream_t s, const d2 **out) {
-  const TableKey key{kMft64, p, uint64_t(q), dbits(n_d), dbits(du), 0};
+  const TableKey key{kMft64, p, uint64_t(q), dbits(n_d), dbits(du), 0}, other{kMft64, q, uint64_t(p), dbits(n_d), dbits(du), 0};
   if (auto it = ctx->tables.find(key); it != ctx->tables.end()) {
     *out = static_cast<const d2 *>(it->second);
     return FR_OK;
   }
-  const int tiles = ztiles(p), steps = zsteps(q);
-  const size_t par = size_t(tiles) * steps * 256;
-  std::vector<double> w(2 * par, 0.0);
+  auto entries = [](int tiles, int steps) { return size_t(tiles) * steps * 256; };  // of one parity
+  auto at = [](int steps, int k, int j) {
+    const int lane = k % 16 + 16 * (j % 4);
+    return (((size_t(k / 32) * steps + j / 8) * 2 + k % 32 / 16) * 64 + lane) * 2 + j % 8 / 4;
+  };
+  const int steps = zsteps(q), steps2 = zsteps(p);
+  const size_t par = entries(ztiles(p), steps), par2 = entries(ztiles(q), steps2);
+  const bool both = p != q && ctx->tables.find(other) == ctx->tables.end();
+  std::vector<double> w(2 * par, 0.0), w2(both ? 2 * par2 : 0, 0.0);
   const double r = du / n_d;
   for (int k = 0; k < p / 2; ++k)
     for (int j = 0; j < q / 2; ++j) {
       double t = double(int64_t(k + 1) * int64_t(j + 1)) * r;
       t -= std::rint(t);
-      const int lane = k % 16 + 16 * (j % 4);
-      const size_t at = (((size_t(k / 32) * steps + j / 8) * 2 + k % 32 / 16) * 64 + lane) * 2 + j % 8 / 4;
-      w[at] = std::cos(2.0 * M_PI * t);
-      w[par + at] = std::sin(2.0 * M_PI * t);
+      const double c = std::cos(2.0 * M_PI * t), sn = std::sin(2.0 * M_PI * t);
+      const size_t i = at(steps, k, j);
+      w[i] = c;
+      w[par + i] = sn;
+      if (both) {
+        const size_t i2 = at(steps2, j, k);
+        w2[i2] = c;
+        w2[par2 + i2] = sn;
+      }
     }
   void *d = nullptr;
-  const int st = ctx->upload(key, w.data(), w.size() * sizeof(double), s, &d);
+  int st = ctx->upload(key, w.data(), w.size() * sizeof(double), s, &d);
   *out = static_cast<const d2 *>(d);
+  if (st == FR_OK && both) {
+    st = ctx->upload(other, w2.data(), w2.size() * sizeof(double), s, &d);
+    if (st == FR_ENOMEM) st = FR_OK;  // (this call does not need it)
+  }
   return st;
 }
 

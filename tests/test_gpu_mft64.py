@@ -95,3 +95,23 @@ def test_short_column_products(n, m):
     e = synth.random_field(m, n + m + 1).astype(np.complex128)
     got = _host(fb.mft_f64(_dev(e), n_d, n, du))
     assert rel_l2(got, oracle.mft(e, n_d, n, du)) <= 1e-12
+
+
+@pytest.mark.parametrize("adjoint", [False, True])
+def test_one_direction_prepares_the_other_for_a_graph(adjoint):
+    # tables cannot be built while a graph is recorded; those of a shape serve both directions
+    n, m, n_d, du = 222, 61, 111.0, 0.29
+    x, y = synth.random_field(n, 1).astype(np.complex128), synth.random_field(m, 2).astype(np.complex128)
+    du += 0.01 * adjoint  # (tables of its own)
+    first, then = ((y, n), (x, m)) if adjoint else ((x, m), (y, n))
+    fb.mft_f64(_dev(first[0]), n_d, first[1], du, adjoint=adjoint)
+    t = _dev(then[0])
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        out = fb.mft_f64(t, n_d, then[1], du, adjoint=not adjoint)
+    ref = (oracle.mft if adjoint else oracle.mft_adjoint)(then[0], n_d, then[1], du)
+    for _ in range(3):
+        out.zero_()
+        graph.replay()
+        assert rel_l2(_host(out), ref) <= TOL
