@@ -561,13 +561,10 @@ int run_planes(Ctx *ctx, PlaneArgs *args, int count, hipStream_t s) {
   }
   const int nr = int(rest.size());
   for (int i = 0; i < nr;) {
+    int edges[kMrMaxBatch];
     int j = group_end(rest.data(), nr, i, kMrMaxBatch);
-    // one class per launch, and an edge with register-resident sweeps in a launch of its own: a
-    // plane's kernels do not depend on its company (and only those sweeps know radices past 16)
-    auto apart = [](int a, int b) {
-      return mr_class(a) != mr_class(b) || (a != b && (mr_default_plan(a) || mr_default_plan(b)));
-    };
-    while (apart(rest[j - 1].n, rest[i].n)) --j;
+    for (int k = i; k < j; ++k) edges[k - i] = rest[k].n;
+    j = i + mr_launch_count(edges, j - i);
     MrBatch b;
     b.count = j - i;
     b.total = 0;

@@ -110,6 +110,11 @@ hipError_t launch_mr_batch(const MrBatch &all, const int *rows_per_cu, const int
 // classes of the runtime plan's instances by the longest line they hold: 256, 512, 1024, 2048, 4096
 constexpr int kMrClasses = 5;
 int mr_class(int n);
+// of planes ordered by edge, how many from the first on may share a launch
+int mr_launch_count(const int *edges, int count);
+// a packed plan with a radix that the runtime plan's sweeps do not have (launch_mr_batch refuses a
+// launch that would run one)
+bool mr_past_16(unsigned plan);
 // blocks of each instance of the two persistent sweeps that one compute unit holds at once
 // (the runtime plan's classes, then the compile-time plans); a device query, made at context
 // creation

@@ -551,6 +551,22 @@ int mr_class(int n) {
   return c;
 }
 
+// a plane's kernels do not depend on its company, and only the register-resident sweeps know radices
+// past 16: no plane of another class, and none of another edge where either has such sweeps
+int mr_launch_count(const int *edges, int count) {
+  int j = 1;
+  while (j < count && (edges[j] == edges[0] || (mr_class(edges[j]) == mr_class(edges[0]) &&
+                                                !mr_default_plan(edges[j]) && !mr_default_plan(edges[0]))))
+    ++j;
+  return j;
+}
+
+bool mr_past_16(unsigned plan) {
+  for (; plan; plan >>= 5)
+    if ((plan & 31u) > 16u) return true;
+  return false;
+}
+
 void mr_resident(int *rows_per_cu, int *cols_per_cu) {
   static_assert(kMrClasses + kMrCt <= kMrPolicies, "residency table size");
   resident_all(rows_per_cu, cols_per_cu);
@@ -590,12 +606,16 @@ hipError_t launch_mr_batch(const MrBatch &all, const int *rows_per_cu, const int
     if (all.p[i].n != all.p[0].n || all.p[i].plan != all.p[0].plan) pol = -1;
     cls = std::max(cls, mr_class(all.p[i].n));
   }
-  // one register-resident instance when every plane has the same edge and its plan
+  // one register-resident instance when every plane has the same edge and its plan; the others know
+  // radices up to 16 only
   bool same = all.count > 0;
   for (int i = 1; i < all.count && same; ++i)
     if (all.p[i].n != all.p[0].n || all.p[i].plan != all.p[0].plan) same = false;
   const int nr = same ? all.p[0].n : 0;
   const unsigned planr = same ? all.p[0].plan : 0u;
+  if (!with_mr_reg(nr, planr, [](auto) {}))
+    for (int i = 0; i < all.count; ++i)
+      if (mr_past_16(all.p[i].plan)) return hipErrorInvalidValue;
   const int n0 = pol >= 0 ? all.p[0].n : 0;
   const unsigned plan0 = pol >= 0 ? all.p[0].plan : 0u;
   const int idx = pol >= 0 ? kMrClasses + pol : cls;
