@@ -160,6 +160,8 @@ constexpr int kMaxSplit = 16;
 // tile numbers a tuning file may carry (they name complex tiles that the folded product, which
 // picks its tile by shape, has replaced; the split factor beside them is used)
 constexpr int kGemmTiles = 7;
+enum { kFoldGeneral, kFoldShort, kFoldFew };
+int fold_kind(int F, int P, int Q);
 int fold_split_for(const FoldArgs &a);
 int fold_short_tiles(int tiles, int ftiles);
 hipError_t launch_fold(const FoldArgs &a, int split, void *partial, hipStream_t stream, const LaunchHook &hook);

@@ -602,14 +602,16 @@ fold_short_kernel(FoldArgs a, int tiles_per_block) {
   double back = 1.0;
   {
     typename Loader::Regs r0, r1;
-    if (ld.fits && ld.half == kShortPairs) {
-      ld.load(r0, 0);
-      ld.load(r1, kFoldStage);
-      ld.trim(r1, kFoldStage);
-    } else {
-      ld.load_any(r0, 0);
-      ld.load_any(r1, kFoldStage);
-    }
+    auto load = [&](typename Loader::Regs &r, int j0) {
+      if (ld.fits && ld.half >= j0 + kFoldStage) {
+        ld.load(r, j0);
+        ld.trim(r, j0);
+      } else {
+        ld.load_any(r, j0);
+      }
+    };
+    load(r0, 0);
+    load(r1, kFoldStage);
     // the block's data in the range of the pieces (see fold_kernel; here the values themselves tell)
     const unsigned peak = max(ld.peak(r0), ld.peak(r1));
     range_mark(range, wave, lane, peak, unsigned(127 - 70) << 23, unsigned(127 + 100) << 23);
@@ -890,17 +892,18 @@ hipError_t launch_few_kernel(const FoldArgs &a, hipStream_t stream) {
   return hipGetLastError();
 }
 
-// short sums over an output large enough that every wave walks tiles: below that the general
-// kernel's two halves of every stage on different waves are faster (256^2 -> 1024^2 with mask and
-// background 16 us against 37 us, 256^2 -> 2048^2 43 us against 25 us)
-bool short_pairs(const FoldArgs &a) {
-  return a.Q / 2 <= kShortPairs && (long long)fold_tiles(a.P) * div_up(a.F, kFoldFree) >= 1024;
-}
-// one matrix step over a smaller output (from there on the short kernel is the faster: the matrix unit's
-// work hides behind the stores)
-bool few_pairs(const FoldArgs &a) { return a.Q / 2 <= kFewPairs && !short_pairs(a); }
-
 }  // namespace
+
+// Which kernel runs a product. Short sums go to the kernel of their own where the output is large enough
+// that every wave walks tiles: below that the general kernel's two halves of every stage on different waves
+// are faster (256^2 -> 1024^2 with mask and background 16 us general, 37 us short; 256^2 -> 2048^2 43 and
+// 25 us). One matrix step over a smaller output goes to the vector units (over a larger one the matrix
+// unit's work hides behind the stores).
+int fold_kind(int F, int P, int Q) {
+  const int half = Q / 2;
+  if (half <= kShortPairs && (long long)fold_tiles(P) * div_up(F, kFoldFree) >= 1024) return kFoldShort;
+  return half <= kFewPairs ? kFoldFew : kFoldGeneral;
+}
 
 // slices of the pairs: the power of two with the least time by what the kernels measured over
 // edges of 256 to 4096 and 64 to 512 (one block per compute unit at a time): 1.6 us a stage of a
@@ -910,7 +913,7 @@ bool few_pairs(const FoldArgs &a) { return a.Q / 2 <= kFewPairs && !short_pairs(
 // 26, 33; 1024 x 256 21, 25, 25; length 512: 512 x 1024 17, 26, 29); over 100 products of those
 // edges this choice is at most 2 % behind that one and 5 % ahead of it in sum.
 int fold_split_for(const FoldArgs &a) {
-  if (short_pairs(a) || few_pairs(a)) return 1;
+  if (fold_kind(a.F, a.P, a.Q) != kFoldGeneral) return 1;
   const double blocks = double(div_up(fold_tiles(a.P), 2)) * div_up(a.F, kFoldFree);
   const int stages = div_up(a.Q / 2, kFoldStage);
   int best = 1;
@@ -927,7 +930,8 @@ int fold_split_for(const FoldArgs &a) {
 }
 
 hipError_t launch_fold(const FoldArgs &a, int split, void *partial, hipStream_t stream, const LaunchHook &hook) {
-  if (short_pairs(a) || few_pairs(a)) split = 1;  // one group of pairs: nothing to slice
+  const int kind = fold_kind(a.F, a.P, a.Q);
+  if (kind != kFoldGeneral) split = 1;  // one group of pairs: nothing to slice
   FoldParams gp;
   gp.a = a;
   gp.split = split;
@@ -937,9 +941,9 @@ hipError_t launch_fold(const FoldArgs &a, int split, void *partial, hipStream_t 
   char name[64];
   std::snprintf(name, sizeof name, "fold%s_%dx%dx%d_s%d", a.cols ? "C" : "R", a.F, a.P, a.Q, split);
   hook(stream, name, a.Q, 0);
-  hipError_t e = short_pairs(a) ? (a.cols ? launch_short_kernel<true>(a, stream) : launch_short_kernel<false>(a, stream))
-                 : few_pairs(a) ? (a.cols ? launch_few_kernel<true>(a, stream) : launch_few_kernel<false>(a, stream))
-                                : (a.cols ? launch_fold_kernel<true>(gp, stream) : launch_fold_kernel<false>(gp, stream));
+  hipError_t e = kind == kFoldShort ? (a.cols ? launch_short_kernel<true>(a, stream) : launch_short_kernel<false>(a, stream))
+                 : kind == kFoldFew ? (a.cols ? launch_few_kernel<true>(a, stream) : launch_few_kernel<false>(a, stream))
+                                    : (a.cols ? launch_fold_kernel<true>(gp, stream) : launch_fold_kernel<false>(gp, stream));
   hook(stream, name, a.Q, 1);
   if (e != hipSuccess || split == 1) return e;
   hook(stream, "split_reduce", a.Q, 0);

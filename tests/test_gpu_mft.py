@@ -276,3 +276,51 @@ def test_few_pairs_with_mask_background_and_range(m):
     for scale in (1e-35, 1e35):
         got = to_np(fb.mft_adjoint(to_gpu(scale * eb), float(nd), nd, du)) / scale
         assert rel_l2(got, oracle.mft_adjoint(f32(scale * eb) / scale, float(nd), nd, du)) <= 1.5e-6
+
+
+GENERAL, SHORT, FEW = 0, 1, 2
+
+
+def _kernel(f, p, q):
+    return fb.lib()._ZN2fr9fold_kindEiii(f, p, q)
+
+
+# the short sums' kernel along columns: inputs of one stage and of two, whole stages, one pair more and
+# less, odd and even; outputs of whole tiles and ragged, odd and even
+@pytest.mark.parametrize("m,n", [(33, 1999), (64, 2050), (65, 2047), (127, 2048), (128, 1780), (129, 1777), (130, 1601),
+                                 (192, 1600), (255, 1601), (256, 1500), (257, 1500)])
+def test_short_sums_of_large_outputs(m, n):
+    # the bar of test_folded_products_at_tile_edges
+    assert _kernel(n, n, m) == SHORT and _kernel(n, n, 258) == GENERAL
+    banner(f"mft_adjoint {m} -> {n}, short sums")
+    n_d, du = 0.4 * n, 0.37
+    eb = synth.random_field(m, n + m)
+    got = to_np(fb.mft_adjoint(to_gpu(eb), n_d, n, du))
+    assert rel_l2(got, oracle.mft_adjoint(f32(eb), n_d, n, du)) <= 1.5e-6
+
+
+@pytest.mark.parametrize("m", [65, 255])
+def test_short_sums_with_mask_and_background(m):
+    n, nd, du = 1700, 1555, 0.37
+    assert _kernel(nd, nd, m) == SHORT
+    plane, eb, lyot = synth.random_field(n, 13), synth.random_field(m, 14), synth.lyot_stop(nd, 0.9)
+    off = (n - nd) // 2
+    t = to_gpu(plane)
+    fb.mft_adjoint(to_gpu(eb), float(nd), nd, du, alpha=-1.0, beta=1.0, mask=to_gpu(lyot, torch.float32),
+                   out=t[off:off + nd, off:off + nd])
+    want = f32(plane).copy()
+    want[off:off + nd, off:off + nd] = lyot * (want[off:off + nd, off:off + nd]
+                                               - oracle.mft_adjoint(f32(eb), float(nd), nd, du))
+    assert rel_l2(to_np(t), want) <= 1.5e-6
+
+
+@pytest.mark.parametrize("m,n", [(254, 8192), (255, 8191)])
+def test_short_sums_along_rows(m, n):
+    # rows of 255 samples on 8191 outputs, then columns of as many; every 97th row and column of the result
+    assert _kernel(m, n, m) == SHORT and _kernel(n, n, m) == SHORT
+    banner(f"mft_adjoint {m} -> {n}, short sums along rows")
+    n_d, du = 0.4 * n, 0.37
+    eb = synth.random_field(m, n + m)
+    got = to_np(fb.mft_adjoint(to_gpu(eb), n_d, n, du)[::97, ::97].contiguous())
+    w = oracle.mft_matrix(m, n, n_d, du)[:, ::97].conj()
+    assert rel_l2(got, (du / n_d) * w.T @ f32(eb) @ w) <= 1.5e-6
