@@ -324,3 +324,17 @@ def test_short_sums_along_rows(m, n):
     got = to_np(fb.mft_adjoint(to_gpu(eb), n_d, n, du)[::97, ::97].contiguous())
     w = oracle.mft_matrix(m, n, n_d, du)[:, ::97].conj()
     assert rel_l2(got, (du / n_d) * w.T @ f32(eb) @ w) <= 1.5e-6
+
+
+@pytest.mark.parametrize("n,m", [(70, 40), (131, 60)])
+def test_rows_past_32_bit_offsets(n, m):
+    # a window of a plane whose 32 rows span more than 2^31 bytes: every stage element by element
+    ld = (1 << 31) // (8 * 31) + 1
+    assert _kernel(n, m, n) == GENERAL and 31 * ld * 8 >= 1 << 31
+    banner(f"mft_forward {n} -> {m}, rows {ld} elements apart")
+    n_d, du = 0.4 * n, 0.37
+    e = synth.random_field(n, n + m)
+    view = torch.empty((n - 1) * ld + n, dtype=torch.complex64, device="cuda:0").as_strided((n, n), (ld, 1))
+    view.copy_(to_gpu(e))
+    got = to_np(fb.mft_forward(view, n_d, m, du))
+    assert rel_l2(got, oracle.mft(f32(e), n_d, m, du)) <= 1.5e-6
