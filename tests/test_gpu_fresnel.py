@@ -552,3 +552,32 @@ def test_three_pass_plans_in_any_company(n, plan, tmp_path):
     rows = np.fft.ifft(np.fft.fft(f32(field), axis=1) * h, axis=1)[:, [0, 1, n // 2, n - 1]]
     want = np.fft.ifft(np.fft.fft(rows, axis=0) * h[:, None], axis=0)
     assert rel_l2(to_np(one)[:, [0, 1, n // 2, n - 1]], want) <= TOL
+
+
+@pytest.mark.parametrize("n,count", [(4096, 2), (4096, 5), (8192, 2)])
+def test_pipelined_column_tiles_of_shared_launches(n, count, tmp_path):
+    """Large planes share a launch only when a tuning file says so (two are past the last-level cache): their
+    blocks then walk 8, 16 and 32 tiles in place of 4, 4 and 16, with the single call's bits."""
+    banner(f"pipelined column sweep n={n}: {count} planes in one launch")
+    saved, shared = tmp_path / "saved.txt", tmp_path / "shared.txt"
+    fb.autotune_save(str(saved))
+    shared.write_text("sweep %d 0 %d\n" % (n, count))
+    dx, lam, z = 2.5e-5, 550e-9, n / 4096.0
+    g = torch.Generator(device="cuda:0").manual_seed(n + count)
+    fields = [torch.randn((n, n), generator=g, device="cuda:0", dtype=torch.complex64) for _ in range(count)]
+    try:
+        for adjoint in (False, True):
+            fb.autotune_load(str(shared))
+            batch = [f.clone() for f in fields]
+            fb.fresnel_step_batched(batch, dx, lam, z, adjoints=adjoint)
+            shared.write_text("sweep %d 0 0\n" % n)
+            fb.autotune_load(str(shared))
+            for f, got in zip(fields, batch):
+                one = f.clone()
+                fb.fresnel_step(one, dx, lam, z, adjoint=adjoint)
+                assert torch.equal(one, got)
+            shared.write_text("sweep %d 0 %d\n" % (n, count))
+    finally:
+        shared.write_text("sweep %d 0 0\n" % n)
+        fb.autotune_load(str(shared))
+        fb.autotune_load(str(saved))
