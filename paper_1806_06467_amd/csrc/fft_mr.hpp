@@ -44,10 +44,14 @@ __device__ __forceinline__ void mr_pass_r(c32 *lds, int n, int P, const float2 *
         c32 q[R];
 #pragma unroll
         for (int r = 0; r < R; ++r) q[r] = ht.load(unsigned(b) * 8u, unsigned(r * nr) * 8u);
+        // (the sign flipped instead of two products to choose from: with two butterflies a thread, as the
+        // longest lines have, 2 to 7 % of a plane, 2500^2 182 and 175 us; with one it is the slower at 1500^2,
+        // 74 and 83 us)
 #pragma unroll
         for (int r = 0; r < R; ++r) {
           const c32 x = lds[lds_pad(b + r * nr)];
-          u[i][r] = hconj ? cmulc(x, q[r]) : cmul(x, q[r]);
+          if constexpr (MAXN > 2048) u[i][r] = cmul(x, c32{q[r].x, hconj ? -q[r].y : q[r].y});
+          else u[i][r] = hconj ? cmulc(x, q[r]) : cmul(x, q[r]);
         }
       } else {
 #pragma unroll

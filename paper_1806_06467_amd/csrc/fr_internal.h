@@ -103,8 +103,8 @@ void mr_twiddle_build(int npass, const int *radix, float2 *out);  // host
 // rows then columns for forward planes, columns then rows for adjoint planes; persistent grids
 // of cus x the resident blocks per compute unit of the instance that runs them (a compile-time
 // plan when every plane has the same edge and one of the broadband grids' plans, else the
-// runtime plan of the largest edge's class; a caller that gives each class a launch of its own
-// gets the same instance for a plane in any batch)
+// runtime plan of the largest edge's class; mr_launch_count says which edges keep their bits in one
+// launch)
 hipError_t launch_mr_batch(const MrBatch &all, const int *rows_per_cu, const int *cols_per_cu, int cus,
                            hipStream_t s, const LaunchHook &hook);
 // classes of the runtime plan's instances by the longest line they hold: 256, 512, 1024, 2048, 4096

@@ -581,3 +581,25 @@ def test_pipelined_column_tiles_of_shared_launches(n, count, tmp_path):
         shared.write_text("sweep %d 0 0\n" % n)
         fb.autotune_load(str(shared))
         fb.autotune_load(str(saved))
+
+
+@pytest.mark.parametrize("edges", [(250, 270), (100, 500, 500, 1000, 1875), (255, 256, 257, 512, 520, 1029, 2025),
+                                   (250, 1000, 2058, 3000), (225, 600, 3888, 3969, 4050)])
+def test_mixed_edges_keep_the_single_planes_bits(edges):
+    """Planes of any classes of line lengths in one call, both directions and with maps: each has the bits of
+    its own call, whichever instance its launch takes."""
+    edges = [n if fb.lib().fr_fft_size_supported(n) else max(m for m in range(2, n) if fb.lib().fr_fft_size_supported(m))
+             for n in edges]
+    banner(f"mixed edges {edges}")
+    g = torch.Generator(device="cuda:0").manual_seed(sum(edges))
+    fields = [torch.randn((n, n), generator=g, device="cuda:0", dtype=torch.complex64) for n in edges]
+    amps = [0.5 + 0.5 * torch.rand((n, n), generator=g, device="cuda:0") for n in edges]
+    opds = [5e-8 * torch.randn((n, n), generator=g, device="cuda:0") for n in edges]
+    dx, lam, zs = 2.5e-5, 550e-9, [n / 4096.0 for n in edges]
+    for adjoints in ([False] * len(edges), [True] * len(edges), [i % 2 == 1 for i in range(len(edges))]):
+        batch = [f.clone() for f in fields]
+        fb.fresnel_step_batched(batch, dx, lam, zs, amps=amps, opds=opds, lens_focals=[2.0] * len(edges), adjoints=adjoints)
+        for n, f, amp, opd, z, adj, got in zip(edges, fields, amps, opds, zs, adjoints, batch):
+            one = f.clone()
+            fb.fresnel_step(one, dx, lam, z, amp=amp, opd=opd, lens_focal=2.0, adjoint=adj)
+            assert torch.equal(one, got), n

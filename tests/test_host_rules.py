@@ -41,7 +41,8 @@ def test_register_resident_edges_share_a_launch_with_none():
         assert run(e, 4050, 4050) == 1 and run(e, e, 4050) == 2 and run(e) == 1
         assert run(2058, e) == 1 and run(e, e, e) == 3
     assert run(2058, 3375, 3969, 4050) == 4
-    assert run(250, 256, 257, 500) == 2 and run(500, 600) == 1
+    # the classes of line lengths up to 2048 give the same bits in one launch, the largest does not
+    assert run(250, 256, 257, 500, 1000, 2025) == 6 and run(250, 2058) == 1 and run(1000, 2025, 2058, 2100) == 2
 
 
 def test_packed_plans_past_radix_16():
