@@ -32,13 +32,13 @@ struct PassOut {
     const int i0 = (b / P) * (P * R) + (b % P);
     base = lds_pad(i0);
   }
-  // valid when P % 16 == 0 (the pad of i0 + rP is pad(i0) + 17 rP/16), or P == 1 with i0 = b R and
-  // 16 % R == 0 (then (b R + r) / 16 = b R / 16 for r < R) or R % 16 == 0
+  // valid when P % 16 == 0 (the pad of i0 + rP is pad(i0) + 17 rP/16), or P == 1 and 16 % R == 0 with
+  // i0 = b R (then (b R + r) / 16 = b R / 16 for r < R)
   __device__ __forceinline__ static constexpr int off(int r) {
     if constexpr (P % 16 == 0) return r * (P + P / 16);
-    return r + r / 16;  // P == 1
+    return r;  // P == 1
   }
-  static constexpr bool exact = (P % 16 == 0) || (P == 1 && (16 % R == 0 || R % 16 == 0));
+  static constexpr bool exact = (P % 16 == 0) || (P == 1 && 16 % R == 0);
 };
 
 // Twiddles of one pass for the NB butterflies a thread owns: leg r of butterfly b is

@@ -910,8 +910,9 @@ int fold_kind(int F, int P, int Q) {
 // round of blocks, and for a split 4 us for the pass that adds the slices and the slices' bytes
 // written and read at 3 TB/s. A slice for every idle compute unit, at least 128 pairs deep, was
 // too many for the middle sizes (us at 1, 2, 4 slices, input length 1024: 1024 x 512 outputs 22,
-// 26, 33; 1024 x 256 21, 25, 25; length 512: 512 x 1024 17, 26, 29); over 100 products of those
-// edges this choice is at most 2 % behind that one and 5 % ahead of it in sum.
+// 26, 33; 1024 x 256 21, 25, 25; length 512: 512 x 1024 17, 26, 29); over the 96 products of
+// those edges that the general kernel runs this choice is at most 2 % behind that one and 5 % ahead of it
+// in sum (2469 us against 2589 us, the best choice of each 2458 us).
 int fold_split_for(const FoldArgs &a) {
   if (fold_kind(a.F, a.P, a.Q) != kFoldGeneral) return 1;
   const double blocks = double(div_up(fold_tiles(a.P), 2)) * div_up(a.F, kFoldFree);

@@ -143,11 +143,9 @@ __device__ __forceinline__ bool pre_optic_row(const PlaneArgs &pa, int n, int y,
   return true;
 }
 
-// G: slots whose factors are loaded together (the pipelined column sweep holds two tiles' elements
-// and takes a few at a time)
 // v times the post optic exp(2 pi i 2 post_surf / lambda) (its conjugate for the adjoint) at rows
-// y = t + T m of column x: the map (4-column tiles) is read for a group of slots before their
-// phasors are formed
+// y = t + T m of column x: the map (4-column tiles) is read for a group of G slots before their
+// phasors are formed (the pipelined column sweep holds two tiles' elements and takes a few at a time)
 template <int G, int E, int T>
 __device__ __forceinline__ void post_optic_col(const PlaneArgs &pa, int n, int t, int x, bool adj, c32 (&v)[E]) {
   const MapBuf map(pa.post_surf, unsigned(post_tiled_size(n)) * 4u);
@@ -549,11 +547,6 @@ __global__ void __launch_bounds__(PL::T *LINES) __attribute__((amdgpu_waves_per_
   }
 }
 
-// Forward planes run the row sweep first (optic prologue on contiguous rows) and the column
-// sweep second (mirror epilogue); adjoint planes run the column sweep first (conjugate mirror
-// prologue) and the row sweep second (conjugate optic epilogue). The two halves of the
-// angular-spectrum step commute, so only the placement of the optics sets the order, and the
-// amplitude/OPD maps are always read along rows.
 // blocks per plane of the pipelined column sweep: as many as run at once (1024 threads per compute
 // unit at its 128 registers) when `count` planes share the launch, a power of two so that a block's
 // tiles are whole runs of 128-byte lines
@@ -567,6 +560,11 @@ int pipe_blocks(int count) {
   return b;
 }
 
+// Forward planes run the row sweep first (optic prologue on contiguous rows) and the column
+// sweep second (mirror epilogue); adjoint planes run the column sweep first (conjugate mirror
+// prologue) and the row sweep second (conjugate optic epilogue). The two halves of the
+// angular-spectrum step commute, so only the placement of the optics sets the order, and the
+// amplitude/OPD maps are always read along rows.
 // PF > 0: the column sweep is the pipelined one with PF elements of the next tile in flight
 template <class PL, int ROW_LINES, int COL_LINES, int PF = 0, bool DIRECT = false>
 hipError_t launch_sweeps(const BatchArgs &fwd, int nf, const BatchArgs &adj, int na,
@@ -661,7 +659,9 @@ hipError_t launch_fresnel_batch(const PlaneArgs *planes, int count, int n, const
   // them 87 us and 51 us, a 1024^2 plane 32 us with 4 and 8 and 23 us. From 2048 the column tile
   // fills half a compute unit or more and the pipelined sweep wins: a 2048^2 plane 54 us with 2
   // rows and 8 columns, 45 us; the 4096^2 column sweeps 92 and 115 us to 83 and 100 us (forward,
-  // adjoint), the 8192^2 ones 877 us to 705 us.
+  // adjoint), the 8192^2 ones 877 us to 705 us. The direct, the exact and the float64 steps take tiles as
+  // small up to 1024 (512^2 18, 29 and 21 us with the larger tiles, 12, 15 and 17 us), and so do large
+  // batches (42 planes of 1024^2, a paraxial step 441 us and 381 us, an exact one 513 us and 443 us).
 #define FR_SWEEPS(...) return launch_sweeps<__VA_ARGS__>(fwd, nf, adj, na, root, s, hook)
   switch (n) {
     case 64: {

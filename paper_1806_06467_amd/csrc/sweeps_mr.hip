@@ -13,8 +13,9 @@
 // transform's first and last passes, as in the power-of-two sweeps) runs instead, one row or
 // 4-column tile per block, when every plane of the launch has that edge and its plan.
 //
-// All global accesses use raw buffer instructions with a per-lane offset clamped inside the
-// array, so every access is range-checked by the hardware.
+// All accesses to fields and maps use raw buffer instructions whose per-lane offset the hardware checks
+// against the array (lines past a plane read 0 and store nothing). The tables' buffers (MrTable) carry no
+// length of their own: their offsets follow from the plan.
 #include <algorithm>
 #include <tuple>
 #include <type_traits>
