@@ -55,16 +55,16 @@ METRIC = "Fresnel planes/sec at 4096^2 c64 (fwd+adjoint, batched vs plain), %HBM
 # 128 MiB plane in the same runs (FETCH x 2.0, WRITE x 1.0). Each entry carries the SHA-256 of the
 # sources it was measured on and reads as unknown (null) once they change.
 MEASURED_TRAFFIC = {
-    "row_sweep": (269239296, 134217728),
-    "col_sweep": (135023002, 154492928),
-    "col_sweep_adj": (135195238, 180686848),
-    "row_sweep_adj": (269254656, 134217728),
+    "row_sweep": (269239091, 134217728),
+    "col_sweep": (135056384, 154291507),
+    "col_sweep_adj": (135103078, 180376576),
+    "row_sweep_adj": (269266125, 134217728),
 }
 _SWEEP_SOURCES = {
-    "paper_1806_06467_amd/csrc/sweeps.hip": "726b2f6fbc97d952eabf4e011c18a1f564916502d66cb9d5be55df4d8c73b733",
-    "paper_1806_06467_amd/csrc/fft_line.hpp": "2857c2ea32366f810489c8996516adef2f3dc3b714bd3af9c253186f1d7e054b",
+    "paper_1806_06467_amd/csrc/sweeps.hip": "0d5c1a02e105a5e004888124414a872f495468731b4dae30ef857516fd2b5643",
+    "paper_1806_06467_amd/csrc/fft_line.hpp": "14f143735094b54e7c5afd5d7322dbbb3eae544ebd0113e61fb6316d6990dbc5",
     "paper_1806_06467_amd/csrc/dft_small.hpp": "7157a77cda1cf2817549098695764b1f3452b199107a6d3d90b27a06a2e0cb9d",
-    "paper_1806_06467_amd/csrc/fr_internal.h": "0db5afa7b5400da9b0f13ee468c63b24704c0c43fb39e5819f382e9c3e54288b",
+    "paper_1806_06467_amd/csrc/fr_internal.h": "2e9c9bd09140d291fdf65e1de4cf1f97edb086d94e1535199063000584294565",
 }
 TRAFFIC_SOURCES = {k: _SWEEP_SOURCES for k in MEASURED_TRAFFIC}
 

@@ -398,8 +398,8 @@ int propagate_train(fr_ctx *ctx, const fr_train_desc *desc, int32_t n_lambda,
  * a hot loop or a graph capture. Errors: FR_EINVAL, FR_EUNSUPPORTED, FR_ENOMEM, FR_EHIP.
  * fr_autotune_save / fr_autotune_load write / read the tuned choices as a text file (one
  * "sweep n variant [planes]" (variant: 0 the default tiles; 1 and 2 at 2048 and 8192, 1 to 3 at 4096
- * other tiles with the same results bit for bit, whose sizes may differ from those a file of an earlier
- * library was tuned on; planes: the power-of-two sweeps' planes per launch in batched calls,
+ * other tiles, at 4096 with the same bits; a file of an earlier library may have been tuned on tiles of
+ * other sizes under the same numbers; planes: the power-of-two sweeps' planes per launch in batched calls,
  * 1..64, or 0 = as many as fit the last-level cache together), "plan n packed_order" (the
  * edge's default plan, or radices 2-10, 12, 14, 15 or 16, 5 bits each from the first pass up, at most
  * 6, product n),

@@ -459,6 +459,9 @@ constexpr int kMrCt = std::tuple_size<MrCtPlans>::value;
 // threads, 392 on 140, 400 on 200, 288 on 168) and large first and last radices: 3888 120 / 121 us
 // against 159 / 147 for the greedy compile-time plan, 3920 169 / 130 against 174 / 183, 4000 179 /
 // 135 against 180 / 159, 4032 132 / 133 against 165 / 204 for 9.16.14.2.
+// The edges are the grids that a broadband model on 4096^2 pads its wavelengths to: every 7-smooth multiple
+// of 16 from 7/8 of 4096 up. Other edges run the runtime plan (a rule over all edges that have such a
+// factorisation would need instances with the edge at run time).
 // These orders are the edges' default plans (mr_default_plan; the last entry of 4032 is the one
 // that older tuning files name); a tuning file may choose another.
 using MrRegPlans = std::tuple<MrReg<3584, 14, 7, 16, 16, 2>, MrReg<3600, 15, 15, 16, 15>,
